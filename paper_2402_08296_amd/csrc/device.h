@@ -61,6 +61,29 @@ struct TileNode {
 };
 static_assert(sizeof(TileNode) == 16, "tile record layout");
 
+// Arrays of the tiled DSS forward in one precision (dss_tile.hip): an in-edge
+// (sender's tile lane, distance) per edge row and node of a tile, the per-tile
+// latent states, and the two sender-row buffers.
+template <typename T>
+struct VtRec;
+template <>
+struct VtRec<float> {
+    int32_t src;
+    float nd;
+};
+template <>
+struct VtRec<double> {
+    int32_t src, pad;
+    double nd;
+};
+template <typename T>
+struct VtVecs {
+    const VtRec<T>* rec;
+    T* info;  // FP32: per tile and node (x, y, in-degree, c); FP64: unused
+    T* h;     // per tile and lane: three components, and (FP64) c or the in-degree
+    T* q[2];  // 20 values per tile lane; the last row is the sentinel (-inf)
+};
+
 // Device view of one problem (all pointers device memory).
 struct DevProb {
     // matrix, right-hand side, boundary
@@ -83,6 +106,11 @@ struct DevProb {
     const TileNode* tiles;      // per slot position in tile order (e0 indexes erec)
     const double* xy64;         // per slot, raw coordinates
     const float* xyc32;         // per slot, sub-mesh-centred coordinates
+    // tiles of 16 nodes of the FP64 and FP32 DSS forward (width 10; null until its first use)
+    const int32_t* vt_ptr;      // [K + 1] tiles of each sub-mesh
+    const int2* vt_node;        // per tile and lane: slot (-1: none), in-degree
+    VtVecs<double> vt64;
+    VtVecs<float> vt32;
     const int32_t* node_ptr;    // per node, range of its slots
     const int32_t* node_slots;
     const int32_t* slot_sub;

@@ -1,0 +1,73 @@
+// The FP64 and FP32 DSS forward in launches of one message-passing block each,
+// over tiles of 16 nodes (dss_tile.hip): weight blobs and launchers. Host part
+// in plain C++.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <vector>
+
+#include "device.h"
+
+namespace ddmgnn {
+
+constexpr int VT_TILE = 16;   // nodes of a tile (the N dimension of the matrix instructions)
+constexpr int VT_BLOCK = 256; // threads of the setup kernels
+constexpr int64_t VT_MAX_FP32 = 48 * 1024;  // most tiles of an FP32 launch in this form
+constexpr int VT_ROWS = 8;    // edge rows read at a time (the array is padded by as many)
+
+// Values per lane of one block's blob: matrix operands, then per-lane constants.
+// The blobs are stored in chunks of 16 bytes per lane ([chunk][lane][16 bytes]).
+template <typename T>
+struct VtLayout;
+template <>
+struct VtLayout<double> {
+    // receiver part of the first message layers (units 0-3 of every lane, unit 4), Psi's hidden
+    // layer (h and c, deg: 3 steps; message sums: 5), Psi's output layer
+    static constexpr int P16 = 0, P4 = 3, HID = 6, N_HID = 8, OUT = 14;
+    static constexpr int CP = 17, CP4 = 21, CH = 22, CO = 25, WN = 28, N_MAIN = 34;
+    // sender part
+    static constexpr int Q16 = 0, Q4 = 3, N_Q = 6;
+    // decoder
+    static constexpr int DH = 0, DO = 3, CDH = 6, CDO = 9, N_DEC = 10;
+};
+template <>
+struct VtLayout<float> {
+    // as above, with the second message layers (FO, FI) and the coordinate weights (WX, WY)
+    static constexpr int P16 = 0, P4 = 3, FO = 6, FI = 9, HID = 12, N_HID = 9, OUT = 21;
+    static constexpr int CP = 24, CP4 = 28, WX = 29, WY = 34, WN = 39, CCO = 44, CCI = 47, CH = 50, CO = 53,
+                         N_MAIN = 56;
+    static constexpr int Q16 = 0, Q4 = 3, QX = 6, QY = 11, N_Q = 16;
+    static constexpr int DH = 0, DO = 3, CDH = 6, CDO = 9, N_DEC = 12;
+};
+
+// Device weights: kbar main blobs, kbar sender blobs, one decoder blob, back to back.
+template <typename T>
+struct VtBlobs {
+    static constexpr size_t MAIN = (size_t)VtLayout<T>::N_MAIN * 64, Q = (size_t)VtLayout<T>::N_Q * 64,
+                            DEC = (size_t)VtLayout<T>::N_DEC * 64;
+    static size_t size(int kbar) { return (size_t)kbar * (MAIN + Q) + DEC; }
+};
+// theta: kbar blocks of the width-10 model (Table II layout).
+void build_vt_blobs(const float* theta, int kbar, std::vector<double>& b64, std::vector<float>& b32);
+
+// Tile of a problem: first slot of its sub-mesh, first position of the tile in
+// it, first edge row, edge rows (the tile's largest in-degree).
+using VtTile = int4;
+// Fills the nodes (slot or -1, in-degree) and slot positions, and the edge records
+// (sentinel sender: 16 n_tiles) in one precision (the other null).
+hipError_t launch_vt_build(const DevProb* tab, const VtTile* info, int n_tiles, int2* node, int32_t* pos,
+                           VtRec<float>* rec32, VtRec<double>* rec64, hipStream_t s);
+// Fills n values with v (the sentinel rows and the padding).
+hipError_t launch_vt_fill(double* p, int64_t n, double v, hipStream_t s);
+hipError_t launch_vt_fill(float* p, int64_t n, float v, hipStream_t s);
+
+// One DSS forward over n_tiles tiles of the sub-meshes in subs: the restriction
+// (apply) with the first sender rows, kbar block launches. tiles: (problem,
+// tile, first edge row, edge rows). solo: every item is of problem 0.
+template <typename T>
+hipError_t launch_dss_tiles(const DevProb* tab, const int2* subs, int n_subs, const int4* tiles, int n_tiles,
+                            bool solo, int kbar, double alpha, int apply, const T* blobs, hipStream_t s, bool check);
+
+}  // namespace ddmgnn

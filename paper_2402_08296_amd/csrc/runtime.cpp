@@ -43,6 +43,11 @@ struct Batch {
     int n_mfma_small = 0;
     size_t lds_mfma = 0, lds_mfma_small = 0;
     int max_k_all = 0, max_k_rest = 0, max_k_valu = 0;
+    // tiles of work_valu and work_rest for the tiled FP64 / FP32 forward (d = 10), by
+    // problem and sub-mesh; built at the first use
+    DevBuf<int4> tiles_valu, tiles_rest;
+    int n_tiles_valu = 0, n_tiles_rest = 0;
+    int64_t vt_valu = 0, vt_rest = 0;  // tiles the lists hold once built
     DevBuf<int2> vec_blk;              // (problem, local workgroup)
     int n_vec = 0;
     DevBuf<int2> coarse_rows;          // (problem, row)
@@ -71,6 +76,10 @@ DevProb make_view(ddmgnn_problem* P) {
     v.edge_ptr = P->edge_ptr.p; v.edge_src = P->edge_src.p; v.edge_nd = P->edge_nd.p; v.erec = P->erec.p;
     v.epad_sub = P->epad_sub.p;
     v.tiles = P->tiles.p; v.xy64 = P->xy64.p; v.xyc32 = P->xyc32.p;
+    v.vt_ptr = P->vt_ptr.p; v.vt_node = P->vt_node.p;
+    const size_t qn = (P->vt_tiles.size() * VT_TILE + 1) * 2 * D;
+    v.vt64 = {P->vt64.rec.p, P->vt64.info.p, P->vt64.h.p, {P->vt64.q.p, P->vt64.q.p ? P->vt64.q.p + qn : nullptr}};
+    v.vt32 = {P->vt32.rec.p, P->vt32.info.p, P->vt32.h.p, {P->vt32.q.p, P->vt32.q.p ? P->vt32.q.p + qn : nullptr}};
     v.node_ptr = P->node_ptr.p; v.node_slots = P->node_slots.p; v.slot_sub = P->slot_sub.p; v.a0inv = P->a0inv.p;
     v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p;
     v.gm_v = P->gm_v.p; v.gm_z = P->gm_z.p; v.gm_part = P->gm_part.p; v.gm_small = P->gm_small.p;
@@ -264,6 +273,95 @@ int prepare_fgmres(Batch& B, int R, bool& changed) {
     return DDMGNN_OK;
 }
 
+// Whether a launch of `tiles` tiles of 16 nodes of a width-d model runs the tiled forward
+// (dss_tile.hip): every FP64 one, and the FP32 ones of up to VT_MAX_FP32 tiles. Larger FP32 launches fill the
+// chip with one workgroup per sub-mesh, whose sender rows stay in LDS, while the tiled
+// form's pass through HBM (537k slots, 34k tiles: 1,176 against 1,462 us per forward;
+// 1.35M slots, 85k tiles: 3,480 against 3,160). Both give the same bits. Other widths
+// and sub-meshes beyond kMaxSubNodes run the kernels of kernels.hip.
+bool runs_tiled(int d, int precision, int64_t tiles) {
+    return d == D && (precision == DDMGNN_FP64 || tiles <= VT_MAX_FP32);
+}
+
+// Tiles of the sub-meshes of at most kMaxSubNodes nodes: their nodes by decreasing
+// in-degree (tnode), so a tile's edge rows are its first node's in-degree (made even: rows
+// are summed in pairs).
+void list_tiles(ddmgnn_problem* P) {
+    if (!P->vt_first.empty()) return;
+    const auto& hs = P->hs;
+    P->vt_first.assign((size_t)hs.K + 1, 0);
+    int64_t rows = 0;
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int64_t b = hs.sub_ptr[i], k = hs.sub_ptr[i + 1] - b;
+        if (k <= kMaxSubNodes)
+            for (int64_t q = 0; q < k; q += VT_TILE) {
+                const int64_t slot = b + hs.tnode[b + q];
+                const int64_t deg = (hs.edge_ptr[slot + 1] - hs.edge_ptr[slot] + 1) & ~int64_t(1);
+                P->vt_tiles.push_back(make_int4((int)b, (int)q, (int)rows, (int)deg));
+                rows += deg;
+            }
+        P->vt_first[i + 1] = (int32_t)P->vt_tiles.size();
+    }
+    P->vt_rows = rows;
+}
+
+// Builds the arrays of P's tiled forward in type T (hook: a one-problem table to build with).
+template <typename T>
+int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, DevBuf<DevProb>& hook, bool& changed) {
+    if (V.q.p) return DDMGNN_OK;
+    hipStream_t s = P->ctx->stream;
+    list_tiles(P);
+    const int64_t sk = P->hs.sk, nt = (int64_t)P->vt_tiles.size(), rows = P->vt_rows + VT_ROWS;
+    if (rows * VT_TILE >= INT32_MAX || nt * VT_TILE >= INT32_MAX)
+        return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
+    const size_t er = (size_t)rows * VT_TILE, pad = (size_t)VT_ROWS * VT_TILE, qn = (size_t)(nt * VT_TILE + 1) * 2 * D;
+    if (!P->vt_pos.p) {
+        HIP_TRY(P->vt_info.upload(P->vt_tiles.data(), (size_t)nt, s));
+        HIP_TRY(P->vt_ptr.upload(P->vt_first.data(), P->vt_first.size(), s));
+        HIP_TRY(P->vt_node.alloc((size_t)nt * VT_TILE));
+        HIP_TRY(P->vt_pos.alloc((size_t)sk));
+    }
+    constexpr bool f64 = sizeof(T) == 8;
+    HIP_TRY(V.rec.alloc(er));
+    HIP_TRY(hipMemsetAsync(V.rec.p + er - pad, 0, pad * sizeof(VtRec<T>), s));
+    if (!f64) HIP_TRY(V.info.alloc((size_t)nt * VT_TILE * 4));
+    HIP_TRY(V.h.alloc((size_t)nt * 64 * 4));
+    DevBuf<T> q;  // moved in last: a failed build is retried whole
+    HIP_TRY(q.alloc(2 * qn));
+    const T inf = std::numeric_limits<T>::infinity();
+    HIP_TRY(launch_vt_fill(q.p + qn - 2 * D, 2 * D, -inf, s));
+    HIP_TRY(launch_vt_fill(q.p + 2 * qn - 2 * D, 2 * D, -inf, s));
+    const DevProb v = make_view(P);
+    HIP_TRY(upload_async(hook.p, &v, sizeof(v), s));
+    HIP_TRY(launch_vt_build(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, P->vt_pos.p,
+                            f64 ? nullptr : reinterpret_cast<VtRec<float>*>(V.rec.p),
+                            f64 ? reinterpret_cast<VtRec<double>*>(V.rec.p) : nullptr, s));
+    std::swap(V.q.p, q.p);
+    std::swap(V.q.n, q.n);
+    P->device_bytes += tile_bytes(sk, nt, P->vt_rows, f64);
+    changed = true;
+    return DDMGNN_OK;
+}
+
+// Tile list of a batch: the tiles of the sub-meshes `take` accepts, by problem and sub-mesh.
+template <class F>
+int upload_tiles(Batch& B, DevBuf<int4>& buf, int& n, F take) {
+    if (n) return DDMGNN_OK;
+    std::vector<int4> v;
+    for (size_t p = 0; p < B.probs.size(); ++p) {
+        const ddmgnn_problem* P = B.probs[p];
+        for (int32_t i = 0; i < P->hs.K; ++i) {
+            if (!take(P, i)) continue;
+            for (int32_t t = P->vt_first[i]; t < P->vt_first[i + 1]; ++t)
+                v.push_back(make_int4((int)p, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
+        }
+    }
+    if (v.size() > (size_t)INT32_MAX) return fail(DDMGNN_E_INVALID, "too many tiles in one batch");
+    if (int rc = upload_list(buf, v, B.ctx->stream)) return rc;
+    n = (int)v.size();
+    return DDMGNN_OK;
+}
+
 // Allocates what the DSS launches of this precision need (fallback storage,
 // LDS attributes). Not allowed during stream capture; returns true in
 // `changed` when a problem's buffers moved (the table must be re-uploaded).
@@ -302,6 +400,17 @@ int prepare_dss(Batch& B, int precision, bool& changed) {
     const int max_k = bf16 ? B.max_k_rest : B.max_k_valu;
     const int n_valu = bf16 ? B.n_rest : B.n_valu;
     if (n_valu == 0) return DDMGNN_OK;
+    if (runs_tiled(d, valu_prec, bf16 ? B.vt_rest : B.vt_valu)) {
+        for (ddmgnn_problem* P : B.probs) {
+            if (bf16 && !any_valu_bf16(P)) continue;
+            const int rc = f64 ? prepare_tiles(P, P->vt64, B.hook, changed) : prepare_tiles(P, P->vt32, B.hook, changed);
+            if (rc) return rc;
+        }
+        if (bf16)
+            return upload_tiles(B, B.tiles_rest, B.n_tiles_rest,
+                                [](const ddmgnn_problem* P, int32_t i) { return !mfma_runs_sub(P, i); });
+        return upload_tiles(B, B.tiles_valu, B.n_tiles_valu, [](const ddmgnn_problem*, int32_t) { return true; });
+    }
     const bool in_lds = valu_q_in_lds(max_k, valu_prec, d);
     for (ddmgnn_problem* P : B.probs) {
         if (bf16 && !any_valu_bf16(P)) continue;
@@ -356,10 +465,23 @@ int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool cap
             a.work = B.work_mfma_small.p;
             HIP_TRY(launch_dss_mfma(a, B.n_mfma_small, B.lds_mfma_small, MFMA_SMALL_BLOCK, s, check));
         }
+        if (runs_tiled(M.d, DDMGNN_FP32, B.vt_rest)) {
+            HIP_TRY(launch_dss_tiles<float>(tab, B.work_rest.p, B.n_rest, B.tiles_rest.p, B.n_tiles_rest,
+                                            B.probs.size() == 1, M.kbar, M.alpha, apply, M.vt32.p, s, check));
+            return DDMGNN_OK;
+        }
         const bool qlds = valu_q_in_lds(B.max_k_rest, DDMGNN_FP32, M.d);
         HIP_TRY(launch_dss_valu(tab, B.work_rest.p, B.n_rest, DDMGNN_FP32, M.d, qlds, M.kbar, M.alpha, apply,
                                 M.theta32.p, M.theta64.p, qlds ? valu_shmem(B.max_k_rest, DDMGNN_FP32, M.d) : 0, s,
                                 check));
+    } else if (runs_tiled(M.d, precision, B.vt_valu)) {
+        const bool solo = B.probs.size() == 1;
+        if (precision == DDMGNN_FP64)
+            HIP_TRY(launch_dss_tiles<double>(tab, B.work_valu.p, B.n_valu, B.tiles_valu.p, B.n_tiles_valu, solo, M.kbar,
+                                             M.alpha, apply, M.vt64.p, s, check));
+        else
+            HIP_TRY(launch_dss_tiles<float>(tab, B.work_valu.p, B.n_valu, B.tiles_valu.p, B.n_tiles_valu, solo, M.kbar,
+                                            M.alpha, apply, M.vt32.p, s, check));
     } else {
         const bool qlds = valu_q_in_lds(B.max_k_valu, precision, M.d);
         HIP_TRY(launch_dss_valu(tab, B.work_valu.p, B.n_valu, precision, M.d, qlds, M.kbar, M.alpha, apply,
@@ -638,6 +760,8 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         }
         wv.push_back(make_int2(w.p, w.sub));
         B->max_k_valu = std::max(B->max_k_valu, w.k);
+        const int64_t vt = (w.k + VT_TILE - 1) / VT_TILE;
+        B->vt_valu += vt;
         if (mfma_runs_sub(Q, w.sub)) {
             const size_t need = Q->mfma_need[w.sub];
             // Each launch reserves the largest need of its members; with two Q'
@@ -656,6 +780,7 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         } else {
             wr.push_back(make_int2(w.p, w.sub));
             B->max_k_rest = std::max(B->max_k_rest, w.k);
+            B->vt_rest += vt;
         }
     }
     B->lds_mfma = std::max(lds_sb, lds_db);
@@ -823,6 +948,22 @@ int check_opts(const ddmgnn_solve_opts& o) {
     if (o.prolong < 0 || o.prolong > 1) return fail(DDMGNN_E_INVALID, "prolong must be POU or UNWEIGHTED");
     if (o.local_solver < 0 || o.local_solver > 1) return fail(DDMGNN_E_INVALID, "local_solver must be GNN or LU");
     return DDMGNN_OK;
+}
+
+// Bytes of the tiled DSS forward's arrays of a problem in one precision (`tiles` tiles,
+// `rows` edge rows).
+size_t tile_bytes(int64_t sk, int64_t tiles, int64_t rows, bool f64) {
+    const size_t e = f64 ? 8 : 4;
+    return (size_t)tiles * (16 + VT_TILE * 8 + (f64 ? 0 : 16 * VT_TILE) + 256 * e) + (size_t)sk * 4 +
+           (size_t)(rows + VT_ROWS) * VT_TILE * 2 * e + (size_t)(tiles * VT_TILE + 1) * 4 * D * e;
+}
+
+// The same for a problem that has not listed its tiles: a tile has at most 15 empty
+// lanes per sub-mesh, and its edge rows at most one more than its nodes' largest
+// in-degree, which its nodes (by decreasing in-degree) have but for the last few.
+size_t tile_bytes_bound(const HostSetup& hs, bool f64) {
+    const int64_t tiles = hs.sk / VT_TILE + hs.K;
+    return tile_bytes(hs.sk, tiles, hs.n_edges / VT_TILE + 3 * tiles, f64);
 }
 
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t ne) {
@@ -1173,6 +1314,13 @@ int ddmgnn_model_create(ddmgnn_ctx* ctx, const ddmgnn_model_desc* desc, const fl
     dev->mfma = d <= D;
     dev->alpha = m->alpha;
     hipStream_t s = ctx->stream;
+    if (d == D) {
+        std::vector<double> b64;
+        std::vector<float> b32;
+        build_vt_blobs(m->theta.data(), m->kbar, b64, b32);
+        HIP_TRY(dev->vt64.upload(b64.data(), b64.size(), s));
+        HIP_TRY(dev->vt32.upload(b32.data(), b32.size(), s));
+    }
     std::vector<double> th64(m->theta.begin(), m->theta.end());
     HIP_TRY(dev->theta32.upload(m->theta.data(), m->theta.size(), s));
     HIP_TRY(dev->theta64.upload(th64.data(), th64.size(), s));
@@ -1480,6 +1628,17 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
         DssMfmaArgs a{B.hook.p, P->one_work.p, M.steps.p, M.dec.p, M.kbar, (float)M.alpha, 0};
         const size_t shmem = P->mfma_need_db[sub] <= MFMA_LDS_LIMIT ? P->mfma_need_db[sub] : P->mfma_need[sub];
         HIP_TRY(launch_dss_mfma(a, 1, shmem, MFMA_BLOCK, s, true));
+    } else if (runs_tiled(M.d, vprec, precision == DDMGNN_BF16 ? B.vt_rest : B.vt_valu)) {  // as prepare_dss
+        std::vector<int4> tl;
+        for (int32_t t = P->vt_first[sub]; t < P->vt_first[sub + 1]; ++t)
+            tl.push_back(make_int4(0, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
+        if (int rc = upload_list(P->one_tiles, tl, s)) return rc;
+        if (vprec == DDMGNN_FP64)
+            HIP_TRY(launch_dss_tiles<double>(B.hook.p, P->one_work.p, 1, P->one_tiles.p, (int)tl.size(), true, M.kbar,
+                                             M.alpha, 0, M.vt64.p, s, true));
+        else
+            HIP_TRY(launch_dss_tiles<float>(B.hook.p, P->one_work.p, 1, P->one_tiles.p, (int)tl.size(), true, M.kbar,
+                                            M.alpha, 0, M.vt32.p, s, true));
     } else {
         const int mk = precision == DDMGNN_BF16 ? B.max_k_rest : B.max_k_valu;  // as prepare_dss sized it
         const bool qlds = valu_q_in_lds(mk, vprec, M.d);

@@ -13,6 +13,7 @@
 #include "ddmgnn.h"
 #include "device.h"
 #include "dss_mfma.h"
+#include "dss_tile.h"
 #include "setup.h"
 
 namespace ddmgnn {
@@ -68,6 +69,15 @@ struct ModelDev {
     DevBuf<double> theta64;
     DevBuf<MfmaStep> steps;
     DevBuf<MfmaDec> dec;
+    DevBuf<double> vt64;  // blobs of the tiled FP64 / FP32 forward (d = 10)
+    DevBuf<float> vt32;
+};
+
+// Device arrays of a problem's tiled DSS forward in one precision.
+template <typename T>
+struct VtBufs {
+    DevBuf<VtRec<T>> rec;
+    DevBuf<T> info, h, q;
 };
 
 struct Batch;
@@ -79,6 +89,10 @@ using BatchPtr = std::unique_ptr<Batch, BatchDeleter>;
 // Bytes of device memory a problem of these sizes holds (all buffers of a
 // solve, excluding the DSS fallback storage of sub-meshes too large for LDS).
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t n_edges);
+// Bytes of the tiled DSS forward's arrays in one precision: exactly, and an estimate
+// before the tiles are listed.
+size_t tile_bytes(int64_t sk, int64_t tiles, int64_t rows, bool f64);
+size_t tile_bytes_bound(const HostSetup& hs, bool f64);
 
 // Creates a problem from a validated descriptor and its host setup (moved in).
 // Fills the device-ready host arrays of hs (plain host work; "" or an error).
@@ -190,6 +204,16 @@ struct ddmgnn_problem {
     // one-sub-mesh forward entry: per-slot input and output, and its one-item work list
     ddmgnn::DevBuf<double> fwd_in, fwd_out;
     ddmgnn::DevBuf<int2> one_work;
+    // tiles of the FP64 and FP32 DSS forward (built at the first use of either)
+    std::vector<ddmgnn::VtTile> vt_tiles;  // host: per tile
+    std::vector<int32_t> vt_first;         // host: [K + 1] tiles of each sub-mesh
+    int64_t vt_rows = 0;                   // edge rows of all tiles
+    ddmgnn::DevBuf<ddmgnn::VtTile> vt_info;
+    ddmgnn::DevBuf<int32_t> vt_ptr, vt_pos;
+    ddmgnn::DevBuf<int2> vt_node;
+    ddmgnn::VtBufs<double> vt64;
+    ddmgnn::VtBufs<float> vt32;
+    ddmgnn::DevBuf<int4> one_tiles;        // tiles of the one-sub-mesh forward entry
     // apply buffers
     ddmgnn::DevBuf<double> s, y0, y, local;
     ddmgnn::DevBuf<double> qglobal64, hglobal64;

@@ -178,6 +178,11 @@ void ddmgnn_server::setup_worker() {
                 }
             r->bytes = problem_device_bytes(r->hs.n, r->hs.nnz, r->hs.K, r->hs.sk, r->hs.n_edges) + lu_bytes +
                        (r->opts.krylov == DDMGNN_FGMRES ? fgmres_bytes(r->hs.n, r->opts.restart) : 0);
+            // The FP64 and FP32 forward's work arrays count too, but a request that fits
+            // the budget without them is still taken: it then runs alone.
+            if (!lu && r->opts.krylov != DDMGNN_CG && r->opts.precision != DDMGNN_BF16 &&
+                model->d == D && r->bytes <= budget)
+                r->bytes = std::min<size_t>(budget, r->bytes + tile_bytes_bound(r->hs, r->opts.precision == DDMGNN_FP64));
         }
         r->t_setup1 = Clock::now();
         std::lock_guard<std::mutex> lk(mu);

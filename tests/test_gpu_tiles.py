@@ -1,0 +1,109 @@
+"""GPU: the tiled FP64 and FP32 DSS forward (tiles of 16 nodes, eight edge rows at a time).
+
+Where it can go wrong: a sub-mesh of fewer nodes than a tile, tiles with empty
+lanes, in-degrees around and beyond the eight rows read at a time, and the two
+forms a launch can take (FP32 launches of more than 48k tiles run one workgroup
+per sub-mesh). The bars are those of the parity tests: relative 1e-12 (FP64,
+reordered sums) and 3e-5 (FP32) of the largest output.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import paper_2402_08296_amd as dg  # noqa: E402
+import workload as W  # noqa: E402
+from oracle import decomp as dc, dss  # noqa: E402
+from tests._cases import oracle_problem  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+XAVIER = W.xavier_theta(W.THETA_SEED)
+SMOOTHER = W.smoother_theta(omega=0.15, out_scale=1.7)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    print("[gpu] creating context", flush=True)
+    return dg.Context()
+
+
+def _fan(m):
+    """A hub inside two rings of m nodes, the outer one Dirichlet: the hub has m in-edges,
+    and the sub-mesh 1 + 2m nodes. The matrix is the graph Laplacian of the free nodes."""
+    a = 2 * np.pi * np.arange(m) / m
+    ring = np.stack([np.cos(a), np.sin(a)], 1)
+    xy = np.concatenate([[[0.1, -0.05]], ring, 2.3 * ring])
+    i, j = np.arange(m), (np.arange(m) + 1) % m
+    tri = np.concatenate([np.stack([0 * i, 1 + i, 1 + j], 1), np.stack([1 + i, 1 + m + i, 1 + m + j], 1),
+                          np.stack([1 + i, 1 + m + j, 1 + j], 1)]).astype(np.int32)
+    n = 1 + 2 * m
+    dirichlet = np.zeros(n, np.uint8)
+    dirichlet[1 + m:] = 1
+    A = np.zeros((n, n))
+    for t in tri:
+        for p in t:
+            for q in t:
+                if p != q:
+                    A[p, q] = -1.0
+    A[np.arange(n), np.arange(n)] = -A.sum(1)
+    A[dirichlet == 1] = A[:, dirichlet == 1] = 0.0
+    A[dirichlet == 1, dirichlet == 1] = 1.0
+    row, col = np.nonzero(A)
+    rowptr = np.searchsorted(row, np.arange(n + 1)).astype(np.int32)
+    return dg.HostProblem(xy, tri, dirichlet, rowptr, col, A[row, col], 1.0 - dirichlet, np.zeros(n),
+                          np.array([0, n]), np.arange(n), 1.0 - dirichlet)
+
+
+@pytest.mark.parametrize("m", [3, 7, 8, 9, 16, 17, 40])
+def test_forward_at_tile_and_row_edges(ctx, m):
+    print(f"[gpu] fan of {m}", flush=True)
+    hp = _fan(m)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, XAVIER))
+    c = np.random.default_rng(m).standard_normal(hp.n)
+    c /= np.linalg.norm(c)
+    ref = dss.forward(dss.unpack(XAVIER, 30, 10), dc.local_graph(np.arange(hp.n), hp.tri.reshape(-1, 3), hp.xy, hp.dirichlet),
+                      c, 1e-3, 10)
+    cd = torch.tensor(c, device="cuda")
+    for prec, tol in (("fp64", 1e-12), ("fp32", 3e-5)):
+        out, one = torch.empty_like(cd), torch.empty_like(cd)
+        prob.dss_forward(cd, out, prec)
+        prob.dss_forward_sub(0, cd, one, prec)
+        assert torch.equal(out, one)
+        assert np.abs(out.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
+
+
+def test_fp32_forms_give_the_same_bits(ctx):
+    """130 copies of a 5k-node problem are more tiles than the tiled form takes: their FP32
+    solves run one workgroup per sub-mesh and equal the solo (tiled) solve bit for bit."""
+    p = W.config_problem("c1", 0)
+    hp = oracle_problem(p)
+    tiles = int(((np.diff(hp.sub_ptr) + 15) // 16).sum())
+    assert tiles < 48 * 1024 < 130 * tiles
+    model = dg.Model(ctx, SMOOTHER)
+    opts = dg.default_opts(precision="fp32", rtol=1e-6, max_it=500)
+    probs = [dg.Problem(ctx, hp, model) for _ in range(130)]
+    outs = [torch.empty(p.n, dtype=torch.float64, device="cuda") for _ in probs]
+    solo = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    st = probs[0].solve(solo, opts)
+    print(f"[gpu] solo {st.iterations} iterations, {tiles} tiles", flush=True)
+    for s, u in zip(dg.solve_batch(ctx, probs, outs, opts), outs):
+        assert s.converged and s.iterations == st.iterations and torch.equal(u, solo)
+
+
+def test_zero_residual_and_repeat(ctx):
+    """A sub-mesh where the residual vanishes has a zero local term; a second apply repeats the first."""
+    p = W.make_problem(205, 3000, 4, 0.2)
+    hp = oracle_problem(p)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, XAVIER))
+    r = np.random.default_rng(3).standard_normal(p.n)
+    r[p.mesh.dirichlet == 1] = 0.0
+    r[hp.sub_nodes[hp.sub_ptr[1]:hp.sub_ptr[2]]] = 0.0
+    rd = torch.tensor(r, device="cuda")
+    for prec in ("fp64", "fp32"):
+        z = [torch.empty_like(rd) for _ in range(2)]
+        for v in z:
+            prob.apply(rd, v, dg.default_opts(precision=prec))
+        s, _, _, loc = prob.intermediates()
+        assert torch.equal(z[0], z[1]) and s[1] == 0.0 and torch.isfinite(z[0]).all()
+        assert not loc[hp.sub_ptr[1]:hp.sub_ptr[2]].any() and loc.any()
