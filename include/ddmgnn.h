@@ -346,9 +346,9 @@ int ddmgnn_train_rhs(ddmgnn_ctx* ctx, ddmgnn_problem* prob, const double* u, flo
  * gradient is deterministic (fixed-order sums; no atomics). *loss_out and
  * *gnorm_out (host, may be NULL) receive the loss (FP64 sum of the FP32
  * residuals) and |grad|_2. The first call builds the local matrices and edge
- * transposes on the device. Samples run in launches of 512 that share one
- * scratch region of about 4 (kbar + 33) d k_i bytes per sample of a launch, plus
- * 4 kbar(11d^2+15d+1) bytes per sample for the per-sample gradients. The
+ * records on the device. Samples run in chunks of up to 32768 tiles of 16 nodes
+ * (about 500 samples of 1000 nodes) that share one scratch region of about
+ * 4 kbar kilobytes per tile. The
  * problem's training buffers serve one call at a time: calls on one problem from
  * several threads must be serialised. E_NONFINITE when the loss or the gradient
  * overflows. */

@@ -269,41 +269,83 @@ constexpr int NOALLOC_SCRATCH_DOUBLES = VEC_GRID;  // the dot product's partial 
 hipError_t noalloc_init(int device);
 double* noalloc_scratch(int device);
 
-// Training of DSS_theta (train.hip): one TRAIN_BLOCK-thread workgroup per local
-// problem; TRAIN_NWB weights per block (d = D).
-constexpr int TRAIN_BLOCK = 1024;
-constexpr int TRAIN_NWB = 11 * D * D + 15 * D + 1;
-struct TrainArgs {
-    const int32_t* sub_ptr;
-    const int32_t* edge_ptr;   // per slot, in-edge range
-    const uint16_t* edge_src;  // per in-edge, sender local id
-    const float* edge_nd;      // per in-edge, |d|
-    const double* xy64;        // per slot, coordinates
-    const int32_t* lm_ptr;     // per slot, range of its row of A_i = R_i A R_i^T
-    const uint16_t* lm_col;    // local column
-    const float* lm_val;
+// Training of DSS_theta (train.hip), in tiles of 16 nodes of all samples (d = D).
+constexpr int TRAIN_BLOCK = 1024;                       // threads of the reductions
+constexpr int TRAIN_NWB = 11 * D * D + 15 * D + 1;      // weights per block
+constexpr int TRAIN_BLOB = (56 + 16 + 12 + 32 + 28) * 64;  // values of a block's blob
+constexpr int TRAIN_ACC = 56;                           // accumulators per lane of the backward pass
+// An edge of a tile's node: the other end's tile lane of the problem (-1: none),
+// d = x_send - x_recv and |d|.
+struct TrainEdge {
+    int32_t node;
+    float dx, dy, nd;
+};
+// Where a weight's gradient lies in the accumulators of a backward launch: that of its
+// block, or the next one (edges); the sum of `lanes` consecutive values.
+struct TrainEntry {
+    int32_t at;
+    int16_t lanes;
+    int8_t edges, negative;
+};
+struct TrainEdgeArgs {
+    const int4* info;          // tiles of the problem (dss_tile.h)
+    const int2* out_rows;      // per tile: first out-edge row, rows
+    int n_tiles;
+    const int2* node;          // per tile lane: slot (-1: none), in-degree
+    const int32_t* pos;        // per slot, its tile lane
+    const int32_t* edge_ptr;
+    const uint16_t* edge_src;
+    const float* edge_nd;
     const int32_t* oe_ptr;     // per slot, range of its out-edges
     const int32_t* oe_edge;    // the in-edge index of each out-edge
     const uint16_t* oe_recv;   // its receiver's local id
-    const int32_t* subs;       // per sample: sub-mesh,
-    const int64_t* c_off;      // offset of its right-hand side in c,
-    const int64_t* s_off;      // offset of its scratch
-    const float* c;
-    const float* theta;        // kbar blocks of TRAIN_NWB weights
-    float* scratch;
-    float* gpart;              // per sample, kbar * TRAIN_NWB weight gradients
-    double* sse;               // per sample, sum of squared residuals over the blocks
-    int kbar;
-    float alpha;
-    int s0;                    // first sample of this launch (workgroup b takes sample s0 + b)
+    const double* xy64;        // per slot, coordinates
+    TrainEdge* rin;
+    TrainEdge* rout;
 };
-// Samples per launch of the training kernel: launches reuse one scratch region.
-constexpr int TRAIN_CHUNK = 512;
-int64_t train_scratch_floats(int kbar, int64_t k);
-hipError_t launch_train_grad(const TrainArgs& a, int n, hipStream_t s);
-// grad = scale * sum over samples of gpart; out2[0] = |grad|^2, out2[1] = sum of sse.
-hipError_t launch_train_reduce(const float* gpart, int n, int64_t nth, double scale, float* grad, double* out2,
-                               const double* sse, hipStream_t s);
+struct TrainArgs {
+    // tiles of the samples: (tile of the problem, batch lane - problem lane, first in-edge
+    // row, rows), (first out-edge row, rows, offset of the right-hand side in c)
+    const int4* items;
+    int n_tiles;
+    int kbar;
+    int ks;                    // values per tile lane in r, rho and gr (>= kbar)
+    float alpha;
+    const int4* info;
+    const int2* node;
+    const int32_t* pos;
+    const TrainEdge* rin;
+    const TrainEdge* rout;
+    const int32_t* lm_ptr;     // per slot, range of its row of A_i = R_i A R_i^T
+    const uint16_t* lm_col;    // local column
+    const float* lm_val;
+    const float* c;
+    const float* blobs;        // per block, TRAIN_BLOB values
+    float* blobs_out;          // the same, written first
+    float2* in;                // per tile lane: c, in-degree
+    float* h;                  // [kbar + 1] latent states of every tile
+    float* q;                  // [kbar] sender rows (20 per tile lane and a sentinel)
+    float* m;                  // [kbar] message hidden sums
+    float* r;                  // decoded states, residuals, dL/dr: per tile lane, ks blocks
+    float* rho;
+    float* gr;
+    float* pg[2];              // receiver rows: receiver part and message gradient
+    float* own;                // the same in lane order, with dL/dH
+    float* part;               // per backward launch and workgroup, its accumulators
+    double* sse;               // per workgroup of the residual kernel
+};
+// Most tiles of the samples run together: they share one scratch region.
+constexpr int64_t TRAIN_TILES = 32768;
+void build_train_maps(std::vector<int32_t>& map, std::vector<TrainEntry>& ent);
+int64_t train_sse_count(int64_t tiles, int ks);
+int train_workgroups(int64_t tiles);
+hipError_t launch_train_edges(const TrainEdgeArgs& a, hipStream_t s);
+// Forward, backward and the accumulators' sums in red ([kbar + 1][TRAIN_ACC * 64], added to when `add`).
+hipError_t launch_train_grad(const TrainArgs& a, const float* theta, const int32_t* map, double* red, bool add,
+                             hipStream_t s);
+// grad = scale * the sums; out2[0] = |grad|^2, out2[1] = sum of sse.
+hipError_t launch_train_reduce(const double* red, const TrainEntry* ent, int kbar, double scale, float* grad,
+                               double* out2, const double* sse, int n_sse, hipStream_t s);
 hipError_t launch_adam(float* theta, const float* grad, float* m, float* v, int64_t n, float gscale, float lr,
                        float b1, float b2, float bc1, float bc2, float eps, hipStream_t s);
 // r = b - A u, then c = R_i r / |R_i r| per sub-mesh (slot order).

@@ -52,12 +52,20 @@ struct VtBlobs {
 // theta: kbar blocks of the width-10 model (Table II layout).
 void build_vt_blobs(const float* theta, int kbar, std::vector<double>& b64, std::vector<float>& b32);
 
+// The FP32 main, sender and decoder blobs of one block given by its TRAIN_NWB values
+// (training passes positions instead of weights and gathers by them).
+void build_vt_maps(const float* one_block, std::vector<float>& main, std::vector<float>& sender,
+                   std::vector<float>& dec);
+
 // Tile of a problem: first slot of its sub-mesh, first position of the tile in
 // it, first edge row, edge rows (the tile's largest in-degree).
 using VtTile = int4;
-// Fills the nodes (slot or -1, in-degree) and slot positions, and the edge records
-// (sentinel sender: 16 n_tiles) in one precision (the other null).
-hipError_t launch_vt_build(const DevProb* tab, const VtTile* info, int n_tiles, int2* node, int32_t* pos,
+// Fills the nodes (slot or -1, in-degree) of every tile and the slots' tile lanes (P's
+// base arrays from *tab); the edge records (sentinel sender: 16 n_tiles) in one
+// precision (the other null).
+hipError_t launch_vt_nodes(const DevProb* tab, const VtTile* info, int n_tiles, int2* node, int32_t* pos,
+                           hipStream_t s);
+hipError_t launch_vt_edges(const DevProb* tab, const VtTile* info, int n_tiles, const int2* node, const int32_t* pos,
                            VtRec<float>* rec32, VtRec<double>* rec64, hipStream_t s);
 // Fills n values with v (the sentinel rows and the padding).
 hipError_t launch_vt_fill(double* p, int64_t n, double v, hipStream_t s);

@@ -181,64 +181,6 @@ int prepare_lu(ddmgnn_problem* P) {
     return DDMGNN_OK;
 }
 
-// Training structures of a problem: per slot, its row of A_i = R_i A R_i^T
-// (local columns, ascending) and the in-edges it sends (ordered by edge index).
-int prepare_train(ddmgnn_problem* P) {
-    if (P->lm_ptr.p) return DDMGNN_OK;
-    hipStream_t s = P->ctx->stream;
-    const auto& hs = P->hs;
-    std::vector<int32_t> rowptr(hs.n + 1), col(hs.nnz), sub_nodes(hs.sk);
-    std::vector<double> val(hs.nnz);
-    HIP_TRY(hipMemcpyAsync(rowptr.data(), P->rowptr.p, rowptr.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(col.data(), P->col.p, col.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(val.data(), P->val.p, val.size() * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(sub_nodes.data(), P->sub_nodes.p, sub_nodes.size() * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    std::vector<int32_t> lm_ptr(hs.sk + 1, 0), oe_ptr(hs.sk + 1, 0), oe_edge(std::max<int64_t>(hs.n_edges, 1));
-    std::vector<uint16_t> lm_col, oe_recv(std::max<int64_t>(hs.n_edges, 1));
-    std::vector<float> lm_val;
-    lm_col.reserve((size_t)hs.sk * 7);
-    lm_val.reserve((size_t)hs.sk * 7);
-    for (int32_t i = 0; i < hs.K; ++i) {
-        const int64_t b = hs.sub_ptr[i], e = hs.sub_ptr[i + 1];
-        const int32_t* first = sub_nodes.data() + b;
-        const int32_t* last = sub_nodes.data() + e;
-        for (int64_t q = b; q < e; ++q) {
-            const int32_t j = sub_nodes[q];
-            for (int32_t a = rowptr[j]; a < rowptr[j + 1]; ++a) {
-                const int32_t* f = std::lower_bound(first, last, col[a]);
-                if (f == last || *f != col[a]) continue;
-                lm_col.push_back((uint16_t)(f - first));
-                lm_val.push_back((float)val[a]);
-            }
-            lm_ptr[q + 1] = (int32_t)lm_col.size();
-        }
-        for (int64_t q = b; q < e; ++q)
-            for (int64_t t = hs.edge_ptr[q]; t < hs.edge_ptr[q + 1]; ++t) oe_ptr[b + hs.edge_src[t] + 1]++;
-    }
-    if (lm_col.size() >= (size_t)INT32_MAX) return fail(DDMGNN_E_INVALID, "local matrices too large");
-    for (int64_t q = 0; q < hs.sk; ++q) oe_ptr[q + 1] += oe_ptr[q];
-    std::vector<int32_t> fill(oe_ptr.begin(), oe_ptr.end() - 1);
-    for (int32_t i = 0; i < hs.K; ++i) {
-        const int64_t b = hs.sub_ptr[i], e = hs.sub_ptr[i + 1];
-        for (int64_t q = b; q < e; ++q)
-            for (int64_t t = hs.edge_ptr[q]; t < hs.edge_ptr[q + 1]; ++t) {
-                const int32_t at = fill[b + hs.edge_src[t]]++;
-                oe_edge[at] = (int32_t)t;
-                oe_recv[at] = (uint16_t)(q - b);
-            }
-    }
-    HIP_TRY(P->lm_ptr.upload(lm_ptr.data(), lm_ptr.size(), s));
-    HIP_TRY(P->lm_col.upload(lm_col.data(), std::max<size_t>(lm_col.size(), 1), s));
-    HIP_TRY(P->lm_val.upload(lm_val.data(), std::max<size_t>(lm_val.size(), 1), s));
-    HIP_TRY(P->oe_ptr.upload(oe_ptr.data(), oe_ptr.size(), s));
-    HIP_TRY(P->oe_edge.upload(oe_edge.data(), oe_edge.size(), s));
-    HIP_TRY(P->oe_recv.upload(oe_recv.data(), oe_recv.size(), s));
-    P->device_bytes += lm_ptr.size() * 4 + lm_col.size() * 2 + lm_val.size() * 4 + oe_ptr.size() * 4 +
-                       oe_edge.size() * 6;
-    return DDMGNN_OK;
-}
-
 // Whether the BF16 MFMA kernel runs sub-mesh `sub` of P (the model has the
 // paper's latent width and the sub-mesh fits the kernel's node and LDS budgets).
 bool mfma_runs_sub(const ddmgnn_problem* P, int sub) {
@@ -305,6 +247,26 @@ void list_tiles(ddmgnn_problem* P) {
     P->vt_rows = rows;
 }
 
+// The nodes of P's tiles and the slots' tile lanes (hook: a one-problem table to build
+// with, left holding P).
+int prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
+    hipStream_t s = P->ctx->stream;
+    list_tiles(P);
+    const size_t nt = P->vt_tiles.size();
+    const DevProb v = make_view(P);
+    HIP_TRY(upload_async(hook.p, &v, sizeof(v), s));
+    if (P->vt_pos.p) return DDMGNN_OK;
+    HIP_TRY(P->vt_info.upload(P->vt_tiles.data(), nt, s));
+    HIP_TRY(P->vt_ptr.upload(P->vt_first.data(), P->vt_first.size(), s));
+    HIP_TRY(P->vt_node.alloc(nt * VT_TILE));
+    DevBuf<int32_t> pos;  // moved in last: a failed build is retried whole
+    HIP_TRY(pos.alloc((size_t)P->hs.sk));
+    HIP_TRY(launch_vt_nodes(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, pos.p, s));
+    std::swap(P->vt_pos.p, pos.p);
+    std::swap(P->vt_pos.n, pos.n);
+    return DDMGNN_OK;
+}
+
 // Builds the arrays of P's tiled forward in type T (hook: a one-problem table to build with).
 template <typename T>
 int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, DevBuf<DevProb>& hook, bool& changed) {
@@ -315,12 +277,7 @@ int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, DevBuf<DevProb>& hook, bool& 
     if (rows * VT_TILE >= INT32_MAX || nt * VT_TILE >= INT32_MAX)
         return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
     const size_t er = (size_t)rows * VT_TILE, pad = (size_t)VT_ROWS * VT_TILE, qn = (size_t)(nt * VT_TILE + 1) * 2 * D;
-    if (!P->vt_pos.p) {
-        HIP_TRY(P->vt_info.upload(P->vt_tiles.data(), (size_t)nt, s));
-        HIP_TRY(P->vt_ptr.upload(P->vt_first.data(), P->vt_first.size(), s));
-        HIP_TRY(P->vt_node.alloc((size_t)nt * VT_TILE));
-        HIP_TRY(P->vt_pos.alloc((size_t)sk));
-    }
+    if (int rc = prepare_tile_nodes(P, hook)) return rc;
     constexpr bool f64 = sizeof(T) == 8;
     HIP_TRY(V.rec.alloc(er));
     HIP_TRY(hipMemsetAsync(V.rec.p + er - pad, 0, pad * sizeof(VtRec<T>), s));
@@ -331,15 +288,115 @@ int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, DevBuf<DevProb>& hook, bool& 
     const T inf = std::numeric_limits<T>::infinity();
     HIP_TRY(launch_vt_fill(q.p + qn - 2 * D, 2 * D, -inf, s));
     HIP_TRY(launch_vt_fill(q.p + 2 * qn - 2 * D, 2 * D, -inf, s));
-    const DevProb v = make_view(P);
-    HIP_TRY(upload_async(hook.p, &v, sizeof(v), s));
-    HIP_TRY(launch_vt_build(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, P->vt_pos.p,
+    HIP_TRY(launch_vt_edges(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, P->vt_pos.p,
                             f64 ? nullptr : reinterpret_cast<VtRec<float>*>(V.rec.p),
                             f64 ? reinterpret_cast<VtRec<double>*>(V.rec.p) : nullptr, s));
     std::swap(V.q.p, q.p);
     std::swap(V.q.n, q.n);
     P->device_bytes += tile_bytes(sk, nt, P->vt_rows, f64);
     changed = true;
+    return DDMGNN_OK;
+}
+
+int solo_batch(ddmgnn_problem* P);
+
+// Training structures of a problem: per slot, its row of A_i = R_i A R_i^T
+// (local columns, ascending), and per tile lane its edges in both directions (those it
+// sends ordered by edge index).
+int prepare_train(ddmgnn_problem* P) {
+    if (P->lm_ptr.p) return DDMGNN_OK;
+    hipStream_t s = P->ctx->stream;
+    const auto& hs = P->hs;
+    std::vector<int32_t> rowptr(hs.n + 1), col(hs.nnz), sub_nodes(hs.sk);
+    std::vector<double> val(hs.nnz);
+    HIP_TRY(hipMemcpyAsync(rowptr.data(), P->rowptr.p, rowptr.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(col.data(), P->col.p, col.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(val.data(), P->val.p, val.size() * 8, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(sub_nodes.data(), P->sub_nodes.p, sub_nodes.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    std::vector<int32_t> lm_ptr(hs.sk + 1, 0), oe_ptr(hs.sk + 1, 0), oe_edge(std::max<int64_t>(hs.n_edges, 1));
+    std::vector<uint16_t> lm_col, oe_recv(std::max<int64_t>(hs.n_edges, 1));
+    std::vector<float> lm_val;
+    lm_col.reserve((size_t)hs.sk * 7);
+    lm_val.reserve((size_t)hs.sk * 7);
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int64_t b = hs.sub_ptr[i], e = hs.sub_ptr[i + 1];
+        const int32_t* first = sub_nodes.data() + b;
+        const int32_t* last = sub_nodes.data() + e;
+        for (int64_t q = b; q < e; ++q) {
+            const int32_t j = sub_nodes[q];
+            for (int32_t a = rowptr[j]; a < rowptr[j + 1]; ++a) {
+                const int32_t* f = std::lower_bound(first, last, col[a]);
+                if (f == last || *f != col[a]) continue;
+                lm_col.push_back((uint16_t)(f - first));
+                lm_val.push_back((float)val[a]);
+            }
+            lm_ptr[q + 1] = (int32_t)lm_col.size();
+        }
+        for (int64_t q = b; q < e; ++q)
+            for (int64_t t = hs.edge_ptr[q]; t < hs.edge_ptr[q + 1]; ++t) oe_ptr[b + hs.edge_src[t] + 1]++;
+    }
+    if (lm_col.size() >= (size_t)INT32_MAX) return fail(DDMGNN_E_INVALID, "local matrices too large");
+    for (int64_t q = 0; q < hs.sk; ++q) oe_ptr[q + 1] += oe_ptr[q];
+    std::vector<int32_t> fill(oe_ptr.begin(), oe_ptr.end() - 1);
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int64_t b = hs.sub_ptr[i], e = hs.sub_ptr[i + 1];
+        for (int64_t q = b; q < e; ++q)
+            for (int64_t t = hs.edge_ptr[q]; t < hs.edge_ptr[q + 1]; ++t) {
+                const int32_t at = fill[b + hs.edge_src[t]]++;
+                oe_edge[at] = (int32_t)t;
+                oe_recv[at] = (uint16_t)(q - b);
+            }
+    }
+    // Tiles (dss_tile.h), their out-edge rows and the edge records of both directions.
+    list_tiles(P);
+    const size_t nt = P->vt_tiles.size();
+    std::vector<int2> out_rows(nt);
+    int64_t rows = 0;
+    for (size_t t = 0; t < nt; ++t) {
+        const VtTile f = P->vt_tiles[t];
+        const int64_t k = hs.sub_ptr[hs.slot_sub[f.x] + 1] - f.x;
+        int32_t deg = 0;
+        for (int64_t q = f.y; q < std::min<int64_t>(k, f.y + VT_TILE); ++q) {
+            const int64_t slot = f.x + hs.tnode[f.x + q];
+            deg = std::max(deg, oe_ptr[slot + 1] - oe_ptr[slot]);
+        }
+        deg = (deg + 1) & ~1;  // rows are summed in pairs
+        out_rows[t] = make_int2((int)rows, deg);
+        rows += deg;
+    }
+    if ((rows + VT_ROWS) * VT_TILE >= INT32_MAX || (P->vt_rows + VT_ROWS) * VT_TILE >= INT32_MAX)
+        return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
+    if (int rc = solo_batch(P)) return rc;
+    if (int rc = prepare_tile_nodes(P, P->solo->hook)) return rc;
+    std::vector<int32_t> map;
+    std::vector<TrainEntry> ent;
+    build_train_maps(map, ent);
+    DevBuf<int32_t> oe_edge_d, oe_ptr_d;
+    DevBuf<uint16_t> oe_recv_d;
+    HIP_TRY(oe_ptr_d.upload(oe_ptr.data(), oe_ptr.size(), s));
+    HIP_TRY(oe_edge_d.upload(oe_edge.data(), oe_edge.size(), s));
+    HIP_TRY(oe_recv_d.upload(oe_recv.data(), oe_recv.size(), s));
+    HIP_TRY(P->tr_map.upload(map.data(), map.size(), s));
+    HIP_TRY(P->tr_ent.upload(ent.data(), ent.size(), s));
+    HIP_TRY(P->tr_orows.upload(out_rows.data(), nt, s));
+    const size_t ni = (size_t)(P->vt_rows + VT_ROWS) * VT_TILE, no = (size_t)(rows + VT_ROWS) * VT_TILE;
+    HIP_TRY(P->tr_rin.alloc(ni));
+    HIP_TRY(P->tr_rout.alloc(no));
+    // the rows past the last tile are read, not looked at
+    HIP_TRY(hipMemsetAsync(P->tr_rin.p, 0, ni * sizeof(TrainEdge), s));
+    HIP_TRY(hipMemsetAsync(P->tr_rout.p, 0, no * sizeof(TrainEdge), s));
+    const TrainEdgeArgs ea{P->vt_info.p, P->tr_orows.p, (int)nt, P->vt_node.p, P->vt_pos.p, P->edge_ptr.p,
+                           P->edge_src.p, P->edge_nd.p, oe_ptr_d.p, oe_edge_d.p, oe_recv_d.p, P->xy64.p,
+                           P->tr_rin.p, P->tr_rout.p};
+    HIP_TRY(launch_train_edges(ea, s));
+    HIP_TRY(P->lm_val.upload(lm_val.data(), lm_val.size(), s));
+    HIP_TRY(P->lm_col.upload(lm_col.data(), lm_col.size(), s));
+    HIP_TRY(hipStreamSynchronize(s));  // before the temporaries go
+    P->tr_out_rows = std::move(out_rows);
+    HIP_TRY(P->lm_ptr.upload(lm_ptr.data(), lm_ptr.size(), s));  // last: says that all is there
+    P->device_bytes += lm_ptr.size() * 4 + lm_col.size() * 2 + lm_val.size() * 4 + map.size() * 4 +
+                       ent.size() * sizeof(TrainEntry) + nt * sizeof(int2) + (ni + no) * sizeof(TrainEdge);
     return DDMGNN_OK;
 }
 
@@ -1902,42 +1959,86 @@ int ddmgnn_train_grad(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_model_des
     if (md->kbar < 1 || md->kbar > 64) return fail(DDMGNN_E_INVALID, "kbar must be in 1..64");
     if (n < 1) return fail(DDMGNN_E_INVALID, "at least one sample required");
     if (!(scale >= 0.0) || !std::isfinite(scale)) return fail(DDMGNN_E_INVALID, "scale must be finite and >= 0");
-    // scratch offsets restart with every chunk of TRAIN_CHUNK samples (one launch each)
-    std::vector<int64_t> soff((size_t)n);
-    int64_t total = 0, used = 0;
     for (int32_t i = 0; i < n; ++i) {
         if (subs[i] < 0 || subs[i] >= P->hs.K) return fail(DDMGNN_E_INVALID, "sub-mesh index out of range");
         if (P->hs.sub_ptr[subs[i] + 1] - P->hs.sub_ptr[subs[i]] > kMaxSubNodes)
             return fail(DDMGNN_E_INVALID, "training samples are limited to sub-meshes of at most 2048 nodes");
         if (c_off[i] < 0) return fail(DDMGNN_E_INVALID, "negative right-hand side offset");
-        if (i % TRAIN_CHUNK == 0) used = 0;
-        soff[(size_t)i] = used;
-        used += train_scratch_floats(md->kbar, P->hs.sub_ptr[subs[i] + 1] - P->hs.sub_ptr[subs[i]]);
-        total = std::max(total, used);
     }
     if (int rc = prepare_train(P)) return rc;
+    // Tiles of all samples; chunks of whole samples share the scratch region.
+    std::vector<int4> items;
+    std::vector<int32_t> chunk{0};  // first tile of each chunk, and the end
+    int64_t most = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const int32_t t0 = P->vt_first[subs[i]], t1 = P->vt_first[subs[i] + 1];
+        int64_t first = (int64_t)items.size() / 2;
+        if (first + (t1 - t0) >= INT32_MAX / 2) return fail(DDMGNN_E_INVALID, "too many samples");
+        if (first > chunk.back() && first - chunk.back() + (t1 - t0) > TRAIN_TILES) chunk.push_back((int32_t)first);
+        first -= chunk.back();  // within the chunk
+        for (int32_t t = t0; t < t1; ++t) {
+            const VtTile f = P->vt_tiles[t];
+            const int2 o = P->tr_out_rows[t];
+            items.push_back(make_int4(t, (int)(first - t0) * VT_TILE, f.z, f.w));
+            items.push_back(make_int4(o.x, o.y, (int)(uint32_t)(uint64_t)c_off[i], (int)(uint32_t)((uint64_t)c_off[i] >> 32)));
+        }
+        most = std::max(most, first + (t1 - t0));
+    }
+    chunk.push_back((int32_t)(items.size() / 2));
+    const int kb = md->kbar, ks = (kb + 3) / 4 * 4;
     hipStream_t s = ctx->stream;
-    const int64_t nth = (int64_t)md->kbar * TRAIN_NWB;
-    if (P->tr_scratch.n < (size_t)total) HIP_TRY(P->tr_scratch.alloc((size_t)total));
-    if (P->tr_gpart.n < (size_t)(n * nth)) HIP_TRY(P->tr_gpart.alloc((size_t)(n * nth)));
-    if (P->tr_subs.n < (size_t)n) {
-        HIP_TRY(P->tr_subs.alloc((size_t)n));
-        HIP_TRY(P->tr_coff.alloc((size_t)n));
-        HIP_TRY(P->tr_soff.alloc((size_t)n));
-        HIP_TRY(P->tr_sse.alloc((size_t)n));
-    }
+    // scratch, in floats: blobs, inputs, states, sender rows, sums, r, rho, gr, receiver rows, own values, accumulators
+    const size_t T = (size_t)most, lanes = T * VT_TILE;
+    const size_t parts[] = {(size_t)kb * TRAIN_BLOB, 2 * lanes, (size_t)(kb + 1) * T * 256,
+                            (size_t)kb * (lanes + 1) * 2 * D, (size_t)kb * T * 320, lanes * ks, lanes * ks, lanes * ks,
+                            (lanes + 1) * 4 * D, (lanes + 1) * 4 * D, T * 1024,
+                            (size_t)(kb + 1) * train_workgroups(most) * TRAIN_ACC * 64};
+    constexpr int NP = sizeof(parts) / sizeof(parts[0]);
+    size_t off[NP + 1] = {0};
+    for (int i = 0; i < NP; ++i) off[i + 1] = off[i] + (parts[i] + 63) / 64 * 64;
+    if (P->tr_scratch.n < off[NP]) HIP_TRY(P->tr_scratch.alloc(off[NP]));
+    if (P->tr_items.n < items.size()) HIP_TRY(P->tr_items.alloc(items.size()));
+    const size_t n_red = (size_t)(kb + 1) * TRAIN_ACC * 64;
+    if (P->tr_red.n < n_red) HIP_TRY(P->tr_red.alloc(n_red));
+    size_t n_sse = 0;
+    for (size_t q = 0; q + 1 < chunk.size(); ++q) n_sse += (size_t)train_sse_count(chunk[q + 1] - chunk[q], ks);
+    if (P->tr_sse.n < n_sse) HIP_TRY(P->tr_sse.alloc(n_sse));
     if (!P->tr_out.p) HIP_TRY(P->tr_out.alloc(2));
-    HIP_TRY(upload_async(P->tr_subs.p, subs, (size_t)n * 4, s));
-    HIP_TRY(upload_async(P->tr_coff.p, c_off, (size_t)n * 8, s));
-    HIP_TRY(upload_async(P->tr_soff.p, soff.data(), (size_t)n * 8, s));
-    TrainArgs a{P->sub_ptr.p, P->edge_ptr.p, P->edge_src.p, P->edge_nd.p, P->xy64.p, P->lm_ptr.p, P->lm_col.p,
-                P->lm_val.p, P->oe_ptr.p, P->oe_edge.p, P->oe_recv.p, P->tr_subs.p, P->tr_coff.p, P->tr_soff.p,
-                c, theta, P->tr_scratch.p, P->tr_gpart.p, P->tr_sse.p, md->kbar, (float)md->alpha, 0};
-    for (int32_t s0 = 0; s0 < n; s0 += TRAIN_CHUNK) {
-        a.s0 = s0;
-        HIP_TRY(launch_train_grad(a, std::min(TRAIN_CHUNK, n - s0), s));
+    HIP_TRY(upload_async(P->tr_items.p, items.data(), items.size() * sizeof(int4), s));
+    float* f = P->tr_scratch.p;
+    TrainArgs a{};
+    a.kbar = kb;
+    a.ks = ks;
+    a.alpha = (float)md->alpha;
+    a.info = P->vt_info.p;
+    a.node = P->vt_node.p;
+    a.pos = P->vt_pos.p;
+    a.rin = P->tr_rin.p;
+    a.rout = P->tr_rout.p;
+    a.lm_ptr = P->lm_ptr.p;
+    a.lm_col = P->lm_col.p;
+    a.lm_val = P->lm_val.p;
+    a.c = c;
+    a.blobs = a.blobs_out = f;
+    a.in = reinterpret_cast<float2*>(f + off[1]);
+    a.h = f + off[2];
+    a.q = f + off[3];
+    a.m = f + off[4];
+    a.r = f + off[5];
+    a.rho = f + off[6];
+    a.gr = f + off[7];
+    a.pg[0] = f + off[8];
+    a.pg[1] = f + off[9];
+    a.own = f + off[10];
+    a.part = f + off[11];
+    a.sse = P->tr_sse.p;
+    for (size_t q = 0; q + 1 < chunk.size(); ++q) {
+        a.items = P->tr_items.p + 2 * (size_t)chunk[q];
+        a.n_tiles = chunk[q + 1] - chunk[q];
+        HIP_TRY(launch_train_grad(a, theta, P->tr_map.p, P->tr_red.p, q > 0, s));
+        a.sse += train_sse_count(a.n_tiles, ks);
     }
-    HIP_TRY(launch_train_reduce(P->tr_gpart.p, n, nth, scale, grad, P->tr_out.p, P->tr_sse.p, s));
+    HIP_TRY(launch_train_reduce(P->tr_red.p, P->tr_ent.p, kb, scale, grad, P->tr_out.p, P->tr_sse.p, (int)n_sse, s));
     double out2[2];
     HIP_TRY(hipMemcpyAsync(out2, P->tr_out.p, sizeof(out2), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));

@@ -227,13 +227,17 @@ struct ddmgnn_problem {
     ddmgnn::DevBuf<double> gm_v, gm_z, gm_part, gm_small;
     int gm_R = 0;
     ddmgnn::DevBuf<float> qglobal32;
-    // training: local matrices A_i and out-edge lists (built on the first training
-    // call), per-call scratch, per-sample arrays and the residual of ddmgnn_train_rhs
-    ddmgnn::DevBuf<int32_t> lm_ptr, oe_ptr, oe_edge, tr_subs;
-    ddmgnn::DevBuf<uint16_t> lm_col, oe_recv;
-    ddmgnn::DevBuf<float> lm_val, tr_scratch, tr_gpart;
-    ddmgnn::DevBuf<int64_t> tr_coff, tr_soff;
-    ddmgnn::DevBuf<double> tr_sse, tr_out, tr_r;
+    // training: local matrices A_i and edge records (built on the first training
+    // call), per-call scratch and the residual of ddmgnn_train_rhs
+    ddmgnn::DevBuf<int32_t> lm_ptr, tr_map;
+    ddmgnn::DevBuf<uint16_t> lm_col;
+    ddmgnn::DevBuf<float> lm_val, tr_scratch;
+    ddmgnn::DevBuf<ddmgnn::TrainEntry> tr_ent;
+    ddmgnn::DevBuf<int2> tr_orows;
+    std::vector<int2> tr_out_rows;   // host: per tile, first out-edge row and rows
+    ddmgnn::DevBuf<ddmgnn::TrainEdge> tr_rin, tr_rout;
+    ddmgnn::DevBuf<int4> tr_items;   // of a call: the samples' tiles
+    ddmgnn::DevBuf<double> tr_red, tr_sse, tr_out, tr_r;
     // Krylov vectors
     ddmgnn::DevBuf<double> u, r, z;
     ddmgnn::DevBuf<double> ring;     // (MAX_M + 1) p vectors then (MAX_M + 1) q vectors

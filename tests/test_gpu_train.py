@@ -245,3 +245,28 @@ def test_largest_sub_mesh_matches_oracle(setup):
     assert np.abs(gg - G).max() <= GRAD_ATOL * np.abs(G).max()
     prob.close()
     model.close()
+
+
+def test_chunks_and_tile_edges_match_oracle_sums(setup):
+    """More tiles than one scratch region holds: the batch is run in two chunks and equals the
+    sum of its parts; a batch of one sample repeated gives the same gradient as that sample
+    once (scale 1/n), whatever tiles of a workgroup the copies fall on."""
+    p, hp, ctx, prob, subs, torch = setup
+    theta = torch.tensor(_theta(5, 2), device="cuda")
+    cs = [_rhs(subs[i][1], 40 + i) for i in range(hp.K)]
+    cdev = torch.tensor(np.concatenate(cs), device="cuda")
+    off = np.cumsum([0] + [c.size for c in cs[:-1]])
+    tiles = [(c.size + 15) // 16 for c in cs]
+    n = 32768 // min(tiles) + 3
+    order = np.arange(n) % hp.K
+    g, one = torch.empty_like(theta), torch.empty_like(theta)
+    loss, _ = prob.train_grad(theta, order, cdev, off[order], g, kbar=2, alpha=0.3, scale=1e-3)
+    assert sum(tiles[i] for i in order) > 32768
+    want, total = torch.zeros_like(theta, dtype=torch.float64), 0.0
+    for i in range(hp.K):
+        L, _ = prob.train_grad(theta, [i], cdev, [off[i]], one, kbar=2, alpha=0.3, scale=1e-3)
+        want += int((order == i).sum()) * one.double()
+        total += int((order == i).sum()) * L
+    assert loss == pytest.approx(total, rel=1e-6)
+    # FP32 sums over the nodes in another order: the bar of the oracle comparison
+    assert float((g.double() - want).abs().max()) <= GRAD_ATOL * float(want.abs().max())
