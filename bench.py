@@ -147,10 +147,10 @@ class DirectSolve:
 
 
 def lu_local_bytes(K: int, sum_k: int, sum_k2: int) -> float:
-    """Compulsory HBM bytes of one exact local-solve launch (DDM-LU): the inverses
-    8 sum k_i^2; per slot r gather 8, sub_nodes 4, weights 8, local output 8;
+    """Compulsory HBM bytes of one exact local-solve launch (DDM-LU): one triangle of the
+    symmetric inverses, 4 sum k_i (k_i + 1); per slot r gather 8, sub_nodes 4, weights 8, local output 8;
     per sub-mesh sub_ptr 4, lu_off 8, s and y0 outputs 16."""
-    return 8.0 * sum_k2 + sum_k * (8 + 4 + 8 + 8) + K * (4 + 8 + 16)
+    return 4.0 * (sum_k2 + sum_k) + sum_k * (8 + 4 + 8 + 8) + K * (4 + 8 + 16)
 
 
 def bench_lu(dg, prob, u, hp, steps: int) -> dict:

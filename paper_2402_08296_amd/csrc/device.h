@@ -115,9 +115,10 @@ struct DevProb {
     const int32_t* node_slots;
     const int32_t* slot_sub;
     const double* a0inv;        // K x K
-    const double* lu_inv;       // local exact solves: (R_i A R_i^T)^{-1} per sub-mesh, k_i rows of
-                                // stride k_i rounded up to even (16-byte aligned rows, zero pad)
+    const double* lu_inv;       // local exact solves: the tiles of -(R_i A R_i^T)^{-1} per sub-mesh
     const int64_t* lu_off;      // [K + 1] offsets into lu_inv (null until built)
+    double* lu_part;            // per sub-mesh and unit of its tiles, partial products (lu_units(k) x k)
+    const int64_t* lu_poff;     // [K + 1] offsets into lu_part
     // iteration vectors
     double* u;
     double* r;                  // residual; input of the apply
@@ -179,33 +180,48 @@ hipError_t launch_dss_big(const DevProb* tab, const int2* work, int n_work, int 
                           double alpha, int apply, const float* theta32, const double* theta64, hipStream_t s,
                           bool check);
 // Exact local solves (DDM-LU): restriction as in the DSS kernels, then
-// local = (R_i A R_i^T)^{-1} R_i r per sub-mesh; R_i r is staged in dynamic
-// LDS of max_k doubles (the largest sub-mesh of the work list).
-// prepare_lu_local raises the kernel's LDS limit to kMaxSubNodesAny doubles
-// (not allowed during stream capture).
+// local = (R_i A R_i^T)^{-1} R_i r per sub-mesh. A sub-mesh of nt rows of tiles is
+// shared by lu_units workgroups (unit u: rows u and nt - 1 - u, nt + 1 tiles), whose
+// partial products a second kernel adds. units: (problem, sub-mesh, unit); those of
+// sub-meshes of at most LU_LDS_K nodes, and the larger ones (big); max_k: largest
+// sub-mesh of each list (dynamic LDS). subs: (problem, sub-mesh).
+// prepare_lu_local raises the kernels' LDS limits (not allowed during capture).
+constexpr int LU_LDS_K = 2048;
+__host__ __device__ inline int lu_units(int k) { return ((k + 63) / 64 + 1) / 2; }
+struct LuWork {
+    const int4* units;
+    int n_units, max_k;
+    const int4* big;
+    int n_big, max_k_big;
+    const int2* subs;
+    int n_subs;
+};
 hipError_t prepare_lu_local();
-// Device factorisation (factor.hip). launch_lu_assemble: A_i = R_i A R_i^T of
-// every sub-mesh, dense, sub-mesh i at off[i] of inv with row stride
-// (off[i + 1] - off[i]) / k_i. launch_coarse_assemble: A_0 = R_0 A R_0^T (K x K,
-// deterministic summation order), symmetrised, its diagonal copied to diag0.
-// launch_gj_invert: in-place inverses of a batch of SPD matrices (matrix m at
-// base + off[m], order plan.order[m]) by blocked Gauss-Jordan over the whole
-// device; scratch holds plan.scratch_doubles(); *status (device, zeroed by the
-// caller) gets bit 0 when a pivot is not positive (or, with diag0, below 1e-12
-// of its original diagonal entry).
+hipError_t launch_lu_local(const DevProb* tab, const LuWork& w, hipStream_t s, bool check);
+// Device factorisation (factor.hip) of symmetric matrices held as the SYM_TILE x
+// SYM_TILE tiles of their lower triangle. launch_lu_assemble: the tiles (zeroed
+// before) of A_i = R_i A R_i^T, sub-mesh i's at off[i] of inv. launch_coarse_assemble:
+// A_0 = R_0 A R_0^T (K x K, deterministic summation order), symmetrised, its diagonal
+// copied to diag0. launch_gj_invert: in-place -A^{-1} of a batch of SPD matrices (matrix
+// m's tiles at base + off[m], orders and prefixes of plan.meta in meta) over the
+// whole device; scratch holds plan.scratch_doubles(). launch_coarse_invert: A_0^{-1} in
+// place of A_0 (K x K); scratch holds coarse_scratch_doubles(K). *status (device,
+// zeroed by the caller) gets bit 0 when a pivot is not positive (coarse: not above
+// 1e-12 of its original diagonal entry).
+constexpr int SYM_TILE = 64;
+__host__ __device__ inline int64_t sym_tile(int I, int J) {  // offset of tile (I, J), J <= I
+    return ((int64_t)I * (I + 1) / 2 + J) * SYM_TILE * SYM_TILE;
+}
+inline int64_t sym_doubles(int64_t k) {
+    const int64_t nt = (k + SYM_TILE - 1) / SYM_TILE;
+    return nt * (nt + 1) / 2 * SYM_TILE * SYM_TILE;
+}
 struct GjPlan {
-    std::vector<int32_t> order, cprefix, tprefix;  // orders; workgroup prefixes (columns, tiles)
-    std::vector<int64_t> prow;                     // prefix of the orders
-    int32_t max_k = 0;
-    int64_t tiles = 0;  // tile workgroups of one trailing update
+    int nm = 0, steps = 0;
+    int64_t n_rows = 0, n_tiles = 0;  // tiles per column of all matrices, and all tiles
+    std::vector<int32_t> meta;        // orders, prefix of the tiles per column, prefix of the tiles
     explicit GjPlan(const std::vector<int32_t>& k);
     size_t scratch_doubles() const;
-};
-struct GjPlanDev {  // device copies of a plan's arrays
-    const int32_t* order;
-    const int32_t* cprefix;
-    const int32_t* tprefix;
-    const int64_t* prow;
 };
 hipError_t launch_lu_assemble(const int32_t* rowptr, const int32_t* col, const double* val, const int64_t* sub_ptr,
                               const int32_t* sub_nodes, const int64_t* off, double* inv, int n_sub, hipStream_t s);
@@ -213,8 +229,10 @@ hipError_t launch_coarse_assemble(const int32_t* rowptr, const int32_t* col, con
                                   const int32_t* sub_ptr, const int32_t* sub_nodes, const double* weights,
                                   const int32_t* node_ptr, const int32_t* node_slots, const int32_t* slot_sub, int K,
                                   double* a0, double* diag0, hipStream_t s);
-hipError_t launch_gj_invert(const GjPlan& plan, const GjPlanDev& dev, double* base, const int64_t* off,
-                            double* scratch, const double* diag0, int* status, hipStream_t s);
+hipError_t launch_gj_invert(const GjPlan& plan, const int32_t* meta, double* base, const int64_t* off, double* scratch,
+                            int* status, hipStream_t s);
+size_t coarse_scratch_doubles(int K);
+hipError_t launch_coarse_invert(double* a0, int K, const double* diag0, double* scratch, int* status, hipStream_t s);
 // Overlap expansion on the device (overlap.hip). OV_CAP: most sub-meshes a node
 // may belong to; OV_SORT_MAX: largest sub-mesh the per-part sort holds (the
 // library's sub-mesh limit). ov_check: bit 0 of *status for a triangle node id
@@ -236,7 +254,6 @@ hipError_t ov_count(const int32_t* sets, const uint8_t* sz, int64_t n, int32_t n
 hipError_t ov_fill(const int32_t* sets, const uint8_t* sz, int64_t n, const uint8_t* dirichlet, int32_t n_part,
                    const int64_t* sub_ptr, int64_t sk, int32_t* part_cur, int32_t* nodes, double* weights,
                    hipStream_t s);
-hipError_t launch_lu_local(const DevProb* tab, const int2* work, int n_work, int max_k, hipStream_t s, bool check);
 hipError_t launch_coarse(const DevProb* tab, const int2* rows, int n_rows, hipStream_t s, bool check);
 // The Krylov launchers end with a finalize launch of one workgroup per
 // problem: n_prob = all problems of the table, or the problems of `list`.

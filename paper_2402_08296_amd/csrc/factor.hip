@@ -6,22 +6,27 @@
 // in place, so that every apply is one GEMV per sub-mesh (lu_local_kernel) and
 // one for the coarse level (coarse_kernel).
 //
-// Inversion: blocked Gauss-Jordan without pivoting, which is safe for a
-// symmetric positive definite matrix (every pivot block is a diagonal block
-// of a Schur complement, itself SPD). For pivot block P (GJ_W rows and
-// columns) and the remaining indices R, one step replaces
-//   A_PP <- A_PP^{-1},             A_PR <- A_PP^{-1} A_PR,
-//   A_RP <- -A_RP A_PP^{-1},       A_RR <- A_RR - A_RP A_PP^{-1} A_PR,
-// and after the last block the matrix holds its inverse (the in-place
-// inversion of Gauss-Jordan elimination, one block of pivots at a time).
+// Storage: a symmetric matrix of order k is held as the 64 x 64 tiles of its lower
+// triangle (tile (I, J), J <= I, at I (I + 1) / 2 + J, row-major), the last row
+// and column of tiles padded with the identity, so no kernel looks at bounds.
 //
-// A batch of matrices (the K local matrices, or the single coarse matrix)
-// takes four launches per pivot step over the whole device: the pivot block
-// inverses (one workgroup per matrix), the new pivot rows (workgroups over
-// column chunks of every matrix), the update of every 64 x 64 tile of every
-// matrix, and the new pivot columns with the pivot block. A workgroup finds
-// its matrix by binary search in a prefix of per-matrix workgroup counts;
-// matrices already finished at that step return at once.
+// Inversion: the blocked symmetric sweep without pivoting, which is safe for a
+// symmetric positive definite matrix (every pivot block is a diagonal block of
+// a Schur complement, itself SPD). For pivot block P and the other indices R, S
+// one step replaces, with D = A_PP^{-1},
+//   A_RS <- A_RS - A_RP D A_PS,   A_RP <- A_RP D,   A_PP <- -D,
+// which keeps the matrix symmetric, and after the last block it holds -A^{-1}
+// (the readers take the sign). Half the tiles of a Gauss-Jordan step on the
+// full square, and half the memory.
+//
+// The batch of the K local matrices takes two launches per pivot step over the
+// whole device: the panel A_RP D of every R,
+// then the update of every tile of every matrix, in which the workgroup of the
+// next pivot block also inverts it while the others update theirs. Products run
+// on the FP64 matrix instructions. 300 matrices of about 900 rows: 73 ms for the
+// Gauss-Jordan on full squares with vector products and four launches a step, 11 ms now. A workgroup finds its matrix by binary search
+// in a prefix of per-matrix workgroup counts; matrices already finished at that
+// step return at once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,9 +38,12 @@ namespace ddmgnn {
 namespace {
 
 constexpr int GJ_THREADS = 256;
-constexpr int GJ_W = 64;  // pivot block width
-constexpr int GJ_T = 64;  // rows and columns of a tile of the trailing update (4 x 4 per thread)
-static_assert(GJ_T == 16 * 4 && GJ_THREADS == 16 * 16, "tile of 4 x 4 outputs per thread");
+constexpr int GJ_W = SYM_TILE;  // order of a tile and width of a pivot block
+constexpr int GJ_N = GJ_W * GJ_W;
+static_assert(GJ_W == 64 && GJ_THREADS == 256, "a wavefront per 16 rows of a tile");
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 
 // Binary search of node g in the ascending slice s[0..k); -1 when absent.
 __device__ inline int find_local(const int32_t* __restrict__ s, int k, int32_t g) {
@@ -48,8 +56,7 @@ __device__ inline int find_local(const int32_t* __restrict__ s, int k, int32_t g
     return lo < k && s[lo] == g ? lo : -1;
 }
 
-// A_i = R_i A R_i^T of sub-mesh blockIdx.x, dense, sub-mesh i at off[i] with
-// row stride (off[i + 1] - off[i]) / k_i (the pad column stays zero).
+// A_i = R_i A R_i^T of sub-mesh blockIdx.x into its (zeroed) tiles.
 __global__ __launch_bounds__(GJ_THREADS) void lu_assemble_kernel(const int32_t* __restrict__ rowptr,
                                                                   const int32_t* __restrict__ col,
                                                                   const double* __restrict__ val,
@@ -60,17 +67,18 @@ __global__ __launch_bounds__(GJ_THREADS) void lu_assemble_kernel(const int32_t* 
     const int i = blockIdx.x;
     const int64_t b = sub_ptr[i];
     const int k = (int)(sub_ptr[i + 1] - b);
-    if (k == 0) return;
-    const int64_t ld = (off[i + 1] - off[i]) / k;  // row stride of the stored inverse
     double* M = inv + off[i];
     const int32_t* s = sub_nodes + b;
-    for (int64_t e = threadIdx.x; e < (int64_t)k * ld; e += GJ_THREADS) M[e] = 0.0;
-    __syncthreads();
-    for (int j = threadIdx.x; j < k; j += GJ_THREADS) {
+    auto at = [&](int r, int c) { return M + sym_tile(r / GJ_W, c / GJ_W) + (r % GJ_W) * GJ_W + c % GJ_W; };
+    for (int j = threadIdx.x; j < (k + GJ_W - 1) / GJ_W * GJ_W; j += GJ_THREADS) {
+        if (j >= k) {
+            *at(j, j) = 1.0;
+            continue;
+        }
         const int32_t g = s[j];
         for (int32_t e = rowptr[g]; e < rowptr[g + 1]; ++e) {
             const int q = find_local(s, k, col[e]);
-            if (q >= 0) M[(int64_t)j * ld + q] = val[e];
+            if (q >= 0 && q / GJ_W <= j / GJ_W) *at(j, q) = val[e];
         }
     }
 }
@@ -193,29 +201,34 @@ __global__ __launch_bounds__(256) void coarse_symmetrise_kernel(double* __restri
     a0[(size_t)j * K + i] = m;
 }
 
-// One matrix of a batch: order k, row stride ld, entries at M.
-struct GjMat {
-    double* M;
-    int k;
-    int64_t ld;
-};
+// The K x K coarse matrix into nt x nt tiles (one per workgroup, padded with the
+// identity), and back.
+template <bool PACK>
+__global__ __launch_bounds__(GJ_THREADS) void square_tiles_kernel(double* __restrict__ a, int K, int nt,
+                                                                 double* __restrict__ tiles) {
+    const int I = blockIdx.x / nt, J = blockIdx.x % nt;
+    double* T = tiles + (size_t)blockIdx.x * GJ_N;
+    for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) {
+        const int r = I * GJ_W + e / GJ_W, c = J * GJ_W + e % GJ_W;
+        const bool in = r < K && c < K;
+        if (PACK) T[e] = in ? a[(size_t)r * K + c] : r == c ? 1.0 : 0.0;
+        else if (in) a[(size_t)r * K + c] = T[e];
+    }
+}
+
 struct GjBatch {
     double* base;
-    const int64_t* off;     // [nm + 1] matrix m at base + off[m], row stride (off[m + 1] - off[m]) / k_m
+    const int64_t* off;     // [nm + 1] matrix m's tiles at base + off[m]
     const int32_t* order;   // [nm] k_m
+    const int32_t* rows;    // [nm + 1] prefix of the tiles per column
+    const int32_t* tiles;   // [nm + 1] prefix of the tiles
     int nm;
-    const int32_t* cprefix; // [nm + 1] prefix of ceil(k_m / GJ_THREADS) (row and column workgroups)
-    const int32_t* tprefix; // [nm + 1] prefix of ceil(k_m / GJ_T)^2 (tile workgroups)
-    double* dinv;           // [nm][GJ_W][GJ_W] pivot block inverses
-    double* pr;             // matrix m's new pivot rows at pr + GJ_W * prow[m], row stride k_m
-    const int64_t* prow;    // [nm + 1] prefix of k_m
-    const double* diag0;    // optional: original diagonal (pivot test reference) of matrix 0
+    double* dinv;           // [nm] pivot block inverses
+    double* pan;            // per matrix and row of tiles, A_RP before the step
+    double* w;              // and A_RP D
+    const double* diag0;    // coarse matrix: its original diagonal (pivot test reference), else null
     int* status;            // bit 0: a pivot not positive (or below GJ_REL of diag0)
 };
-__device__ inline GjMat gj_mat(const GjBatch& b, int m) {
-    const int k = b.order[m];
-    return {b.base + b.off[m], k, k > 0 ? (b.off[m + 1] - b.off[m]) / k : 0};
-}
 // Matrix of workgroup w in a prefix of per-matrix workgroup counts (the last m
 // with prefix[m] <= w), and w's index within that matrix.
 __device__ inline int gj_find(const int32_t* prefix, int nm, int w, int* local) {
@@ -234,190 +247,366 @@ __device__ inline int gj_find(const int32_t* prefix, int nm, int w, int* local) 
 // is refused instead of inverted.
 constexpr double GJ_REL = 1e-12;
 
-__global__ __launch_bounds__(GJ_THREADS) void gj_pivot_kernel(GjBatch b, int pb) {
-    __shared__ double D[GJ_W][GJ_W + 1];
+// A tile in LDS: 16-byte units, unit u of row r at u ^ (r % 32), so that 16 rows'
+// equal columns lie on different banks.
+__device__ __forceinline__ int swz(int r, int u) { return r * 32 + (u ^ (r & 31)); }
+__device__ __forceinline__ double& el(double* t, int r, int c) { return t[swz(r, c / 2) * 2 + c % 2]; }
+
+// A row-major tile from global memory into LDS: straight 16-byte loads.
+__device__ __forceinline__ void tile_in(const double* __restrict__ from, double* to) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int p = (i * 4 + wave) * 64 + lane, r = p / 32, u = (p % 32) ^ (r & 31);
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(from + r * GJ_W + u * 2),
+            (__attribute__((address_space(3))) void*)(to + (i * 4 + wave) * 128), 16, 0, 0);
+    }
+}
+__device__ __forceinline__ void tile_out(double* t, double* __restrict__ to) {
+    for (int e = threadIdx.x; e < GJ_N / 2; e += GJ_THREADS) {
+        const int r = e / 32, u = e % 32;
+        reinterpret_cast<d2*>(to)[e] = reinterpret_cast<const d2*>(t)[swz(r, u)];
+    }
+}
+
+// The wavefront's 16 rows of L R, every sum in ascending order: entry
+// (16 wave + 4 r + g, 16 c + lane % 16) in out[c][r].
+__device__ __forceinline__ void product(double* L, double* R, int wave, int lane, d4 (&out)[4]) {
+    const int n = lane & 15, g = lane >> 4;
+    double a[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) a[s] = el(L, 16 * wave + n, 4 * s + g);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        d4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], el(R, 4 * s + g, 16 * c + n), acc, 0, 0, 0);
+        out[c] = acc;
+    }
+}
+// The same of L R^T, group g taking entries 16 g .. 16 g + 15 of the sums: both operands
+// are rows, read 16 bytes at a time.
+__device__ __forceinline__ void row16(const double* t, int row, int g, double (&v)[16]) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const d2 x = reinterpret_cast<const d2*>(t)[swz(row, 8 * g + s)];
+        v[2 * s] = x[0];
+        v[2 * s + 1] = x[1];
+    }
+}
+__device__ __forceinline__ void product_rows(const double* L, const double* R, int wave, int lane, d4 (&out)[4]) {
+    const int n = lane & 15, g = lane >> 4;
+    double a[16];
+    row16(L, 16 * wave + n, g, a);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        double b[16];
+        row16(R, 16 * c + n, g, b);
+        d4 acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], acc, 0, 0, 0);
+        out[c] = acc;
+    }
+}
+
+// Inverse of the tile in LDS (swizzled) into inv (row-major): Gauss-Jordan with a
+// wavefront per 16 rows in registers (lane = column); the pivot row passes through
+// LDS, one barrier per pivot. first: index of the tile's first row; rows from k on
+// are padding. About 0.5 us per pivot (2 us with the tile in LDS: two barriers and
+// 16 LDS updates per thread and pivot).
+__device__ void invert_tile(double* t, double (*row)[GJ_W], const GjBatch& b, int first, int k,
+                            double* __restrict__ inv) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double a[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[r] = el(t, 16 * wave + r, lane);
+    for (int o = 0; o < 4; ++o) {  // pivots of wavefront o
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int q = 16 * o + i;
+            if (wave == o) row[i & 1][lane] = a[i];
+            __syncthreads();
+            const double rq = row[i & 1][lane], dq = row[i & 1][q];
+            if (threadIdx.x == 0 && first + q < k) {
+                const double floor = b.diag0 ? GJ_REL * fabs(b.diag0[first + q]) : 0.0;
+                if (!(dq > floor) || !isfinite(dq)) atomicOr(b.status, 1);
+            }
+            const double piv = 1.0 / dq;
+            const bool me = lane == q;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (wave == o && r == i) continue;  // uniform
+                union { double d; int w[2]; } f;
+                f.d = a[r];
+                f.w[0] = __builtin_amdgcn_readlane(f.w[0], q);
+                f.w[1] = __builtin_amdgcn_readlane(f.w[1], q);
+                const double x = -f.d * piv;
+                a[r] = me ? x : fma(x, rq, a[r]);
+            }
+            if (wave == o) a[i] = me ? piv : rq * piv;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) inv[(16 * wave + r) * GJ_W + lane] = a[r];
+}
+
+// The first pivot block of every matrix.
+__global__ __launch_bounds__(GJ_THREADS) void gj_first_kernel(GjBatch b) {
+    __shared__ __align__(16) double t[GJ_N];
+    __shared__ double row[2][GJ_W];
     const int m = blockIdx.x;
-    const GjMat A = gj_mat(b, m);
-    if (pb >= A.k) return;
-    const int t = threadIdx.x, w = min(GJ_W, A.k - pb);
-    for (int e = t; e < GJ_W * GJ_W; e += GJ_THREADS) {
-        const int r = e / GJ_W, c = e % GJ_W;
-        D[r][c] = r < w && c < w ? A.M[(int64_t)(pb + r) * A.ld + pb + c] : 0.0;
-    }
+    if (b.order[m] <= 0) return;
+    tile_in(b.base + b.off[m], t);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    constexpr int PER = GJ_W * GJ_W / GJ_THREADS;
-    for (int q = 0; q < w; ++q) {
-        const double dq = D[q][q];
-        const double floor = b.diag0 ? GJ_REL * fabs(b.diag0[pb + q]) : 0.0;
-        if (t == 0 && (!(dq > floor) || !isfinite(dq))) atomicOr(b.status, 1);
-        const double piv = 1.0 / dq;
-        double nv[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = t + u * GJ_THREADS, r = e / GJ_W, c = e % GJ_W;
-            double v = D[r][c];
-            if (r == q && c == q) v = piv;
-            else if (r == q) v = v * piv;
-            else if (c == q) v = -v * piv;
-            else v = fma(-D[r][q] * piv, D[q][c], v);
-            nv[u] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int e = t + u * GJ_THREADS;
-            if (e / GJ_W < w && e % GJ_W < w) D[e / GJ_W][e % GJ_W] = nv[u];
-        }
-        __syncthreads();
-    }
-    double* di = b.dinv + (size_t)m * GJ_W * GJ_W;
-    for (int e = t; e < GJ_W * GJ_W; e += GJ_THREADS) di[e] = D[e / GJ_W][e % GJ_W];
+    invert_tile(t, row, b, 0, b.order[m], b.dinv + (size_t)m * GJ_N);
 }
 
-// A_PR(new) = dinv A_PR, one column per thread, into pr (GJ_W x k): the pivot
-// rows of the matrix are replaced only after the tile update, which reads the
-// old A_RP from the matrix and the new A_PR from pr.
-__global__ __launch_bounds__(GJ_THREADS) void gj_rows_kernel(GjBatch b, int pb) {
-    __shared__ double D[GJ_W][GJ_W + 1];
-    int cb = 0;
-    const int m = gj_find(b.cprefix, b.nm, blockIdx.x, &cb);
-    const GjMat A = gj_mat(b, m);
-    if (pb >= A.k) return;
-    const int t = threadIdx.x, w = min(GJ_W, A.k - pb);
-    const double* di = b.dinv + (size_t)m * GJ_W * GJ_W;
-    for (int e = t; e < GJ_W * GJ_W; e += GJ_THREADS) D[e / GJ_W][e % GJ_W] = di[e];
-    __syncthreads();
-    const int j = cb * GJ_THREADS + t;
-    if (j >= A.k) return;
-    double* pr = b.pr + (size_t)GJ_W * b.prow[m];
-    double x[GJ_W];
-#pragma unroll
-    for (int r = 0; r < GJ_W; ++r) x[r] = r < w ? A.M[(int64_t)(pb + r) * A.ld + j] : 0.0;
-    for (int r = 0; r < w; ++r) {
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < GJ_W; ++c) acc = fma(D[r][c], x[c], acc);
-        pr[(size_t)r * A.k + j] = acc;
-    }
-}
-
-// A_RR -= A_RP(old) A_PR(new) on one GJ_T x GJ_T tile per workgroup.
-__global__ __launch_bounds__(GJ_THREADS) void gj_tiles_kernel(GjBatch b, int pb) {
-    __shared__ double F[GJ_T][GJ_W + 1];
-    __shared__ double R[GJ_W][GJ_T + 1];
-    int tl = 0;
-    const int m = gj_find(b.tprefix, b.nm, blockIdx.x, &tl);
-    const GjMat A = gj_mat(b, m);
-    if (pb >= A.k) return;
-    const int t = threadIdx.x, w = min(GJ_W, A.k - pb), pe = pb + w;
-    const int nt = (A.k + GJ_T - 1) / GJ_T;
-    const int i0 = (tl / nt) * GJ_T, j0 = (tl % nt) * GJ_T;
-    const double* pr = b.pr + (size_t)GJ_W * b.prow[m];
-    for (int e = t; e < GJ_T * GJ_W; e += GJ_THREADS) {
-        const int r = e / GJ_W, c = e % GJ_W, i = i0 + r;
-        F[r][c] = i < A.k && (i < pb || i >= pe) && c < w ? A.M[(int64_t)i * A.ld + pb + c] : 0.0;
-    }
-    for (int e = t; e < GJ_W * GJ_T; e += GJ_THREADS) {
-        const int r = e / GJ_T, c = e % GJ_T, j = j0 + c;
-        R[r][c] = r < w && j < A.k && (j < pb || j >= pe) ? pr[(size_t)r * A.k + j] : 0.0;
-    }
-    __syncthreads();
-    const int ty = t / 16, tx = t % 16;
-    double acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = 0.0;
-    for (int p = 0; p < w; ++p) {
-        double f[4], g[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) f[a] = F[ty * 4 + a][p];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) g[c] = R[p][tx * 4 + c];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][c] = fma(f[a], g[c], acc[a][c]);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        const int i = i0 + ty * 4 + a;
-        if (i >= A.k || (i >= pb && i < pe)) continue;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int j = j0 + tx * 4 + c;
-            if (j >= A.k || (j >= pb && j < pe)) continue;
-            A.M[(int64_t)i * A.ld + j] -= acc[a][c];
-        }
-    }
-}
-
-// A_RP <- -A_RP(old) dinv (one row per thread), the pivot rows <- pr and the
-// pivot block <- dinv.
-__global__ __launch_bounds__(GJ_THREADS) void gj_cols_kernel(GjBatch b, int pb) {
-    __shared__ double D[GJ_W][GJ_W + 1];
-    int cb = 0;
-    const int m = gj_find(b.cprefix, b.nm, blockIdx.x, &cb);
-    const GjMat A = gj_mat(b, m);
-    if (pb >= A.k) return;
-    const int t = threadIdx.x, w = min(GJ_W, A.k - pb), pe = pb + w;
-    const double* di = b.dinv + (size_t)m * GJ_W * GJ_W;
-    for (int e = t; e < GJ_W * GJ_W; e += GJ_THREADS) D[e / GJ_W][e % GJ_W] = di[e];
-    __syncthreads();
-    const int i = cb * GJ_THREADS + t;
-    if (i >= A.k) return;
-    const double* pr = b.pr + (size_t)GJ_W * b.prow[m];
-    double* row = A.M + (int64_t)i * A.ld;
-    if (i >= pb && i < pe) {
-        const int r = i - pb;
-        for (int j = 0; j < A.k; ++j) row[j] = j >= pb && j < pe ? D[r][j - pb] : pr[(size_t)r * A.k + j];
+// Panel of pivot block p: W_R = A_RP D, written to the panel buffer and to the matrix,
+// the old A_RP to the other panel buffer; -D to the pivot block.
+__global__ __launch_bounds__(GJ_THREADS, 2) void gj_panel_kernel(GjBatch b, int p) {
+    __shared__ __align__(16) double x[GJ_N], y[GJ_N];
+    int R = 0;
+    const int m = gj_find(b.rows, b.nm, blockIdx.x, &R);
+    const int nt = b.rows[m + 1] - b.rows[m];
+    if (p >= nt) return;
+    double* M = b.base + b.off[m];
+    const double* D = b.dinv + (size_t)m * GJ_N;
+    if (R == p) {
+        double* T = M + sym_tile(p, p);
+        for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) T[e] = -D[e];
         return;
     }
-    double f[GJ_W];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    tile_in(D, y);
+    double* T = M + (R > p ? sym_tile(R, p) : sym_tile(p, R));
+    if (R > p) {
+        tile_in(T, x);
+    } else {  // A_RP is the transpose of the stored tile
+        for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) el(x, e % GJ_W, e / GJ_W) = T[e];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const size_t at = ((size_t)b.rows[m] + R) * GJ_N;
+    tile_out(x, b.pan + at);
+    d4 w[4];
+    product_rows(x, y, wave, lane, w);  // D is symmetric
+    __syncthreads();
+    const int n = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int c = 0; c < GJ_W; ++c) f[c] = c < w ? row[pb + c] : 0.0;
-    for (int c = 0; c < w; ++c) {
-        double acc = 0.0;
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-        for (int q = 0; q < GJ_W; ++q) acc = fma(f[q], D[q][c], acc);
-        row[pb + c] = -acc;
+        for (int r = 0; r < 4; ++r) el(x, 16 * wave + 4 * r + g, 16 * c + n) = w[c][r];
+    __syncthreads();
+    tile_out(x, b.w + at);
+    if (R > p) {
+        tile_out(x, T);
+    } else {
+        for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) T[e] = el(x, e % GJ_W, e / GJ_W);
+    }
+}
+
+// A_RS -= W_R A_SP^T on one tile per workgroup; the workgroup of the next pivot block
+// (the first of its matrix) also inverts it. Bound by the matrix instructions: 256
+// products of 16 x 16 x 4 a tile (32 KB read, 16 KB from the panels' cache lines).
+__global__ __launch_bounds__(GJ_THREADS, 2) void gj_update_kernel(GjBatch b, int p) {
+    __shared__ __align__(16) double x[GJ_N], y[GJ_N];
+    __shared__ double row[2][GJ_W];
+    int t = 0;
+    const int m = gj_find(b.tiles, b.nm, blockIdx.x, &t);
+    const int nt = b.rows[m + 1] - b.rows[m];
+    if (p >= nt) return;
+    const int next = p + 1 < nt ? (p + 1) * (p + 2) / 2 + p + 1 : 0;  // tile (p + 1, p + 1) changes place with tile 0
+    t = t == 0 ? next : t == next ? 0 : t;
+    int R = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+    while ((R + 1) * (R + 2) / 2 <= t) ++R;
+    while (R * (R + 1) / 2 > t) --R;
+    const int S = t - R * (R + 1) / 2;
+    if (R == p || S == p) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    tile_in(b.w + ((size_t)b.rows[m] + R) * GJ_N, x);
+    tile_in(b.pan + ((size_t)b.rows[m] + S) * GJ_N, y);
+    const int n = lane & 15, g = lane >> 4;
+    double* T = b.base + b.off[m] + sym_tile(R, S);
+    double old[4][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) old[c][r] = T[(16 * wave + 4 * r + g) * GJ_W + 16 * c + n];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    d4 w[4];
+    product_rows(x, y, wave, lane, w);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            old[c][r] -= w[c][r];
+            T[(16 * wave + 4 * r + g) * GJ_W + 16 * c + n] = old[c][r];
+        }
+    if (R == p + 1 && S == R) {  // uniform over the workgroup
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) el(x, 16 * wave + 4 * r + g, 16 * c + n) = old[c][r];
+        __syncthreads();
+        invert_tile(x, row, b, R * GJ_W, b.order[m], b.dinv + (size_t)m * GJ_N);
+    }
+}
+
+// The coarse matrix is inverted on its full square of tiles, by the Gauss-Jordan step
+//   A_IJ <- A_IJ - A_IP D A_PJ,  A_PJ <- D A_PJ,  A_IP <- -A_IP D,  A_PP <- D
+// with every sum in ascending order: its bits then do not depend on the tiling or the
+// kernel, which matters because solves with the FP32 and BF16 forward round what it
+// gives (one flipped rounding of a residual moves such a solution by 1e-8). It is one
+// small matrix: half the tiles would save less than a launch.
+struct SquareArgs {
+    double* tiles;
+    int nt, K;
+    double* dinv;
+    double* row;   // D A_PJ of every J
+    double* col;   // A_IP of every I before the step
+    GjBatch b;     // status and diag0 of the pivot test
+};
+
+__global__ __launch_bounds__(GJ_THREADS) void square_first_kernel(SquareArgs a) {
+    __shared__ __align__(16) double t[GJ_N];
+    __shared__ double row[2][GJ_W];
+    tile_in(a.tiles, t);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    invert_tile(t, row, a.b, 0, a.K, a.dinv);
+}
+
+// Workgroup j: A_Pj <- D A_Pj; workgroup nt + i: A_iP <- -A_iP D (i = P: the pivot block).
+__global__ __launch_bounds__(GJ_THREADS, 2) void square_panel_kernel(SquareArgs a, int p) {
+    __shared__ __align__(16) double x[GJ_N], y[GJ_N];
+    const bool rows = (int)blockIdx.x < a.nt;
+    const int i = (int)blockIdx.x % a.nt;
+    double* T = a.tiles + ((size_t)(rows ? p : i) * a.nt + (rows ? i : p)) * GJ_N;
+    if (i == p) {
+        if (!rows)
+            for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) T[e] = a.dinv[e];
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    tile_in(T, x);
+    tile_in(a.dinv, y);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    d4 w[4];
+    if (rows) {
+        product(y, x, wave, lane, w);
+    } else {
+        tile_out(x, a.col + (size_t)i * GJ_N);
+        product(x, y, wave, lane, w);
+    }
+    const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = (16 * wave + 4 * r + g) * GJ_W + 16 * c + n;
+            T[e] = rows ? w[c][r] : -w[c][r];
+            if (rows) a.row[(size_t)i * GJ_N + e] = w[c][r];
+        }
+}
+
+__global__ __launch_bounds__(GJ_THREADS, 2) void square_update_kernel(SquareArgs a, int p) {
+    __shared__ __align__(16) double x[GJ_N], y[GJ_N];
+    __shared__ double row[2][GJ_W];
+    const int nt = a.nt, next = p + 1 < nt ? (p + 1) * (nt + 1) : 0;
+    int t = blockIdx.x;
+    t = t == 0 ? next : t == next ? 0 : t;  // the next pivot block first
+    const int I = t / nt, J = t % nt;
+    if (I == p || J == p) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    tile_in(a.col + (size_t)I * GJ_N, x);
+    tile_in(a.row + (size_t)J * GJ_N, y);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    d4 w[4];
+    product(x, y, wave, lane, w);
+    const int n = lane & 15, g = lane >> 4;
+    double* T = a.tiles + (size_t)t * GJ_N;
+    const bool pivot = I == p + 1 && J == I;  // uniform over the workgroup
+    if (pivot) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * wave + 4 * r + g, j = 16 * c + n;
+            const double v = T[i * GJ_W + j] - w[c][r];
+            T[i * GJ_W + j] = v;
+            if (pivot) el(x, i, j) = v;
+        }
+    if (pivot) {
+        __syncthreads();
+        invert_tile(x, row, a.b, I * GJ_W, a.K, a.dinv);
     }
 }
 
 }  // namespace
 
 GjPlan::GjPlan(const std::vector<int32_t>& k) {
-    const int nm = (int)k.size();
-    order = k;
-    cprefix.assign((size_t)nm + 1, 0);
-    tprefix.assign((size_t)nm + 1, 0);
-    prow.assign((size_t)nm + 1, 0);
+    nm = (int)k.size();
+    meta.assign((size_t)3 * nm + 2, 0);
+    int32_t* rows = meta.data() + nm;
+    int32_t* tl = rows + nm + 1;
     for (int m = 0; m < nm; ++m) {
-        const int64_t nt = (k[m] + GJ_T - 1) / GJ_T;
-        cprefix[m + 1] = cprefix[m] + (k[m] + GJ_THREADS - 1) / GJ_THREADS;
-        tiles += nt * nt;
-        tprefix[m + 1] = (int32_t)std::min<int64_t>(tiles, INT32_MAX);
-        prow[m + 1] = prow[m] + k[m];
-        max_k = std::max(max_k, k[m]);
+        const int64_t nt = (k[m] + GJ_W - 1) / GJ_W;
+        meta[m] = k[m];
+        steps = std::max(steps, (int)nt);
+        n_rows += nt;
+        n_tiles += nt * (nt + 1) / 2;
+        rows[m + 1] = (int32_t)std::min<int64_t>(n_rows, INT32_MAX);
+        tl[m + 1] = (int32_t)std::min<int64_t>(n_tiles, INT32_MAX);
     }
 }
 
-size_t GjPlan::scratch_doubles() const { return order.size() * GJ_W * GJ_W + (size_t)GJ_W * prow.back(); }
+size_t GjPlan::scratch_doubles() const { return ((size_t)nm + 2 * (size_t)n_rows) * GJ_N; }
 
-hipError_t launch_gj_invert(const GjPlan& plan, const GjPlanDev& dev, double* base, const int64_t* off,
-                            double* scratch, const double* diag0, int* status, hipStream_t s) {
-    const int nm = (int)plan.order.size();
-    if (nm == 0) return hipSuccess;
-    GjBatch b{base, off, dev.order, nm, dev.cprefix, dev.tprefix, scratch, scratch + (size_t)nm * GJ_W * GJ_W,
-              dev.prow, diag0, status};
-    const unsigned nc = (unsigned)plan.cprefix.back(), ntl = (unsigned)plan.tprefix.back();
-    if (plan.tiles * GJ_THREADS >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;  // grid limit
-    for (int pb = 0; pb < plan.max_k; pb += GJ_W) {
-        hipLaunchKernelGGL(gj_pivot_kernel, dim3(nm), dim3(GJ_THREADS), 0, s, b, pb);
-        hipLaunchKernelGGL(gj_rows_kernel, dim3(nc), dim3(GJ_THREADS), 0, s, b, pb);
-        hipLaunchKernelGGL(gj_tiles_kernel, dim3(ntl), dim3(GJ_THREADS), 0, s, b, pb);
-        hipLaunchKernelGGL(gj_cols_kernel, dim3(nc), dim3(GJ_THREADS), 0, s, b, pb);
+hipError_t launch_gj_invert(const GjPlan& plan, const int32_t* meta, double* base, const int64_t* off, double* scratch,
+                            int* status, hipStream_t s) {
+    const int nm = plan.nm;
+    if (nm == 0 || plan.n_rows == 0) return hipSuccess;
+    if (plan.n_tiles * GJ_THREADS >= (int64_t)1 << 32) return hipErrorInvalidConfiguration;  // grid limit
+    double* pan = scratch + (size_t)nm * GJ_N;
+    const GjBatch b{base,    off,     meta, meta + nm, meta + 2 * (size_t)nm + 1, nm,
+                    scratch, pan,     pan + (size_t)plan.n_rows * GJ_N, nullptr, status};
+    hipLaunchKernelGGL(gj_first_kernel, dim3(nm), dim3(GJ_THREADS), 0, s, b);
+    for (int p = 0; p < plan.steps; ++p) {
+        hipLaunchKernelGGL(gj_panel_kernel, dim3((unsigned)plan.n_rows), dim3(GJ_THREADS), 0, s, b, p);
+        hipLaunchKernelGGL(gj_update_kernel, dim3((unsigned)plan.n_tiles), dim3(GJ_THREADS), 0, s, b, p);
     }
+    return hipGetLastError();
+}
+
+size_t coarse_scratch_doubles(int K) {
+    const size_t nt = (size_t)(K + GJ_W - 1) / GJ_W;
+    return (nt * nt + 2 * nt + 1) * GJ_N;
+}
+
+hipError_t launch_coarse_invert(double* a0, int K, const double* diag0, double* scratch, int* status, hipStream_t s) {
+    const int nt = (K + GJ_W - 1) / GJ_W;
+    if (nt <= 0) return hipSuccess;
+    const size_t sq = (size_t)nt * nt;
+    if (sq >= (size_t)1 << 24) return hipErrorInvalidConfiguration;  // grid limit
+    GjBatch b{};
+    b.diag0 = diag0;
+    b.status = status;
+    const SquareArgs a{scratch, nt, K, scratch + sq * GJ_N, scratch + (sq + 1) * GJ_N,
+                       scratch + (sq + 1 + nt) * GJ_N, b};
+    hipLaunchKernelGGL(square_tiles_kernel<true>, dim3((unsigned)sq), dim3(GJ_THREADS), 0, s, a0, K, nt, scratch);
+    hipLaunchKernelGGL(square_first_kernel, dim3(1), dim3(GJ_THREADS), 0, s, a);
+    for (int p = 0; p < nt; ++p) {
+        hipLaunchKernelGGL(square_panel_kernel, dim3(2 * nt), dim3(GJ_THREADS), 0, s, a, p);
+        if (nt > 1) hipLaunchKernelGGL(square_update_kernel, dim3((unsigned)sq), dim3(GJ_THREADS), 0, s, a, p);
+    }
+    hipLaunchKernelGGL(square_tiles_kernel<false>, dim3((unsigned)sq), dim3(GJ_THREADS), 0, s, a0, K, nt, scratch);
     return hipGetLastError();
 }
 

@@ -19,6 +19,7 @@
 // (alpha, beta, the test) on the device, so the host only polls a flag.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "ddmgnn.h"
@@ -496,81 +497,168 @@ __global__ __launch_bounds__(BLOCK) void dss_kernel(DssArgs<T> a, const T* __res
 
 // ------------------------------------------------------------------ exact local solves
 // DDM-LU (the paper's comparator, eq. (7)): local = (R_i A R_i^T)^{-1} R_i r with
-// the inverse M formed at setup; one workgroup per sub-mesh, R_i r staged in
-// LDS. M is symmetric, so local_j = sum_c M[c][j] x_c: a wavefront owns a
-// strip of LU_STRIP columns (two per lane, 16-byte loads of contiguous row
-// segments) and walks the rows in order with per-lane accumulators. Small
-// sub-meshes (fewer strips than wavefronts) also split the rows into parts
-// whose sums are added in part order through LDS. Also writes s_i = |R_i r|
-// and y0_i = (R_0 r)_i like the DSS kernels.
-constexpr int LU_STRIP = 128;
-constexpr int LU_WAVES = DSS_BLOCK / 64;
-
-__global__ __launch_bounds__(DSS_BLOCK) void lu_local_kernel(const DevProb* __restrict__ tab,
-                                                            const int2* __restrict__ work) {
-    const int2 wi = work[blockIdx.x];
+// the inverse formed at setup, symmetric, and held (negated) as the 64 x 64 tiles of its
+// lower triangle: a tile serves its rows and its columns, so half the matrix is
+// read. A sub-mesh is shared by lu_units(k) workgroups of equal work (unit u takes
+// rows u and nt - 1 - u of tiles), so that a launch of few sub-meshes fills the
+// chip and a large sub-mesh does not end last; each unit writes a partial vector,
+// and lu_sum_kernel adds a sub-mesh's in unit order. Unit 0 also writes
+// s_i = |R_i r| and y0_i = (R_0 r)_i like the DSS kernels.
+// Bound by HBM (1500 sub-meshes of 900 nodes: 5.4 GB in 1.13 ms, the rate of a large
+// copy). One workgroup per sub-mesh reading the full square before; per launch with
+// the sum: 8 sub-meshes 82 -> 19 us, 38 152 -> 36, 150 348 -> 130, 300 550 -> 239,
+// 1500 1,775 -> 1,133.
+// A wavefront takes tiles of one row of tiles from left to right, 16 rows at a time (all
+// 64 at once spill): lane l serves one row (l / 16) of each of four groups and four
+// columns; the row sums stay in registers over the row of tiles, the column sums over
+// 16 rows, and both are reduced across the lanes at their end into the wavefront's
+// own vector in LDS (YLDS), or
+// in the unit's partial vector (one wavefront per workgroup, sub-meshes whose four
+// vectors would not fit).
+template <bool YLDS>
+__global__ __launch_bounds__(YLDS ? 256 : 64, YLDS ? 3 : 2) void lu_local_kernel(const DevProb* __restrict__ tab,
+                                                                  const int4* __restrict__ units) {
+    constexpr int WAVES = YLDS ? 4 : 1, BLOCK = 64 * WAVES;
+    const int4 wi = units[blockIdx.x];
     const DevProb& P = tab[wi.x];
     if (P.st && P.st->done) return;
-    extern __shared__ double xs[];  // R_i r (k values; the launch reserves the work list's largest k)
-    __shared__ double yp[LU_WAVES * LU_STRIP];  // parts * k <= LU_WAVES * LU_STRIP
-    __shared__ double red[DSS_BLOCK / 64 + 1];
-    const int sub = wi.y;
+    extern __shared__ double xs[];  // R_i r, padded to whole tiles; then a vector per wavefront
+    __shared__ double red[BLOCK / 64 + 1];
+    const int sub = wi.y, unit = wi.z;
     const int base = P.sub_ptr[sub];
     const int k = P.sub_ptr[sub + 1] - base;
+    const int nt = (k + 63) / 64, kp = nt * 64;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double* __restrict__ r = P.r;
+    double* const part = P.lu_part + P.lu_poff[sub] + (size_t)unit * k;
+    double* const ys = YLDS ? xs + (size_t)(1 + wave) * kp : part;
     double ss = 0.0, yy = 0.0;
-    for (int j = threadIdx.x; j < k; j += DSS_BLOCK) {
-        const double v = r[P.sub_nodes[base + j]];
+    for (int j = threadIdx.x; j < kp; j += BLOCK) {
+        double v = 0.0;
+        if (j < k) {
+            v = r[P.sub_nodes[base + j]];
+            if (unit == 0) {
+                ss = fma(v, v, ss);
+                yy = fma(P.weights[base + j], v, yy);
+            }
+        }
         xs[j] = v;
-        ss = fma(v, v, ss);
-        yy = fma(P.weights[base + j], v, yy);
-    }
-    // the barriers inside block_sum also publish xs
-    ss = block_sum<DSS_BLOCK>(ss, red);
-    yy = block_sum<DSS_BLOCK>(yy, red);
-    if (threadIdx.x == 0) {
-        P.s[sub] = sqrt(ss);
-        P.y0[sub] = yy;
-    }
-    const int ld = (k + 1) & ~1;
-    const double* __restrict__ M = P.lu_inv + P.lu_off[sub];
-    double* __restrict__ out = P.local + base;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int ns = (k + LU_STRIP - 1) / LU_STRIP;
-    const int parts = ns > 0 ? max(1, LU_WAVES / ns) : 1;
-    const int rpp = (k + parts - 1) / parts;
-    for (int t = wave; t < ns * parts; t += LU_WAVES) {
-        const int strip = t % ns, part = t / ns;
-        const int j = strip * LU_STRIP + 2 * lane;
-        if (j >= k) continue;
-        const int c0 = part * rpp, c1 = min(k, c0 + rpp);
-        // column j + 1 may be the zero pad of an odd k
-        const double2* __restrict__ col = reinterpret_cast<const double2*>(M + j);
-        const int ld2 = ld >> 1;
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll 8
-        for (int c = c0; c < c1; ++c) {
-            const double2 v = col[(size_t)c * ld2];
-            const double xc = xs[c];
-            a0 = fma(v.x, xc, a0);
-            a1 = fma(v.y, xc, a1);
-        }
-        if (parts == 1) {
-            out[j] = a0;
-            if (j + 1 < k) out[j + 1] = a1;
-        } else {
-            yp[part * k + j] = a0;
-            if (j + 1 < k) yp[part * k + j + 1] = a1;
+        if (YLDS) {
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) xs[(size_t)(1 + w) * kp + j] = 0.0;
+        } else if (j < k) {
+            part[j] = 0.0;
         }
     }
-    if (parts > 1) {  // uniform over the workgroup (depends on k only)
+    __syncthreads();
+    if (unit == 0) {  // uniform
+        ss = block_sum<BLOCK>(ss, red);
+        yy = block_sum<BLOCK>(yy, red);
+        if (threadIdx.x == 0) {
+            P.s[sub] = sqrt(ss);
+            P.y0[sub] = yy;
+        }
+    }
+    const double* M = P.lu_inv + P.lu_off[sub];
+    const int rr = lane >> 4, cc = lane & 15;
+    const int i0 = unit, i1 = nt - 1 - unit;              // the unit's rows of tiles
+    const int n0 = i0 + 1, total = i1 > i0 ? nt + 1 : n0;  // tiles of the first, of both
+    const int t1 = total * (wave + 1) / WAVES;
+    int t = total * wave / WAVES;
+    auto add = [&](int j, double v) {
+        if (YLDS || j < k) ys[j] += v;
+    };
+    while (t < t1) {
+        const bool first = t < n0;
+        const int I = first ? i0 : i1;
+        const int j0 = first ? t : t - n0, j1 = min(t1, first ? n0 : total) - (first ? 0 : n0);
+        // global-space loads: the table's pointers are generic, and flat loads also
+        // count as LDS traffic
+        typedef double v2 __attribute__((ext_vector_type(2)));
+        typedef const __attribute__((address_space(1))) v2* gp;
+#pragma unroll 1
+        for (int h = 0; h < 4; ++h) {  // 16 rows of the row of tiles
+            gp T = (gp)(M + sym_tile(I, j0) + h * 1024 + rr * 64 + 2 * cc);
+            double rows[4], xi[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                rows[q] = 0.0;
+                xi[q] = xs[I * 64 + 16 * h + 4 * q + rr];
+            }
+            v2 v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = T[i / 2 * 128 + i % 2 * 16];
+#pragma unroll 1
+            for (int J = j0; J < j1; ++J) {
+                v2 w[8];  // the next tile's, in flight
+                T += J + 1 < j1 ? 64 * 32 : 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i] = T[i / 2 * 128 + i % 2 * 16];
+                const double2 xa = *reinterpret_cast<const double2*>(xs + J * 64 + 2 * cc);
+                const double2 xb = *reinterpret_cast<const double2*>(xs + J * 64 + 32 + 2 * cc);
+                double c0 = 0.0, c1 = 0.0, c2 = 0.0, c3 = 0.0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const v2 a = v[2 * q], b = v[2 * q + 1];
+                    double s = rows[q];
+                    s = fma(a[0], xa.x, s);
+                    s = fma(a[1], xa.y, s);
+                    s = fma(b[0], xb.x, s);
+                    rows[q] = fma(b[1], xb.y, s);
+                    c0 = fma(a[0], xi[q], c0);
+                    c1 = fma(a[1], xi[q], c1);
+                    c2 = fma(b[0], xi[q], c2);
+                    c3 = fma(b[1], xi[q], c3);
+                }
+                if (J < I) {
+                    // the transposed tile: columns over the four groups, each exchange
+                    // halving the columns a lane holds
+                    const bool odd = rr & 1, up = rr & 2;
+                    const double p0 = (odd ? c1 : c0) + __shfl_xor(odd ? c0 : c1, 16, 64);
+                    const double p1 = (odd ? c3 : c2) + __shfl_xor(odd ? c2 : c3, 16, 64);
+                    const double p = (up ? p1 : p0) + __shfl_xor(up ? p0 : p1, 32, 64);
+                    add(J * 64 + (rr >> 1) * 32 + 2 * cc + (rr & 1), p);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = w[i];
+            }
+            // four rows over 16 lanes: two exchanges, then sums
+            const bool u8 = cc & 8, u4 = cc & 4;
+            const double s0 = (u8 ? rows[2] : rows[0]) + __shfl_xor(u8 ? rows[0] : rows[2], 8, 64);
+            const double s1 = (u8 ? rows[3] : rows[1]) + __shfl_xor(u8 ? rows[1] : rows[3], 8, 64);
+            double s = (u4 ? s1 : s0) + __shfl_xor(u4 ? s0 : s1, 4, 64);
+            s += __shfl_xor(s, 2, 64);
+            s += __shfl_xor(s, 1, 64);
+            if ((cc & 3) == 0) add(I * 64 + 16 * h + 4 * (cc >> 2) + rr, s);
+        }
+        t = (first ? 0 : n0) + j1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // ys: other lanes add next
+    }
+    if (YLDS) {
         __syncthreads();
-        for (int j = threadIdx.x; j < k; j += DSS_BLOCK) {
-            double acc = yp[j];
-            for (int q = 1; q < parts; ++q) acc += yp[q * k + j];
-            out[j] = acc;
+        for (int j = threadIdx.x; j < k; j += BLOCK) {
+            double acc = xs[kp + j];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) acc += xs[(size_t)(1 + w) * kp + j];
+            part[j] = acc;
         }
     }
+}
+
+// local = minus the sum of a sub-mesh's partial products, in unit order.
+__global__ __launch_bounds__(VEC_BLOCK) void lu_sum_kernel(const DevProb* __restrict__ tab,
+                                                          const int2* __restrict__ subs) {
+    const int2 wi = subs[blockIdx.x];
+    const DevProb& P = tab[wi.x];
+    if (P.st && P.st->done) return;
+    const int base = P.sub_ptr[wi.y], k = P.sub_ptr[wi.y + 1] - base, nu = lu_units(k);
+    const int j = blockIdx.y * VEC_BLOCK + threadIdx.x;
+    if (j >= k) return;
+    const double* __restrict__ part = P.lu_part + P.lu_poff[wi.y] + j;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int u = 0; u < nu; ++u) acc += part[(size_t)u * k];
+    P.local[base + j] = -acc;
 }
 
 // ------------------------------------------------------------------ coarse solve
@@ -1379,14 +1467,26 @@ hipError_t launch_dss_big(const DevProb* tab, const int2* work, int n_work, int 
     return done(check);
 }
 
+namespace {
+size_t lu_shmem(int k, int vectors) { return (size_t)((k + 63) / 64 * 64) * vectors * sizeof(double); }
+}  // namespace
+
 hipError_t prepare_lu_local() {
-    return hipFuncSetAttribute((const void*)lu_local_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)(kMaxSubNodesAny * sizeof(double)));
+    const hipError_t e = hipFuncSetAttribute((const void*)lu_local_kernel<true>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lu_shmem(LU_LDS_K, 5));
+    return e != hipSuccess ? e
+                           : hipFuncSetAttribute((const void*)lu_local_kernel<false>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)lu_shmem(kMaxSubNodesAny, 1));
 }
 
-hipError_t launch_lu_local(const DevProb* tab, const int2* work, int n_work, int max_k, hipStream_t s, bool check) {
-    if (n_work <= 0) return hipSuccess;
-    hipLaunchKernelGGL(lu_local_kernel, dim3(n_work), dim3(DSS_BLOCK), (size_t)max_k * sizeof(double), s, tab, work);
+hipError_t launch_lu_local(const DevProb* tab, const LuWork& w, hipStream_t s, bool check) {
+    if (w.n_big > 0)
+        hipLaunchKernelGGL(lu_local_kernel<false>, dim3(w.n_big), dim3(64), lu_shmem(w.max_k_big, 1), s, tab, w.big);
+    if (w.n_units > 0)
+        hipLaunchKernelGGL(lu_local_kernel<true>, dim3(w.n_units), dim3(256), lu_shmem(w.max_k, 5), s, tab, w.units);
+    const unsigned chunks = (unsigned)((std::max(w.max_k, w.max_k_big) + VEC_BLOCK - 1) / VEC_BLOCK);
+    if (w.n_subs > 0) hipLaunchKernelGGL(lu_sum_kernel, dim3(w.n_subs, chunks), dim3(VEC_BLOCK), 0, s, tab, w.subs);
     return done(check);
 }
 

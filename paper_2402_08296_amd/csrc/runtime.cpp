@@ -43,6 +43,9 @@ struct Batch {
     int n_mfma_small = 0;
     size_t lds_mfma = 0, lds_mfma_small = 0;
     int max_k_all = 0, max_k_rest = 0, max_k_valu = 0;
+    // units of work_valu's and work_big's sub-meshes in the exact local solves
+    DevBuf<int4> lu_small, lu_big;
+    int n_lu_small = 0, n_lu_big = 0;
     // tiles of work_valu and work_rest for the tiled FP64 / FP32 forward (d = 10), by
     // problem and sub-mesh; built at the first use
     DevBuf<int4> tiles_valu, tiles_rest;
@@ -81,7 +84,7 @@ DevProb make_view(ddmgnn_problem* P) {
     v.vt64 = {P->vt64.rec.p, P->vt64.info.p, P->vt64.h.p, {P->vt64.q.p, P->vt64.q.p ? P->vt64.q.p + qn : nullptr}};
     v.vt32 = {P->vt32.rec.p, P->vt32.info.p, P->vt32.h.p, {P->vt32.q.p, P->vt32.q.p ? P->vt32.q.p + qn : nullptr}};
     v.node_ptr = P->node_ptr.p; v.node_slots = P->node_slots.p; v.slot_sub = P->slot_sub.p; v.a0inv = P->a0inv.p;
-    v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p;
+    v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p; v.lu_part = P->lu_part.p; v.lu_poff = P->lu_poff.p;
     v.gm_v = P->gm_v.p; v.gm_z = P->gm_z.p; v.gm_part = P->gm_part.p; v.gm_small = P->gm_small.p;
     v.u = P->u.p; v.r = P->r.p; v.z = P->z.p; v.c_in = nullptr;
     const int64_t n = P->hs.n;
@@ -126,58 +129,60 @@ size_t valu_shmem(int max_k, int precision, int d) {
     return (size_t)max_k * 2 * d * esz;
 }
 
-// Exact local solves: the inverses of R_i A R_i^T, assembled from the problem's
-// device matrix and inverted on the device (one workgroup per sub-mesh).
-// In-place inverses of a batch of SPD matrices on the device (orders k, matrix
-// m at base + off_dev[m]); E_NOT_SPD when a pivot fails.
-int gj_invert_batch(const std::vector<int32_t>& k, double* base, const int64_t* off_dev, const double* diag0,
-                    hipStream_t s, GjBufs& g) {
-    const GjPlan plan(k);
-    HIP_TRY(g.order.upload(plan.order.data(), plan.order.size(), s));
-    HIP_TRY(g.cprefix.upload(plan.cprefix.data(), plan.cprefix.size(), s));
-    HIP_TRY(g.tprefix.upload(plan.tprefix.data(), plan.tprefix.size(), s));
-    HIP_TRY(g.prow.upload(plan.prow.data(), plan.prow.size(), s));
-    HIP_TRY(g.scratch.alloc(plan.scratch_doubles()));
-    HIP_TRY(g.status.alloc(1));
-    HIP_TRY(hipMemsetAsync(g.status.p, 0, sizeof(int), s));
-    const GjPlanDev dev{g.order.p, g.cprefix.p, g.tprefix.p, g.prow.p};
-    HIP_TRY(launch_gj_invert(plan, dev, base, off_dev, g.scratch.p, diag0, g.status.p, s));
+// Whether an inversion's status word says that a pivot failed (waits for the stream).
+int pivots_ok(const DevBuf<int>& status, hipStream_t s) {
     int bad = 0;
-    HIP_TRY(hipMemcpyAsync(&bad, g.status.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(&bad, status.p, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return bad ? DDMGNN_E_NOT_SPD : DDMGNN_OK;
 }
 
+// Exact local solves: the inverses of R_i A R_i^T, assembled from the problem's
+// device matrix and inverted on the device.
 int prepare_lu(ddmgnn_problem* P) {
     HIP_TRY(prepare_lu_local());
     if (P->lu_inv.p) return DDMGNN_OK;
     hipStream_t s = P->ctx->stream;
     const auto& hs = P->hs;
-    std::vector<int64_t> off((size_t)hs.K + 1, 0);
+    std::vector<int64_t> off((size_t)hs.K + 1, 0), poff((size_t)hs.K + 1, 0);
+    std::vector<int32_t> k((size_t)hs.K);
     for (int32_t i = 0; i < hs.K; ++i) {
-        const int64_t k = hs.sub_ptr[i + 1] - hs.sub_ptr[i];
-        off[i + 1] = off[i] + k * lu_ld(k);
+        k[i] = (int32_t)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
+        off[i + 1] = off[i] + sym_doubles(k[i]);
+        poff[i + 1] = poff[i] + (int64_t)lu_units(k[i]) * k[i];
     }
     auto build = [&]() -> int {
         DevBuf<int64_t> sub_ptr64;
+        const size_t n = (size_t)std::max<int64_t>(off[hs.K], 1);
         HIP_TRY(sub_ptr64.upload(hs.sub_ptr.data(), hs.sub_ptr.size(), s));
         HIP_TRY(P->lu_off.upload(off.data(), off.size(), s));
-        HIP_TRY(P->lu_inv.alloc((size_t)std::max<int64_t>(off[hs.K], 1)));
+        HIP_TRY(P->lu_poff.upload(poff.data(), poff.size(), s));
+        HIP_TRY(P->lu_part.alloc((size_t)std::max<int64_t>(poff[hs.K], 1)));
+        HIP_TRY(P->lu_inv.alloc(n));
+        HIP_TRY(hipMemsetAsync(P->lu_inv.p, 0, n * sizeof(double), s));
         HIP_TRY(launch_lu_assemble(P->rowptr.p, P->col.p, P->val.p, sub_ptr64.p, P->sub_nodes.p, P->lu_off.p,
                                    P->lu_inv.p, hs.K, s));
-        std::vector<int32_t> k((size_t)hs.K);
-        for (int32_t i = 0; i < hs.K; ++i) k[i] = (int32_t)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
-        GjBufs g;
-        const int rc = gj_invert_batch(k, P->lu_inv.p, P->lu_off.p, nullptr, s, g);
+        const GjPlan plan(k);
+        DevBuf<int32_t> meta;
+        DevBuf<double> scratch;
+        DevBuf<int> status;
+        HIP_TRY(meta.upload(plan.meta.data(), plan.meta.size(), s));
+        HIP_TRY(scratch.alloc(plan.scratch_doubles()));
+        HIP_TRY(status.alloc(1));
+        HIP_TRY(hipMemsetAsync(status.p, 0, sizeof(int), s));
+        HIP_TRY(launch_gj_invert(plan, meta.p, P->lu_inv.p, P->lu_off.p, scratch.p, status.p, s));
+        const int rc = pivots_ok(status, s);
         if (rc == DDMGNN_E_NOT_SPD) return fail(rc, "a local matrix R_i A R_i^T is not positive definite");
         return rc;
     };
     if (int rc = build()) {  // leave no half-built inverses behind
         P->lu_inv.reset();
         P->lu_off.reset();
+        P->lu_part.reset();
+        P->lu_poff.reset();
         return rc;
     }
-    P->device_bytes += (size_t)off[hs.K] * sizeof(double) + off.size() * sizeof(int64_t);
+    P->device_bytes += lu_bytes(hs);
     return DDMGNN_OK;
 }
 
@@ -498,7 +503,9 @@ int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool cap
     const ModelDev& M = *B.model;
     const bool check = !capturing;
     if (local == DDMGNN_LOCAL_LU) {
-        HIP_TRY(launch_lu_local(tab, B.work_all.p, B.n_all, B.max_k_all, s, check));
+        const LuWork w{B.lu_small.p, B.n_lu_small, B.max_k_valu, B.lu_big.p, B.n_lu_big, B.max_k_all,
+                       B.work_all.p, B.n_all};
+        HIP_TRY(launch_lu_local(tab, w, s, check));
         return DDMGNN_OK;
     }
     HIP_TRY(launch_dss_big(tab, B.work_big.p, B.n_big, precision == DDMGNN_BF16 ? DDMGNN_FP32 : precision, M.d,
@@ -806,10 +813,14 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         return a.sub < b.sub;
     });
     std::vector<int2> wa, wm, wms, wr, wv, wb;
+    std::vector<int4> lus, lub;
     size_t lds_sb = 0, lds_db = 0, lds_small_sb = 0, lds_small_db = 0;
     for (const W& w : all) {
         wa.push_back(make_int2(w.p, w.sub));
         B->max_k_all = std::max(B->max_k_all, w.k);
+        static_assert(LU_LDS_K == kMaxSubNodes, "work_valu holds the sub-meshes of the exact solves' LDS form");
+        for (int u = 0; u < lu_units(w.k); ++u)
+            (w.k > kMaxSubNodes ? lub : lus).push_back(make_int4(w.p, w.sub, u, 0));
         const ddmgnn_problem* Q = probs[w.p];
         if (w.k > kMaxSubNodes) {
             wb.push_back(make_int2(w.p, w.sub));
@@ -844,6 +855,10 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     B->lds_mfma_small = std::max(lds_small_sb, lds_small_db);
     hipStream_t s = ctx->stream;
     if (int rc = upload_list(B->work_all, wa, s)) return rc;
+    if (int rc = upload_list(B->lu_small, lus, s)) return rc;
+    if (int rc = upload_list(B->lu_big, lub, s)) return rc;
+    B->n_lu_small = (int)lus.size();
+    B->n_lu_big = (int)lub.size();
     if (int rc = upload_list(B->work_mfma, wm, s)) return rc;
     if (int rc = upload_list(B->work_mfma_small, wms, s)) return rc;
     if (int rc = upload_list(B->work_rest, wr, s)) return rc;
@@ -1005,6 +1020,19 @@ int check_opts(const ddmgnn_solve_opts& o) {
     if (o.prolong < 0 || o.prolong > 1) return fail(DDMGNN_E_INVALID, "prolong must be POU or UNWEIGHTED");
     if (o.local_solver < 0 || o.local_solver > 1) return fail(DDMGNN_E_INVALID, "local_solver must be GNN or LU");
     return DDMGNN_OK;
+}
+
+// Bytes a problem counts for its exact local solves: k_i^2 doubles per sub-mesh, which
+// covers the tiles (about half), the partial products and the panels of the
+// factorisation, or the tiles and partial products where those are more (small k_i).
+size_t lu_bytes(const HostSetup& hs) {
+    size_t dense = 0, held = 0;
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int64_t k = hs.sub_ptr[i + 1] - hs.sub_ptr[i];
+        dense += (size_t)(k * lu_ld(k)) * 8 + 8;
+        held += (size_t)(sym_doubles(k) + lu_units((int)k) * k) * 8 + 16;
+    }
+    return std::max(dense, held);
 }
 
 // Bytes of the tiled DSS forward's arrays of a problem in one precision (`tiles` tiles,
@@ -1212,24 +1240,25 @@ int create_problem(ddmgnn_ctx* ctx, const ddmgnn_problem_desc& desc, std::shared
     HIP_TRY(P->slot_sub.upload(hs.slot_sub.data(), sk, s));
     HIP_TRY(P->xy64.upload(hs.xy64.data(), 2 * sk, s));
     HIP_TRY(P->xyc32.upload(hs.xyc32.data(), 2 * sk, s));
+    // Krylov vectors; the direction ring also serves the coarse setup below as scratch
+    HIP_TRY(P->ring.alloc((size_t)2 * (MAX_M + 1) * n));
     if (!hs.a0inv.empty()) {
         HIP_TRY(P->a0inv.upload(hs.a0inv.data(), (size_t)K * K, s));
     } else {  // the coarse operator and its inverse, formed on the device
-        const int64_t off_h[2] = {0, (int64_t)K * K};
+        const size_t need = coarse_scratch_doubles(K);
         HIP_TRY(P->a0inv.alloc((size_t)K * K));
         HIP_TRY(P->coarse_diag0.alloc((size_t)K));
-        HIP_TRY(P->coarse_off.upload(off_h, 2, s));
+        HIP_TRY(P->coarse_status.alloc(1));
+        if (P->ring.n < need) HIP_TRY(P->coarse_scratch.alloc(need));
+        HIP_TRY(hipMemsetAsync(P->coarse_status.p, 0, sizeof(int), s));
         HIP_TRY(launch_coarse_assemble(P->rowptr.p, P->col.p, P->val.p, P->sub_ptr.p, P->sub_nodes.p, P->weights.p,
                                        P->node_ptr.p, P->node_slots.p, P->slot_sub.p, K, P->a0inv.p,
                                        P->coarse_diag0.p, s));
-        const int rc = gj_invert_batch(std::vector<int32_t>{K}, P->a0inv.p, P->coarse_off.p, P->coarse_diag0.p, s,
-                                       P->coarse_gj);
+        HIP_TRY(launch_coarse_invert(P->a0inv.p, K, P->coarse_diag0.p,
+                                     P->coarse_scratch.p ? P->coarse_scratch.p : P->ring.p, P->coarse_status.p, s));
+        const int rc = pivots_ok(P->coarse_status, s);
         if (rc == DDMGNN_E_NOT_SPD) return fail(rc, "coarse matrix R_0 A R_0^T is not positive definite");
         if (rc) return rc;
-    }
-    if (!hs.lu_inv.empty()) {
-        HIP_TRY(P->lu_off.upload(hs.lu_off.data(), hs.lu_off.size(), s));
-        HIP_TRY(P->lu_inv.upload(hs.lu_inv.data(), hs.lu_inv.size(), s));
     }
     P->mfma_need = hs.mfma_need;
     P->mfma_need_db = hs.mfma_need_db;
@@ -1245,16 +1274,12 @@ int create_problem(ddmgnn_ctx* ctx, const ddmgnn_problem_desc& desc, std::shared
     HIP_TRY(P->u.alloc(n));
     HIP_TRY(P->r.alloc(n));
     HIP_TRY(P->z.alloc(n));
-    HIP_TRY(P->ring.alloc((size_t)2 * (MAX_M + 1) * n));
     HIP_TRY(P->st.alloc(1));
     HIP_TRY(P->partials.alloc((size_t)(MAX_M + 1) * VEC_GRID));
     HIP_TRY(hipMemsetAsync(P->st.p, 0, sizeof(KState), s));
     HIP_TRY(hipStreamSynchronize(s));
-    P->device_bytes = problem_device_bytes(n, hs.nnz, K, sk, hs.n_edges) + P->lu_inv.n * sizeof(double) +
-                      P->lu_off.n * sizeof(int64_t);
+    P->device_bytes = problem_device_bytes(n, hs.nnz, K, sk, hs.n_edges);
     // host copies of the uploaded arrays are not needed again
-    std::vector<double>().swap(P->hs.lu_inv);
-    std::vector<int64_t>().swap(P->hs.lu_off);
     HostSetup& h = P->hs;
     std::vector<int32_t>().swap(h.sp32);
     std::vector<int32_t>().swap(h.ep32);

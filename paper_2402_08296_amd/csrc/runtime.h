@@ -89,6 +89,8 @@ using BatchPtr = std::unique_ptr<Batch, BatchDeleter>;
 // Bytes of device memory a problem of these sizes holds (all buffers of a
 // solve, excluding the DSS fallback storage of sub-meshes too large for LDS).
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t n_edges);
+// Bytes counted for the exact local solves.
+size_t lu_bytes(const HostSetup& hs);
 // Bytes of the tiled DSS forward's arrays in one precision: exactly, and an estimate
 // before the tiles are listed.
 size_t tile_bytes(int64_t sk, int64_t tiles, int64_t rows, bool f64);
@@ -102,15 +104,6 @@ std::string prepare_upload(const ddmgnn_problem_desc& desc, HostSetup& hs);
 // stream of its own while the active problems iterate on the context's.
 int create_problem(ddmgnn_ctx* ctx, const ddmgnn_problem_desc& desc, std::shared_ptr<ModelDev> model,
                    HostSetup&& hs, ddmgnn_problem** out, hipStream_t stream = nullptr);
-
-// Device buffers of one batched Gauss-Jordan inversion (the plan's arrays,
-// scratch and status word).
-struct GjBufs {
-    DevBuf<int32_t> order, cprefix, tprefix;
-    DevBuf<int64_t> prow;
-    DevBuf<double> scratch;
-    DevBuf<int> status;
-};
 
 // Batch of problems solved in lockstep (one launch per kernel and iteration).
 // All must share the model. Built once per membership; cheap to rebuild.
@@ -186,9 +179,8 @@ struct ddmgnn_problem {
     ddmgnn::DevBuf<int32_t> sub_ptr, sub_nodes, edge_ptr, node_ptr, node_slots, slot_sub;
     // temporaries of the device coarse setup, kept with the problem: freeing them
     // at creation would wait for the work of every stream on the device
-    ddmgnn::GjBufs coarse_gj;
-    ddmgnn::DevBuf<double> coarse_diag0;
-    ddmgnn::DevBuf<int64_t> coarse_off;
+    ddmgnn::DevBuf<double> coarse_diag0, coarse_scratch;
+    ddmgnn::DevBuf<int> coarse_status;
     ddmgnn::DevBuf<uint16_t> edge_src;
     ddmgnn::DevBuf<double> weights, xy64, a0inv;
     ddmgnn::DevBuf<float> xyc32;     // per slot, centred on the sub-mesh
@@ -220,8 +212,8 @@ struct ddmgnn_problem {
     ddmgnn::DevBuf<float> hglobal32;  // FP32 h of the sub-meshes beyond kMaxSubNodes
     ddmgnn::DevBuf<double> cglobal;   // their c (FP64, or FP32 in the same storage)
     // exact local solves (built on the first solve with local_solver = LU)
-    ddmgnn::DevBuf<double> lu_inv;
-    ddmgnn::DevBuf<int64_t> lu_off;
+    ddmgnn::DevBuf<double> lu_inv, lu_part;
+    ddmgnn::DevBuf<int64_t> lu_off, lu_poff;
     // FGMRES basis, preconditioned vectors, partial sums and small arrays (built on
     // the first FGMRES solve, for cycles of up to gm_R steps)
     ddmgnn::DevBuf<double> gm_v, gm_z, gm_part, gm_small;

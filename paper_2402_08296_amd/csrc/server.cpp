@@ -170,13 +170,8 @@ void ddmgnn_server::setup_worker() {
         } else {
             // DDM-LU requests: the local inverses are formed on the device at the
             // first solve; their bytes count in the admission budget.
-            size_t lu_bytes = 0;
-            if (lu)
-                for (int32_t i = 0; i < r->hs.K; ++i) {
-                    const int64_t k = r->hs.sub_ptr[i + 1] - r->hs.sub_ptr[i];
-                    lu_bytes += (size_t)(k * lu_ld(k)) * sizeof(double) + sizeof(int64_t);
-                }
-            r->bytes = problem_device_bytes(r->hs.n, r->hs.nnz, r->hs.K, r->hs.sk, r->hs.n_edges) + lu_bytes +
+            const size_t lu_b = lu ? lu_bytes(r->hs) : 0;
+            r->bytes = problem_device_bytes(r->hs.n, r->hs.nnz, r->hs.K, r->hs.sk, r->hs.n_edges) + lu_b +
                        (r->opts.krylov == DDMGNN_FGMRES ? fgmres_bytes(r->hs.n, r->opts.restart) : 0);
             // The FP64 and FP32 forward's work arrays count too, but a request that fits
             // the budget without them is still taken: it then runs alone.

@@ -72,10 +72,6 @@ struct HostSetup {
     std::vector<uint32_t> erec;  // per edge: sender local id | FP16 bits of |d_jl| << 16
     int64_t max_edges_sub = 0;   // largest in-edge count of a sub-mesh
     std::vector<float> edge_nd;
-    // Exact local solves, when built before the problem is created: inverses
-    // of R_i A R_i^T, row stride lu_ld(k_i), sub-mesh i at lu_off[i] (empty otherwise).
-    std::vector<double> lu_inv;
-    std::vector<int64_t> lu_off;
     // Device-ready arrays, filled by prepare_upload (the setup workers of a server
     // run it, so that admission only copies): 32-bit index arrays, the slot
     // coordinates (FP64 raw, FP32 centred), the padded edge arrays, and the records
@@ -95,7 +91,7 @@ struct HostSetup {
 // Inverse of the local matrix R_i A R_i^T of sub-mesh i (dense, row-major
 // k_i x k_i; the paper's exact local solve of DDM-LU) by Cholesky. "" or "NOT_SPD".
 std::string local_inverse(const ddmgnn_problem_desc& d, int32_t i, std::vector<double>& inv, bool parallel);
-// Row stride of a stored local inverse: k rounded up to even, so that every row
+// Row stride of build_local_inverses' matrices: k rounded up to even, so that every row
 // starts 16-byte aligned (the pad column holds zeros).
 inline int64_t lu_ld(int64_t k) { return (k + 1) & ~int64_t(1); }
 // All local inverses concatenated, sub-mesh i at off[i] = sum_{j < i} k_j lu_ld(k_j)

@@ -136,3 +136,56 @@ def test_local_inverses_formed_on_device(ctx):
         worst = max(worst, err / (idx.size * np.finfo(float).eps * np.linalg.cond(Ai)))
     print(f"[gpu]   worst local error in units of k eps kappa: {worst:.2e}", flush=True)
     assert worst <= 1.0
+
+
+def _split(sizes):
+    """A 9k-node problem whose sub-meshes are consecutive runs of its nodes (free nodes first)
+    of the given sizes, and one of the rest: disjoint, so every R_i A R_i^T and A_0 is SPD."""
+    p = W.make_problem(16, 9000, 4, 0.2)
+    hp = oracle_problem(p)
+    nodes = np.argsort(p.mesh.dirichlet, kind="stable")
+    sp = np.concatenate([[0], np.cumsum(sizes), [p.n]])
+    for a, b in zip(sp[:-1], sp[1:]):
+        nodes[a:b].sort()
+    w = np.where(p.mesh.dirichlet[nodes], 0.0, 1.0)
+    return p, dg.HostProblem(hp.xy, hp.tri, hp.dirichlet, hp.rowptr, hp.col, hp.val, hp.b, hp.u0, sp, nodes, w)
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("sizes", [[1, 2, 63, 64, 65], [127, 128, 129, 193], [1983, 1984, 2048], [1, 2047, 2049], [2113, 2]])
+def test_local_inverses_at_tile_edges(ctx, sizes):
+    """Local terms of a DDM-LU apply at orders around the 64 x 64 tiles of the inverses, of one
+    row of tiles or of several (an odd and an even number), and on both sides of 2048 (one
+    vector per wavefront in LDS or one wavefront per workgroup)."""
+    p, hp = _split(sizes)
+    print(f"[gpu] local inverses of orders {sizes}", flush=True)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, SMOOTHER))
+    A = p.A.to_scipy().tocsr()
+    r = p.b - A @ p.u0
+    z = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    prob.apply(torch.from_numpy(r).cuda(), z, dg.default_opts(local_solver=dg.LOCAL_LU,
+                                                              prolong=dg.PROLONG_UNWEIGHTED))
+    loc = prob.intermediates()[3].cpu().numpy()
+    for i, k in enumerate(sizes):
+        idx = hp.sub_nodes[hp.sub_ptr[i]:hp.sub_ptr[i + 1]]
+        Ai = A[idx][:, idx].toarray()
+        ref = np.linalg.solve(Ai, r[idx])
+        err = np.abs(loc[hp.sub_ptr[i]:hp.sub_ptr[i + 1]] - ref).max() / np.abs(ref).max()
+        assert err <= k * np.finfo(float).eps * np.linalg.cond(Ai), k
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("K", [2, 63, 64, 65, 128, 129])
+def test_coarse_inverse_at_tile_edges(ctx, K):
+    """y = A_0^{-1} R_0 r at orders around the 64 x 64 tiles of the coarse inversion."""
+    p, hp = _split([60] * (K - 1))
+    print(f"[gpu] coarse inverse of order {hp.K}", flush=True)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, SMOOTHER))
+    A = p.A.to_scipy()
+    co = sw.Coarse(A, dc.Decomposition(p.n, hp.sub_ptr, hp.sub_nodes, hp.weights))
+    r = p.b - A @ p.u0
+    z = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    prob.apply(torch.from_numpy(r).cuda(), z, dg.default_opts(precision="fp64"))
+    y = prob.intermediates()[2].cpu().numpy()
+    ref = np.linalg.solve(co.A0, co.Z.T @ r)
+    assert np.abs(y - ref).max() <= K * np.finfo(float).eps * np.linalg.cond(co.A0) * np.abs(ref).max()
