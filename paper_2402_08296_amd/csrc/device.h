@@ -27,13 +27,16 @@ constexpr int DSS_WIDE_BLOCK = 1024;  // its form for launches of fewer sub-mesh
 constexpr int N_CU = 256;  // compute units of an MI355X
 constexpr size_t LDS_LIMIT = 160 * 1024;
 
+// Rows of a problem's partial sums: the prolongation's dots, <p, A p> and <p, r>, |r|^2.
+// A kernel that completes another's sums writes its own to other rows.
+constexpr int PART_PROLONG = 0, PART_SPMV = MAX_M + 1, PART_UPDATE = MAX_M + 3, N_PART = MAX_M + 4;
+
 // Krylov scalars of one problem, resident in device memory.
 struct KState {
     double r0n;            // |r_0|
     double rtol;
     double rel;            // |r_it| / |r_0|
-    double alpha;
-    double beta[MAX_M];    // p_new = z + sum_k beta[k] p_(it-1-k)
+    double beta;           // CG: p_new = r + beta p
     double pq[MAX_M + 1];  // <p, A p> of each direction-ring slot
     double rho;            // PCG/CG: <r, z> of the current iteration
     double rr_true;        // |b - A u|^2 at exit
@@ -137,7 +140,7 @@ struct DevProb {
     double* c64;                // normalised local right-hand sides of those sub-meshes (FP64 form),
     float* c32;                 // and the same storage read as FP32 (FP32 form)
     KState* st;                 // null: no Krylov scalars, no done flag
-    double* partials;           // (MAX_M + 1) x VEC_GRID per-workgroup partial sums
+    double* partials;           // N_PART x VEC_GRID per-workgroup partial sums
     // FGMRES storage (null until a problem is solved with FGMRES)
     double* gm_v;               // (restart + 1) x n: Arnoldi basis V
     double* gm_z;               // restart x n: preconditioned vectors Z = M(V)
@@ -255,10 +258,10 @@ hipError_t ov_fill(const int32_t* sets, const uint8_t* sz, int64_t n, const uint
                    const int64_t* sub_ptr, int64_t sk, int32_t* part_cur, int32_t* nodes, double* weights,
                    hipStream_t s);
 hipError_t launch_coarse(const DevProb* tab, const int2* rows, int n_rows, hipStream_t s, bool check);
-// The Krylov launchers end with a finalize launch of one workgroup per
+hipError_t launch_prolong(const DevProb* tab, const int2* blk, int n_blk, const IterArgs& it, hipStream_t s,
+                          bool check);
+// The launchers below end with a finalize launch of one workgroup per
 // problem: n_prob = all problems of the table, or the problems of `list`.
-hipError_t launch_prolong(const DevProb* tab, const int2* blk, int n_blk, int n_prob, const IterArgs& it,
-                          hipStream_t s, bool check);
 // FGMRES: one step of every problem of the table (after its apply) and the
 // normalisation that starts the next step (before it).
 hipError_t launch_fgmres_next(const DevProb* tab, const int2* blk, int n_blk, const IterArgs& it, hipStream_t s,

@@ -45,8 +45,7 @@ static_assert(DssLayout<10>::BLOCK_W == 1251 && DssLayout<5>::BLOCK_W == 351 && 
               "weight block size");
 
 // Which reduction a finalize launch completes.
-enum FinStage { FIN_PROLONG, FIN_SPMV, FIN_UPDATE, FIN_INIT, FIN_RESID, FIN_GM_DOT1, FIN_GM_DOT2, FIN_GM_ROT,
-                FIN_GM_RESTART };
+enum FinStage { FIN_UPDATE, FIN_INIT, FIN_RESID, FIN_GM_ROT, FIN_GM_RESTART };
 
 // ------------------------------------------------------------------ reductions
 // Deterministic: fixed shuffle tree inside a wave, fixed order across waves,
@@ -121,10 +120,15 @@ __device__ inline double vblock_sum(const double (&v)[DSS_VBLOCK / BLOCK], doubl
 
 // Two-kernel reductions of the Krylov iteration: every workgroup of a large
 // kernel stores its partial sums with plain stores (no fence, no shared
-// counter), and a finalize kernel with one workgroup per problem sums them in
-// a fixed order after the large kernel has ended (the kernel boundary makes
+// counter), and a later kernel sums them in a fixed order (the kernel boundary makes
 // the stores visible). The sums therefore do not depend on which workgroup
 // finishes last, nor on the other problems of the launch.
+// The iteration's beta and alpha are summed by every workgroup of the kernel that uses
+// them: a kernel of one workgroup between two large ones is a chain of memory latencies
+// (4.5 us), the sums at the start of the large kernel cost it 1.2 us (SpMV) and 0.8
+// (update) at 77k nodes.
+// Only the finalize kernel at the end of the iteration, one workgroup per problem, writes the
+// problem's state.
 template <int NV>
 __device__ inline void put_partials(double (&v)[NV], double* partials, int lb) {
     __shared__ double sh[NV * (VEC_BLOCK / 64)];
@@ -796,24 +800,40 @@ __global__ __launch_bounds__(VEC_BLOCK) void prolong_kernel(const DevProb* __res
         prolong_rows<-1>(P.node_ptr, P.node_slots, P.slot_sub, P.weights, P.local, y, P.dirichlet, P.r, P.z,
                          nullptr, nullptr, nullptr, nullptr, m, uw, rg, P.n, dots);
     if (mode < 0) return;
-    put_partials<MAX_M + 1>(dots, P.partials, g.lb);
+    put_partials<MAX_M + 1>(dots, P.partials + PART_PROLONG * VEC_GRID, g.lb);
 }
 
 // ------------------------------------------------------------------ Krylov kernels
 // Direction source of the iteration: z = M(r), or r itself for CG (M = I).
 __device__ inline const double* dir_src(const DevProb& P, int mode) { return mode == DDMGNN_CG ? P.r : P.z; }
 
-// Step length from <p, A p> and <p, r> (FCG) or rho (PCG/CG, Algorithm 1).
-__device__ inline void set_alpha(KState* st, const double (&tot)[2], int mode, int slot) {
-    const double pq = tot[0];
-    st->pq[slot] = pq;
-    if (!(pq > 0.0) || !isfinite(pq)) {
-        st->status = isfinite(pq) ? DDMGNN_E_BREAKDOWN : DDMGNN_E_NONFINITE;
-        st->done = 1;
-        st->alpha = 0.0;
+// Whether the curvature <p, A p> admits a step.
+__device__ inline bool curved(double pq) { return pq > 0.0 && isfinite(pq); }
+// Step length from <p, A p> and <p, r> (FCG) or rho = <r, z> (PCG; CG: <r, r>), Algorithm 1.
+__device__ inline double step_length(int mode, double pq, double pr, double rho) {
+    return (mode == DDMGNN_FCG ? pr : rho) / pq;
+}
+
+// The direction's coefficients from the sums of the prolongation.
+// FCG: p_new = z - sum_k (<z, q_k> / <p_k, q_k>) p_k; PCG: beta = rho_{i+1} / rho_i.
+template <int NM>
+__device__ inline void direction(const DevProb& P, const KState* st, const IterArgs& ia, double (&beta)[NM]) {
+    if (ia.mode == DDMGNN_CG) {
+        beta[0] = st->beta;
         return;
     }
-    st->alpha = (mode == DDMGNN_FCG ? tot[1] : st->rho) / pq;
+    const int it = st->it, m = ia.m;
+    const double rho = st->rho;
+    double pq[NM], tot[NM];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) pq[i] = i < m ? st->pq[ring_prev(it, m, i)] : 1.0;
+    sum_partials<NM>(P.partials + PART_PROLONG * VEC_GRID, P.nblk, tot);
+    if (ia.mode == DDMGNN_FCG) {
+#pragma unroll
+        for (int i = 0; i < NM; ++i) beta[i] = i < m ? -tot[i] / pq[i] : 0.0;
+    } else {
+        beta[0] = it == 0 ? 0.0 : tot[0] / rho;
+    }
 }
 
 __device__ __forceinline__ void pupdate_rows(const double* __restrict__ z, double* __restrict__ pn,
@@ -837,13 +857,15 @@ __global__ __launch_bounds__(VEC_BLOCK) void pupdate_kernel(const DevProb* __res
     const Seg g = seg(tab, blk);
     const DevProb& P = *g.P;
     const KState* st = P.st;
+    double beta[MAX_M];
+    direction<MAX_M>(P, st, ia, beta);
     if (st->done) return;
     const int it = st->it, m = ia.m;
     const double* pk[MAX_M] = {nullptr, nullptr, nullptr, nullptr};
     for (int i = 0; i < MAX_M; ++i)
         if (i < m) pk[i] = P.p[ring_prev(it, m, i)];
-    pupdate_rows(dir_src(P, ia.mode), P.p[ring_cur(it, m)], pk[0], pk[1], pk[2], pk[3], st->beta[0], st->beta[1],
-                 st->beta[2], st->beta[3], m, rows_of(g.lb, P.nblk, P.n), P.n);
+    pupdate_rows(dir_src(P, ia.mode), P.p[ring_cur(it, m)], pk[0], pk[1], pk[2], pk[3], beta[0], beta[1], beta[2],
+                 beta[3], m, rows_of(g.lb, P.nblk, P.n), P.n);
 }
 
 // CSR SpMV in groups of VEC_BLOCK consecutive rows (the groups of rows_of). The group's nonzeros are contiguous in CSR:
@@ -900,7 +922,7 @@ __global__ __launch_bounds__(VEC_BLOCK) void spmv_dots_kernel(const DevProb* __r
                     d[0] = fma(p[i], acc, d[0]);
                     d[1] = fma(p[i], r[i], d[1]);
                 });
-    put_partials<2>(d, P.partials, g.lb);
+    put_partials<2>(d, P.partials + PART_SPMV * VEC_GRID, g.lb);
 }
 
 // One kept direction (FCG(1), PCG, CG): p_new = z + beta p_old is formed on the
@@ -911,7 +933,9 @@ __global__ __launch_bounds__(VEC_BLOCK) void spmv_p_dots_kernel(const DevProb* _
                                                                const int2* __restrict__ blk, IterArgs ia) {
     const Seg g = seg(tab, blk);
     const DevProb& P = *g.P;
-    KState* st = P.st;
+    const KState* st = P.st;
+    double beta_1[1];
+    direction<1>(P, st, ia, beta_1);
     if (st->done) return;
     const int it = st->it;
     const int slot = ring_cur(it, 1);
@@ -920,7 +944,7 @@ __global__ __launch_bounds__(VEC_BLOCK) void spmv_p_dots_kernel(const DevProb* _
     double* __restrict__ p_new = P.p[slot];
     double* __restrict__ q = P.q[slot];
     const double* __restrict__ r = P.r;
-    const double beta = st->beta[0];
+    const double beta = beta_1[0];
     double d[2] = {0.0, 0.0};
     spmv_groups(P.rowptr, P.col, P.val, P.n, g.lb, P.nblk, [&](int c) { return fma(beta, p_old[c], z[c]); },
                 [&](int i, double acc) {
@@ -930,7 +954,7 @@ __global__ __launch_bounds__(VEC_BLOCK) void spmv_p_dots_kernel(const DevProb* _
                     d[0] = fma(pi, acc, d[0]);
                     d[1] = fma(pi, r[i], d[1]);
                 });
-    put_partials<2>(d, P.partials, g.lb);
+    put_partials<2>(d, P.partials + PART_SPMV * VEC_GRID, g.lb);
 }
 
 __device__ __forceinline__ void update_rows(double* __restrict__ u, double* __restrict__ r,
@@ -946,17 +970,24 @@ __device__ __forceinline__ void update_rows(double* __restrict__ u, double* __re
     }
 }
 
-// u += alpha p; r -= alpha q; convergence test on |r| / |r_0|.
+// u += alpha p; r -= alpha q, with the partial |r|^2. No step if the curvature admits none.
 __global__ __launch_bounds__(VEC_BLOCK) void update_kernel(const DevProb* __restrict__ tab,
                                                           const int2* __restrict__ blk, IterArgs ia) {
     const Seg g = seg(tab, blk);
     const DevProb& P = *g.P;
-    KState* st = P.st;
-    if (st->done) return;
+    const KState* st = P.st;
     const int slot = ring_cur(st->it, ia.m);
+    double rho = st->rho, dots[2], rz[1];
+    sum_partials<2>(P.partials + PART_SPMV * VEC_GRID, P.nblk, dots);
+    if (ia.mode == DDMGNN_PCG) {
+        sum_partials<1>(P.partials + PART_PROLONG * VEC_GRID, P.nblk, rz);
+        rho = rz[0];
+    }
+    if (st->done || !curved(dots[0])) return;
     double d[1] = {0.0};
-    update_rows(P.u, P.r, P.p[slot], P.q[slot], st->alpha, rows_of(g.lb, P.nblk, P.n), P.n, d);
-    put_partials<1>(d, P.partials, g.lb);
+    update_rows(P.u, P.r, P.p[slot], P.q[slot], step_length(ia.mode, dots[0], dots[1], rho),
+                rows_of(g.lb, P.nblk, P.n), P.n, d);
+    put_partials<1>(d, P.partials + PART_UPDATE * VEC_GRID, g.lb);
 }
 
 __device__ __forceinline__ void residual_rows(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ col,
@@ -1167,70 +1198,79 @@ __global__ __launch_bounds__(VEC_BLOCK) void fgm_resid_kernel(const DevProb* __r
     put_partials<1>(d, P.partials, g.lb);
 }
 
-// Sums of gm_part[k][*] for k = 0..j in fixed order, one wavefront per k.
-__device__ inline void gm_sum_dots(const DevProb& P, int j, double* out) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int k = wave; k <= j; k += VEC_BLOCK / 64) {
+// h_k of a Gram pass into tmp, the sums of gm_part[k][*] in fixed order, one wavefront per
+// k; the second pass adds to column j of H. One workgroup per problem: a chain of
+// memory latencies, so of sixteen wavefronts and eight loads in flight (four wavefronts
+// before: 10.7 us, the mean over cycles of 30 at 100k nodes; 5.2 now).
+constexpr int DOTS_BLOCK = 1024;
+template <bool SECOND>
+__global__ __launch_bounds__(DOTS_BLOCK) void fgm_dots_kernel(const DevProb* __restrict__ tab, IterArgs ia) {
+    const DevProb& P = tab[blockIdx.x];
+    const KState* st = P.st;
+    if (st->done) return;
+    const GmSmall m = gm_small(P, ia.m);
+    const int j = st->gm_j, nblk = P.nblk, lane = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k <= j; k += DOTS_BLOCK / 64) {
+        double* hk = m.H + (size_t)j * m.ld + k;
+        const double* __restrict__ part = P.gm_part + (size_t)k * VEC_GRID;
+        const double h = SECOND && lane == 0 ? *hk : 0.0;
         double acc = 0.0;
-        for (int b = lane; b < P.nblk; b += 64) acc += P.gm_part[(size_t)k * VEC_GRID + b];
+#pragma unroll 8
+        for (int b = lane; b < nblk; b += 64) acc += part[b];
         acc = wave_sum(acc);
-        if (lane == 0) out[k] = acc;
+        if (lane == 0) {
+            m.tmp[k] = acc;
+            *hk = SECOND ? h + acc : acc;
+        }
     }
 }
 
 // Scalar recurrences of one problem from the partial sums of the preceding
-// large kernel; one workgroup per problem (list[blockIdx.x], or blockIdx.x).
+// large kernel; one workgroup per problem (list[blockIdx.x], or blockIdx.x). The time is
+// the chain of dependent loads, so the sums' and the state's are issued together.
+template <int STAGE>
 __global__ __launch_bounds__(VEC_BLOCK) void finalize_kernel(const DevProb* __restrict__ tab,
-                                                            const int* __restrict__ list, int stage, IterArgs ia) {
+                                                            const int* __restrict__ list, IterArgs ia) {
     const DevProb& P = tab[list ? list[blockIdx.x] : blockIdx.x];
     KState* st = P.st;
-    const bool always = stage == FIN_INIT || stage == FIN_RESID;
-    if (!always && st->done) return;
     const bool t0 = threadIdx.x == 0;
-    if (stage == FIN_PROLONG) {
-        double tot[MAX_M + 1];
-        sum_partials<MAX_M + 1>(P.partials, P.nblk, tot);
-        if (!t0) return;
-        const int it = st->it, m = ia.m;
-        if (ia.mode == DDMGNN_FCG) {
-            // p_new = z - sum_k (<z, q_k> / <p_k, q_k>) p_k
-            for (int i = 0; i < MAX_M; ++i) st->beta[i] = i < m ? -tot[i] / st->pq[ring_prev(it, m, i)] : 0.0;
-        } else {
-            // Algorithm 1: beta = rho_{i+1} / rho_i, p = z + beta p
-            const double rho_new = tot[0];
-            st->beta[0] = it == 0 ? 0.0 : rho_new / st->rho;
-            st->rho = rho_new;
+    if constexpr (STAGE == FIN_UPDATE) {
+        const KState old = *st;
+        // the rows of update_kernel, of the SpMV (<p, A p> first) and of the prolongation
+        static_assert(PART_PROLONG == 0 && PART_SPMV == 1 + MAX_M && PART_UPDATE == 3 + MAX_M, "rows");
+        double rr[1], pq[1], rz[1];
+        sum_partials<1>(P.partials + PART_UPDATE * VEC_GRID, P.nblk, rr);
+        sum_partials<1>(P.partials + PART_SPMV * VEC_GRID, P.nblk, pq);
+        if (ia.mode == DDMGNN_PCG) sum_partials<1>(P.partials + PART_PROLONG * VEC_GRID, P.nblk, rz);
+        if (!t0 || old.done) return;
+        if (ia.mode == DDMGNN_PCG) st->rho = rz[0];
+        st->pq[ring_cur(old.it, ia.m)] = pq[0];
+        if (!curved(pq[0])) {
+            st->status = isfinite(pq[0]) ? DDMGNN_E_BREAKDOWN : DDMGNN_E_NONFINITE;
+            st->done = 1;
+            return;
         }
-    } else if (stage == FIN_SPMV) {
-        double tot[2];
-        sum_partials<2>(P.partials, P.nblk, tot);
-        if (t0) set_alpha(st, tot, ia.mode, ring_cur(st->it, ia.m));
-    } else if (stage == FIN_UPDATE) {
-        double tot[1];
-        sum_partials<1>(P.partials, P.nblk, tot);
-        if (!t0) return;
-        const double rr = tot[0];
-        st->it += 1;
-        if (!isfinite(rr)) {
+        st->it = old.it + 1;
+        if (!isfinite(rr[0])) {
             st->status = DDMGNN_E_NONFINITE;
             st->done = 1;
             return;
         }
-        st->rel = sqrt(rr) / st->r0n;
+        const double rel = sqrt(rr[0]) / old.r0n;
+        st->rel = rel;
         if (ia.mode == DDMGNN_CG) {  // M = I: rho = <r, r>, beta = rho_new / rho_old
-            st->beta[0] = rr / st->rho;
-            st->rho = rr;
+            st->beta = rr[0] / old.rho;
+            st->rho = rr[0];
         }
-        if (st->rel <= st->rtol || st->it >= st->max_it) st->done = 1;
-    } else if (stage == FIN_INIT) {
+        if (rel <= old.rtol || old.it + 1 >= old.max_it) st->done = 1;
+    } else if constexpr (STAGE == FIN_INIT) {
         double tot[1];
         sum_partials<1>(P.partials, P.nblk, tot);
         if (!t0) return;
         st->r0n = sqrt(tot[0]);
         st->rtol = P.rtol;
         st->rel = tot[0] == 0.0 ? 0.0 : 1.0;
-        st->alpha = 0.0;
-        for (int i = 0; i < MAX_M; ++i) st->beta[i] = 0.0;
+        st->beta = 0.0;
         for (int i = 0; i <= MAX_M; ++i) st->pq[i] = 1.0;
         st->rho = tot[0];
         st->rr_true = 0.0;
@@ -1244,68 +1284,89 @@ __global__ __launch_bounds__(VEC_BLOCK) void finalize_kernel(const DevProb* __re
         st->gm_conv = 0;
         st->status = isfinite(tot[0]) ? 0 : DDMGNN_E_NONFINITE;
         st->done = (tot[0] == 0.0 || !isfinite(tot[0]) || P.max_it <= 0) ? 1 : 0;
-    } else if (stage == FIN_GM_DOT1 || stage == FIN_GM_DOT2) {
-        // h_k of the Gram pass into tmp; the second pass adds to column j of H
+    } else if constexpr (STAGE == FIN_GM_ROT) {
+        // The rotations and the back substitution are serial chains of one thread: their
+        // operands come to LDS first (100k nodes, the step that ends a cycle of 30: 52 us from
+        // global memory, 20 from LDS; the mean step 6.6 and 4.8).
+        __shared__ double hj[MAX_RESTART + 1], cs[MAX_RESTART], sn[MAX_RESTART], gg[MAX_RESTART + 1], Hs[MAX_RESTART * MAX_RESTART];
+        __shared__ int over;
+        const KState old = *st;
         const GmSmall m = gm_small(P, ia.m);
-        const int j = st->gm_j;
-        gm_sum_dots(P, j, m.tmp);
-        __syncthreads();
-        for (int k = threadIdx.x; k <= j; k += VEC_BLOCK) {
-            double* hk = m.H + (size_t)j * m.ld + k;
-            *hk = stage == FIN_GM_DOT1 ? m.tmp[k] : *hk + m.tmp[k];
+        const int j = old.gm_j, R = ia.m, tid = threadIdx.x;
+        double* Hj = m.H + (size_t)j * m.ld;
+        if (tid <= j) {
+            hj[tid] = Hj[tid];
+            cs[tid] = tid < j ? m.cs[tid] : 0.0;
+            sn[tid] = tid < j ? m.sn[tid] : 0.0;
+            gg[tid] = tid == 0 && j == 0 ? old.gm_beta : m.g[tid];
         }
-    } else if (stage == FIN_GM_ROT) {
         double tot[1];
         sum_partials<1>(P.gm_part, P.nblk, tot);
-        if (!t0) return;
-        const GmSmall m = gm_small(P, ia.m);
-        const int j = st->gm_j, R = ia.m;
-        double* Hj = m.H + (size_t)j * m.ld;
-        const double hn = sqrt(tot[0]);
-        if (j == 0) m.g[0] = st->gm_beta;
-        // earlier rotations on column j, then the one that zeroes h_{j+1,j}
-        for (int i = 0; i < j; ++i) {
-            const double t = m.cs[i] * Hj[i] + m.sn[i] * Hj[i + 1];
-            Hj[i + 1] = -m.sn[i] * Hj[i] + m.cs[i] * Hj[i + 1];
-            Hj[i] = t;
-        }
-        const double dd = hypot(Hj[j], hn);
-        m.cs[j] = Hj[j] / dd;
-        m.sn[j] = hn / dd;
-        Hj[j] = dd;
-        Hj[j + 1] = 0.0;
-        m.g[j + 1] = -m.sn[j] * m.g[j];
-        m.g[j] = m.cs[j] * m.g[j];
-        st->it += 1;
-        const double rel = fabs(m.g[j + 1]) / st->r0n;
-        if (!isfinite(rel) || !isfinite(dd)) {
-            st->status = DDMGNN_E_NONFINITE;
-            st->done = 1;
-            return;
-        }
-        if (!(dd > 0.0)) {  // H_j singular: no update possible
-            st->status = DDMGNN_E_BREAKDOWN;
-            st->done = 1;
-            return;
-        }
-        st->rel = rel;
-        st->gm_conv = rel <= st->rtol || hn == 0.0;
-        if (st->gm_conv || j + 1 == R || st->it >= st->max_it) {
-            // y = H_k^{-1} g (upper triangular), k = j + 1
-            const int k = j + 1;
-            for (int i = k - 1; i >= 0; --i) {
-                double acc = m.g[i];
-                for (int c = i + 1; c < k; ++c) acc -= m.H[(size_t)c * m.ld + i] * m.y[c];
-                m.y[i] = acc / m.H[(size_t)i * m.ld + i];
+        if (old.done) return;
+        if (t0) {
+            over = 0;
+            const double hn = sqrt(tot[0]);
+            // earlier rotations on column j, then the one that zeroes h_{j+1,j}
+            double hi = hj[0];
+            for (int i = 0; i < j; ++i) {
+                const double hk = hj[i + 1];
+                const double t = cs[i] * hi + sn[i] * hk;
+                const double next = -sn[i] * hi + cs[i] * hk;
+                hj[i] = t;
+                hi = next;
             }
-            st->gm_k = k;
-            st->gm_end = 1;
-        } else {
-            st->gm_j = j + 1;
-            st->gm_hnext = hn;
+            const double dd = hypot(hi, hn);
+            const double c = hi / dd, s = hn / dd, gj = gg[j];
+            m.cs[j] = c;
+            m.sn[j] = s;
+            hj[j] = dd;
+            hj[j + 1] = 0.0;
+            const double gn = -s * gj;
+            m.g[j + 1] = gn;
+            gg[j] = c * gj;
+            m.g[j] = gg[j];
+            st->it = old.it + 1;
+            const double rel = fabs(gn) / old.r0n;
+            if (!isfinite(rel) || !isfinite(dd)) {
+                st->status = DDMGNN_E_NONFINITE;
+                st->done = 1;
+            } else if (!(dd > 0.0)) {  // H_j singular: no update possible
+                st->status = DDMGNN_E_BREAKDOWN;
+                st->done = 1;
+            } else {
+                st->rel = rel;
+                const bool conv = rel <= old.rtol || hn == 0.0;
+                st->gm_conv = conv;
+                if (conv || j + 1 == R || old.it + 1 >= old.max_it) {
+                    over = 1;
+                    st->gm_k = j + 1;
+                    st->gm_end = 1;
+                } else {
+                    st->gm_j = j + 1;
+                    st->gm_hnext = hn;
+                }
+            }
         }
-    } else if (stage == FIN_GM_RESTART) {
-        if (!st->gm_end) return;
+        __syncthreads();
+        if (tid <= j + 1) Hj[tid] = hj[tid];
+        if (!over) return;
+        // y = H_k^{-1} g (upper triangular), k = j + 1
+        const int k = j + 1;
+        for (int e = tid; e < k * k; e += VEC_BLOCK) {
+            const int c = e / k, i = e % k;
+            Hs[c * MAX_RESTART + i] = c == j ? hj[i] : m.H[(size_t)c * m.ld + i];
+        }
+        __syncthreads();
+        if (!t0) return;
+        double* y = cs;  // no longer needed
+        for (int i = k - 1; i >= 0; --i) {
+            double acc = gg[i];
+            for (int c = i + 1; c < k; ++c) acc -= Hs[c * MAX_RESTART + i] * y[c];
+            y[i] = acc / Hs[i * MAX_RESTART + i];
+            m.y[i] = y[i];
+        }
+    } else if constexpr (STAGE == FIN_GM_RESTART) {
+        if (st->done || !st->gm_end) return;
         double tot[1];
         sum_partials<1>(P.partials, P.nblk, tot);
         if (!t0) return;
@@ -1318,7 +1379,8 @@ __global__ __launch_bounds__(VEC_BLOCK) void finalize_kernel(const DevProb* __re
         } else if (st->gm_conv || st->it >= st->max_it || tot[0] == 0.0) {
             st->done = 1;
         }
-    } else {  // FIN_RESID
+    } else {
+        static_assert(STAGE == FIN_RESID, "stages");
         double tot[1];
         sum_partials<1>(P.partials, P.nblk, tot);
         if (t0) st->rr_true = tot[0];
@@ -1496,12 +1558,9 @@ hipError_t launch_coarse(const DevProb* tab, const int2* rows, int n_rows, hipSt
     return done(check);
 }
 
-hipError_t launch_prolong(const DevProb* tab, const int2* blk, int n_blk, int n_prob, const IterArgs& it,
-                          hipStream_t s, bool check) {
+hipError_t launch_prolong(const DevProb* tab, const int2* blk, int n_blk, const IterArgs& it, hipStream_t s,
+                          bool check) {
     hipLaunchKernelGGL(prolong_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    if (it.mode >= 0 && it.mode != DDMGNN_FGMRES)
-        hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, (const int*)nullptr,
-                           (int)FIN_PROLONG, it);
     return done(check);
 }
 
@@ -1514,9 +1573,8 @@ hipError_t launch_krylov(const DevProb* tab, const int2* blk, int n_blk, int n_p
         hipLaunchKernelGGL(pupdate_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
         hipLaunchKernelGGL(spmv_dots_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
     }
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_SPMV, it);
     hipLaunchKernelGGL(update_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_UPDATE, it);
+    hipLaunchKernelGGL(finalize_kernel<FIN_UPDATE>, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, it);
     return done(check);
 }
 
@@ -1531,26 +1589,26 @@ hipError_t launch_fgmres_step(const DevProb* tab, const int2* blk, int n_blk, in
     const int* all = nullptr;
     hipLaunchKernelGGL(fgm_spmv_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
     hipLaunchKernelGGL(fgm_gram_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_GM_DOT1, it);
+    hipLaunchKernelGGL(fgm_dots_kernel<false>, dim3(n_prob), dim3(DOTS_BLOCK), 0, s, tab, it);
     hipLaunchKernelGGL(fgm_orth_kernel<false>, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_GM_DOT2, it);
+    hipLaunchKernelGGL(fgm_dots_kernel<true>, dim3(n_prob), dim3(DOTS_BLOCK), 0, s, tab, it);
     hipLaunchKernelGGL(fgm_orth_kernel<true>, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_GM_ROT, it);
+    hipLaunchKernelGGL(finalize_kernel<FIN_GM_ROT>, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, it);
     hipLaunchKernelGGL(fgm_xupd_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
     hipLaunchKernelGGL(fgm_resid_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk, it);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, (int)FIN_GM_RESTART, it);
+    hipLaunchKernelGGL(finalize_kernel<FIN_GM_RESTART>, dim3(n_prob), dim3(VEC_BLOCK), 0, s, tab, all, it);
     return done(check);
 }
 
 hipError_t launch_init(const DevProb* tab, const int2* blk, int n_blk, const int* list, int n_list, hipStream_t s) {
     hipLaunchKernelGGL(init_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_list), dim3(VEC_BLOCK), 0, s, tab, list, (int)FIN_INIT, IterArgs{});
+    hipLaunchKernelGGL(finalize_kernel<FIN_INIT>, dim3(n_list), dim3(VEC_BLOCK), 0, s, tab, list, IterArgs{});
     return hipGetLastError();
 }
 
 hipError_t launch_resid(const DevProb* tab, const int2* blk, int n_blk, const int* list, int n_list, hipStream_t s) {
     hipLaunchKernelGGL(resid_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk);
-    hipLaunchKernelGGL(finalize_kernel, dim3(n_list), dim3(VEC_BLOCK), 0, s, tab, list, (int)FIN_RESID, IterArgs{});
+    hipLaunchKernelGGL(finalize_kernel<FIN_RESID>, dim3(n_list), dim3(VEC_BLOCK), 0, s, tab, list, IterArgs{});
     return hipGetLastError();
 }
 

@@ -573,7 +573,7 @@ int enqueue_apply(Batch& B, const DevProb* tab, const ddmgnn_solve_opts& o, int 
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
     if (o.coarse) HIP_TRY(launch_coarse(tab, B.coarse_rows.p, B.n_coarse, s, !capturing));
     if (ev) HIP_TRY(hipEventRecord(ev[2], s));
-    HIP_TRY(launch_prolong(tab, B.vec_blk.p, B.n_vec, (int)B.probs.size(), iter_args(o, mode), s, !capturing));
+    HIP_TRY(launch_prolong(tab, B.vec_blk.p, B.n_vec, iter_args(o, mode), s, !capturing));
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     return DDMGNN_OK;
 }
@@ -1063,7 +1063,7 @@ size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64
     b += 8 * (size_t)K * K + 24 * (size_t)K;     // a0inv, s, y0, y
     b += 8 * sk;                                 // local
     b += 8 * n * (3 + 2 * (MAX_M + 1));          // u, r, z, direction ring
-    b += 8 * (MAX_M + 1) * VEC_GRID + 16 + sizeof(KState);
+    b += 8 * N_PART * VEC_GRID + 16 + sizeof(KState);
     return b;
 }
 
@@ -1275,7 +1275,7 @@ int create_problem(ddmgnn_ctx* ctx, const ddmgnn_problem_desc& desc, std::shared
     HIP_TRY(P->r.alloc(n));
     HIP_TRY(P->z.alloc(n));
     HIP_TRY(P->st.alloc(1));
-    HIP_TRY(P->partials.alloc((size_t)(MAX_M + 1) * VEC_GRID));
+    HIP_TRY(P->partials.alloc((size_t)N_PART * VEC_GRID));
     HIP_TRY(hipMemsetAsync(P->st.p, 0, sizeof(KState), s));
     HIP_TRY(hipStreamSynchronize(s));
     P->device_bytes = problem_device_bytes(n, hs.nnz, K, sk, hs.n_edges);
@@ -1775,7 +1775,7 @@ int ddmgnn_time_apply_stages(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_so
                 else if (stage == 1)
                     he = launch_coarse(tab, B.coarse_rows.p, B.n_coarse, ctx->cap, false);
                 else
-                    he = launch_prolong(tab, B.vec_blk.p, B.n_vec, 1, ia, ctx->cap, false);
+                    he = launch_prolong(tab, B.vec_blk.p, B.n_vec, ia, ctx->cap, false);
             }
             ctx->launch = ctx->stream;
             const hipError_t ee = hipStreamEndCapture(ctx->cap, &g);
