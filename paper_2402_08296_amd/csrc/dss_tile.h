@@ -23,10 +23,12 @@ template <typename T>
 struct VtLayout;
 template <>
 struct VtLayout<double> {
-    // receiver part of the first message layers (units 0-3 of every lane, unit 4), Psi's hidden
-    // layer (h and c, deg: 3 steps; message sums: 5), Psi's output layer
-    static constexpr int P16 = 0, P4 = 3, HID = 6, N_HID = 8, OUT = 14;
-    static constexpr int CP = 17, CP4 = 21, CH = 22, CO = 25, WN = 28, N_MAIN = 34;
+    // Psi's hidden layer (h and c, deg: 3 steps; message sums: 5) and output layer, operands of
+    // the 4-row product (16 values each), three per step: 10 places of 64 values;
+    // receiver part of the first message layers (units 0-3 of every lane, unit 4)
+    static constexpr int HID = 0, OUT = 24, N_QUAD = 33;
+    static constexpr int P16 = 10, P4 = 13, CP = 16, CP4 = 20, CH = 21, CO = 24, WN = 27, N_MAIN = 32;
+    static_assert((N_QUAD + 1) / 2 * 32 <= P16 * 64, "the 4-row operands fit before the others");
     // sender part
     static constexpr int Q16 = 0, Q4 = 3, N_Q = 6;
     // decoder

@@ -347,13 +347,22 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 3) void dss_block_kernel(
 
         // Psi.
         A4 hid = {w[L::CH], w[L::CH + 1], w[L::CH + 2], 0};
+        A4 out = {w[L::CO], w[L::CO + 1], w[L::CO + 2], 0};
         if constexpr (sizeof(T) == 8) {
-            const T hx = g >= 2 ? x4 : h[2];
-            hid = M::mm(w[L::HID], h[0], hid);
-            hid = M::mm(w[L::HID + 1], h[1], hid);
-            hid = M::mm(w[L::HID + 2], hx, hid);
+            // ten rows: three products of four rows are 48 cycles, one of sixteen 64, and their
+            // three chains hide each other's latency
+            const QuadBlob w4{sw, lane};
+            const T in[8] = {h[0], h[1], g >= 2 ? x4 : h[2], m[0], m[1], m[2], m[3], m[4]};
 #pragma unroll
-            for (int s = 0; s < 5; ++s) hid = M::mm(w[L::HID + 3 + s], m[s], hid);
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    hid[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(w4[L::HID + 3 * s + q], in[s], hid[q], 0, 0, 0);
+#pragma unroll
+            for (int s = 0; s < 3; ++s)
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    out[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(w4[L::OUT + 3 * s + q], M::relu(hid[s]), out[q], 0, 0, 0);
         } else {
             const T deg = info[2], c = info[3];
             A4 fo = {w[L::CCO] * deg, w[L::CCO + 1] * deg, w[L::CCO + 2] * deg, 0};
@@ -371,10 +380,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 3) void dss_block_kernel(
             for (int s = 0; s < 3; ++s) hid = M::mm(w[L::HID + 3 + s], fo[s], hid);
 #pragma unroll
             for (int s = 0; s < 3; ++s) hid = M::mm(w[L::HID + 6 + s], fi[s], hid);
-        }
-        A4 out = {w[L::CO], w[L::CO + 1], w[L::CO + 2], 0};
 #pragma unroll
-        for (int s = 0; s < 3; ++s) out = M::mm(w[L::OUT + s], M::relu(hid[s]), out);
+            for (int s = 0; s < 3; ++s) out = M::mm(w[L::OUT + s], M::relu(hid[s]), out);
+        }
         // rows past the last component are zero: FP64 keeps its coordinates there
 #pragma unroll
         for (int r = 0; r < 3; ++r) h[r] = fma(a.alpha, out[r], h[r]);
@@ -549,10 +557,19 @@ void build_main(const Wts& w, T* blob) {
     put_c(blob, L::CP4, [&](int g) { return w.phi1b(unit(g, 4)); });
     for (int r = 0; r < 5; ++r) put_c(blob, L::WN + r, [&](int g) { return w.phi1(unit(g, r), 2 * D + 2); });
     auto component = [&](int idx, auto f) {  // weights whose rows are latent components
-        put_a16(blob, idx, [&](int r, int g, int kg) {
+        auto row = [&](int r, int g, int kg) {
             const int u = r < 3 ? comp(g, r) : -1;
             return u < 0 ? 0.0 : f(u, kg);
-        });
+        };
+        if constexpr (sizeof(T) == 8) {  // QuadBlob: the three operands of step idx
+            for (int r = 0; r < 3; ++r)
+                for (int l = 0; l < 16; ++l) {
+                    const int i = 3 * idx + r;
+                    blob[(i / 2 * 16 + l) * 2 + i % 2] = row(r, l % 4, l / 4);
+                }
+        } else {
+            put_a16(blob, idx, row);
+        }
     };
     auto constant = [&](int idx, auto f) {
         for (int r = 0; r < 3; ++r)
@@ -561,7 +578,7 @@ void build_main(const Wts& w, T* blob) {
     constant(L::CH, [&](int u) { return w.psi1b(u); });
     constant(L::CO, [&](int u) { return w.psi2b(u); });
     for (int s = 0; s < 3; ++s)
-        component(L::OUT + s, [&](int o, int kg) { return comp(kg, s) < 0 ? 0.0 : w.psi2(o, comp(kg, s)); });
+        component((sizeof(T) == 8 ? L::OUT / 3 : L::OUT) + s, [&](int o, int kg) { return comp(kg, s) < 0 ? 0.0 : w.psi2(o, comp(kg, s)); });
     // entries of the third h step past the components: c, and (FP64) the in-degree
     auto past = [&](int u, int kg) {
         if (kg == 2) return w.psi1(u, D);

@@ -64,6 +64,15 @@ struct LaneBlob {
     }
 };
 
+// The lane's values of the 4-row operands at the start of a blob (lane l holds row l % 4 and
+// the input of group l / 16, so 16 lanes' values serve all): pairs of operands.
+struct QuadBlob {
+    const double* p;
+    int at;
+    __device__ __forceinline__ QuadBlob(const double* blob, int lane) : p(blob), at(lane % 4 + lane / 16 * 4) {}
+    __device__ __forceinline__ double operator[](int i) const { return p[(i / 2 * 16 + at) * 2 + i % 2]; }
+};
+
 // Sender rows. A row holds 20 values: units 0-3 of the four groups in 16-byte
 // pieces (FP32: one per group; FP64: units 0, 1 of every group, then 2, 3), then
 // unit 4 of the groups. A lane's five values are spread over its node's row and
