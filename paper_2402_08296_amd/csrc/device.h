@@ -257,6 +257,8 @@ hipError_t ov_count(const int32_t* sets, const uint8_t* sz, int64_t n, int32_t n
 hipError_t ov_fill(const int32_t* sets, const uint8_t* sz, int64_t n, const uint8_t* dirichlet, int32_t n_part,
                    const int64_t* sub_ptr, int64_t sk, int32_t* part_cur, int32_t* nodes, double* weights,
                    hipStream_t s);
+// Writes a one-problem table.
+hipError_t launch_set_view(DevProb* at, const DevProb& v, hipStream_t s);
 hipError_t launch_coarse(const DevProb* tab, const int2* rows, int n_rows, hipStream_t s, bool check);
 hipError_t launch_prolong(const DevProb* tab, const int2* blk, int n_blk, const IterArgs& it, hipStream_t s,
                           bool check);

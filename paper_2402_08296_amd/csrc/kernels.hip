@@ -1425,6 +1425,13 @@ __global__ __launch_bounds__(VEC_BLOCK) void gather_states_kernel(const DevProb*
     if (i < n) out[i] = *tab[i].st;
 }
 
+// A one-problem table from the launch's own arguments. (A copy from pageable host memory makes
+// the caller wait for it before the next launch: an apply at 5k nodes 145 us with it, 135
+// without; at 200k nodes with exact local solves 266 and 255.)
+__global__ void set_view_kernel(DevProb v, DevProb* at) {
+    if (threadIdx.x == 0) *at = v;
+}
+
 inline hipError_t done(bool check) { return check ? hipGetLastError() : hipSuccess; }
 
 }  // namespace
@@ -1609,6 +1616,11 @@ hipError_t launch_init(const DevProb* tab, const int2* blk, int n_blk, const int
 hipError_t launch_resid(const DevProb* tab, const int2* blk, int n_blk, const int* list, int n_list, hipStream_t s) {
     hipLaunchKernelGGL(resid_kernel, dim3(n_blk), dim3(VEC_BLOCK), 0, s, tab, blk);
     hipLaunchKernelGGL(finalize_kernel<FIN_RESID>, dim3(n_list), dim3(VEC_BLOCK), 0, s, tab, list, IterArgs{});
+    return hipGetLastError();
+}
+
+hipError_t launch_set_view(DevProb* at, const DevProb& v, hipStream_t s) {
+    hipLaunchKernelGGL(set_view_kernel, dim3(1), dim3(64), 0, s, v, at);
     return hipGetLastError();
 }
 

@@ -259,7 +259,7 @@ int prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
     list_tiles(P);
     const size_t nt = P->vt_tiles.size();
     const DevProb v = make_view(P);
-    HIP_TRY(upload_async(hook.p, &v, sizeof(v), s));
+    HIP_TRY(launch_set_view(hook.p, v, s));
     if (P->vt_pos.p) return DDMGNN_OK;
     HIP_TRY(P->vt_info.upload(P->vt_tiles.data(), nt, s));
     HIP_TRY(P->vt_ptr.upload(P->vt_first.data(), P->vt_first.size(), s));
@@ -1671,7 +1671,7 @@ int ddmgnn_dss_forward(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision, co
     v.c_in = c;
     v.local = out;
     v.st = nullptr;
-    HIP_TRY(upload_async(B.hook.p, &v, sizeof(v), ctx->stream));
+    HIP_TRY(launch_set_view(B.hook.p, v, ctx->stream));
     if (int rc = enqueue_dss(B, B.hook.p, precision, 0, false)) return rc;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return DDMGNN_OK;
@@ -1700,7 +1700,7 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
     v.c_in = P->fwd_in.p;
     v.local = P->fwd_out.p;
     v.st = nullptr;
-    HIP_TRY(upload_async(B.hook.p, &v, sizeof(v), s));
+    HIP_TRY(launch_set_view(B.hook.p, v, s));
     const ModelDev& M = *B.model;
     const int vprec = precision == DDMGNN_BF16 ? DDMGNN_FP32 : precision;
     if (k > kMaxSubNodes) {
@@ -1750,7 +1750,7 @@ int ddmgnn_time_apply_stages(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_so
     v.r = const_cast<double*>(r);  // read only
     v.z = z;
     v.st = nullptr;
-    HIP_TRY(upload_async(B.hook.p, &v, sizeof(v), ctx->stream));
+    HIP_TRY(launch_set_view(B.hook.p, v, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     const IterArgs ia = iter_args(*opts, -1);
     const DevProb* tab = B.hook.p;
@@ -1818,7 +1818,7 @@ int ddmgnn_precond_apply(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_solve_
     v.r = const_cast<double*>(r);  // read only: the apply never writes its input
     v.z = z;
     v.st = nullptr;
-    HIP_TRY(upload_async(B.hook.p, &v, sizeof(v), ctx->stream));
+    HIP_TRY(launch_set_view(B.hook.p, v, ctx->stream));
     if (int rc = enqueue_apply(B, B.hook.p, *opts, -1, nullptr, false)) return rc;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return DDMGNN_OK;
