@@ -201,9 +201,9 @@ typedef struct {
     double coarse_ms;          /* coarse solve (step 1) */
     double prolong_ms;         /* gluing (step 3) with its fused dot products */
     double krylov_ms;          /* direction update, SpMV with dots, solution update */
-    int32_t dss_kernel;        /* kernel that ran the local solves: 0 FP64 VALU DSS, 1 FP32 VALU DSS,
+    int32_t dss_kernel;        /* kernel that ran the local solves: 0 FP64 DSS, 1 FP32 DSS,
                                 * 2 BF16 MFMA DSS for every sub-mesh, 3 exact local solves (DDM-LU),
-                                * 4 BF16 MFMA DSS for some sub-meshes and the FP32 VALU DSS for those
+                                * 4 BF16 MFMA DSS for some sub-meshes and the FP32 DSS for those
                                 * beyond its LDS or 2048-node budget (a BF16 request of a model with
                                 * d = 20 runs 1 throughout; d = 5 runs on matrix cores) */
     int32_t status;            /* this problem's own status (DDMGNN_OK, E_MAXIT, E_BREAKDOWN, ...) */
