@@ -31,6 +31,7 @@ struct VtLayout<double> {
     static_assert((N_QUAD + 1) / 2 * 32 <= P16 * 64, "the 4-row operands fit before the others");
     // sender part
     static constexpr int Q16 = 0, Q4 = 3, N_Q = 6;
+    static constexpr int N_OPS = CP, N_QOPS = N_Q;  // operands; the rest are constants of a group
     // decoder
     static constexpr int DH = 0, DO = 3, CDH = 6, CDO = 9, N_DEC = 10;
 };
@@ -41,13 +42,28 @@ struct VtLayout<float> {
     static constexpr int CP = 24, CP4 = 28, WX = 29, WY = 34, WN = 39, CCO = 44, CCI = 47, CH = 50, CO = 53,
                          N_MAIN = 56;
     static constexpr int Q16 = 0, Q4 = 3, QX = 6, QY = 11, N_Q = 16;
+    static constexpr int N_OPS = CP, N_QOPS = QX;
     static constexpr int DH = 0, DO = 3, CDH = 6, CDO = 9, N_DEC = 12;
 };
 
+// A blob of n values per lane on the device, where it is read from LDS: the first n_ops,
+// operands, are held per lane; the others are constants of a lane's group and follow as
+// four rows (a quarter of the constants' LDS, which limits the wavefronts in flight). Whole KB.
+template <typename T>
+struct VtBlob {
+    static constexpr int PER = 16 / (int)sizeof(T);
+    static constexpr int ops(int n_ops) { return (n_ops + PER - 1) / PER * PER * 64; }
+    // (padded by 16 bytes: the four rows start on different banks)
+    static constexpr int row(int n, int n_ops) { return n > n_ops ? (n - n_ops + 2 * PER - 1) / PER * PER : 0; }
+    static constexpr int size(int n, int n_ops) {
+        return (ops(n_ops) + 4 * row(n, n_ops) + 64 * PER - 1) / (64 * PER) * (64 * PER);
+    }
+};
 // Device weights: kbar main blobs, kbar sender blobs, one decoder blob, back to back.
 template <typename T>
 struct VtBlobs {
-    static constexpr size_t MAIN = (size_t)VtLayout<T>::N_MAIN * 64, Q = (size_t)VtLayout<T>::N_Q * 64,
+    static constexpr size_t MAIN = VtBlob<T>::size(VtLayout<T>::N_MAIN, VtLayout<T>::N_OPS),
+                            Q = VtBlob<T>::size(VtLayout<T>::N_Q, VtLayout<T>::N_QOPS),
                             DEC = (size_t)VtLayout<T>::N_DEC * 64;
     static size_t size(int kbar) { return (size_t)kbar * (MAIN + Q) + DEC; }
 };

@@ -53,7 +53,7 @@ __device__ __forceinline__ void sender_rows(const T* blob, int lane, const T (&h
     const int n = lane & 15, g = lane >> 4;
     typename Mx<T>::A4 acc = {0, 0, 0, 0};
     T q[5];
-    const LaneBlob<T> w{blob, lane};
+    const WeightBlob<T, L::N_Q, L::N_QOPS> w{blob, lane};
     if constexpr (sizeof(T) == 8) {
         T q4 = 0;
 #pragma unroll
@@ -112,15 +112,14 @@ template <typename T>
 __global__ __launch_bounds__(RB) void dss_restrict_kernel(const DevProb* __restrict__ tab,
                                                          const int2* __restrict__ work, const T* __restrict__ qblob,
                                                          int apply) {
-    using L = VtLayout<T>;
     const int2 wi = work[blockIdx.x];
     const DevProb& P = tab[wi.x];
     if (P.st && P.st->done) return;
     __shared__ double cj[kMaxSubNodes];
     __shared__ double red[RB / 64];
-    __shared__ __align__(16) T sw[L::N_Q * 64];
+    __shared__ __align__(16) T sw[VtBlobs<T>::Q];
     __shared__ __align__(16) T buf[RB / 64][VT_TILE * ROW];
-    stage<T, L::N_Q, RB>(qblob, sw);
+    stage<T, VtBlobs<T>::Q / 64, RB>(qblob, sw);
     const int sub = wi.y, tid = threadIdx.x;
     const int base = P.sub_ptr[sub], k = P.sub_ptr[sub + 1] - base;
     if (apply) {
@@ -193,15 +192,20 @@ struct VtArgs {
 // would halve the wavefronts in flight). The tiles are dealt to the eight dies in
 // contiguous slabs, so that a sub-mesh's sender rows are gathered through one
 // die's L2.
-template <typename T, bool LAST, int BLOCK>
-__global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 3) void dss_block_kernel(VtArgs<T> a) {
+// Workgroups of a wavefront per SIMD, so that they spread evenly, as many as the LDS holds
+// (FP64: 40,960 bytes each; the last block's, with the decoder's weights, three). 100k nodes in 150
+// parts, one forward: FP32 419 us, FP64 563; two of eight wavefronts 439 and 584. More than 16
+// wavefronts per compute unit are slower (FP32, 22: 467).
+constexpr int BLOCK = 256, WG_PER_CU = 4;
+template <typename T, bool LAST>
+__global__ __launch_bounds__(BLOCK, LAST && sizeof(T) == 8 ? WG_PER_CU - 1 : WG_PER_CU) void dss_block_kernel(VtArgs<T> a) {
     using L = VtLayout<T>;
     using M = Mx<T>;
     using A4 = typename M::A4;
     using R = Rows20<T>;
-    constexpr int N_NEXT = LAST ? L::N_DEC : L::N_Q;
-    __shared__ __align__(16) T sw[L::N_MAIN * 64];
-    __shared__ __align__(16) T swn[N_NEXT * 64];
+    constexpr size_t MAIN = VtBlobs<T>::MAIN, NEXT = LAST ? VtBlobs<T>::DEC : VtBlobs<T>::Q;
+    __shared__ __align__(16) T sw[MAIN];
+    __shared__ __align__(16) T swn[NEXT];
     __shared__ __align__(16) T buf[BLOCK / 64][R::BUF];
     __shared__ __align__(16) VtRec<T> recs[BLOCK / 64][R::RECS];
     const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
@@ -215,8 +219,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 3) void dss_block_kernel(
         return st && uload(&st->done);
     };
     if (a.solo && done(a.tab)) return;
-    stage<T, L::N_MAIN, BLOCK>(a.main, sw);
-    stage<T, N_NEXT, BLOCK>(a.next, swn);
+    stage<T, MAIN / 64, BLOCK>(a.main, sw);
+    stage<T, NEXT / 64, BLOCK>(a.next, swn);
     // Pieces this lane gathers of a chunk's rows: the (edge row, node) and the byte offset in the row.
     int gat[R::LOADS], off[R::LOADS];
 #pragma unroll
@@ -253,7 +257,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 512 ? 4 : 3) void dss_block_kernel(
     fetch();
     vmem_done();
     __syncthreads();
-    const LaneBlob<T> w{sw, lane}, wn{swn, lane};
+    const WeightBlob<T, L::N_MAIN, L::N_OPS> w{sw, lane};
+    const LaneBlob<T> wn{swn, lane};  // the decoder's
     while (it < end) {
         asm volatile("" ::: "memory");  // keeps the weights in LDS: hoisted, they would fill the registers
         const DevProb* PA = P;
@@ -651,14 +656,29 @@ void build_dec(const Wts& w, T* blob) {
     put_c(blob, L::CDO, [&](int g) { return g == 0 ? w.dec2b() : 0.0; });
 }
 
+// A blob of N values per lane in the form of the device (VtBlob).
+template <typename T, int N, int N_OPS>
+void compact(const std::vector<T>& full, T* out) {
+    constexpr int OPS = VtBlob<T>::ops(N_OPS), PER = VtBlob<T>::PER;
+    std::copy(full.begin(), full.begin() + OPS, out);
+    for (int i = N_OPS; i < N; ++i)
+        for (int g = 0; g < 4; ++g)
+            out[OPS + g * VtBlob<T>::row(N, N_OPS) + (i - N_OPS)] =
+                full[((size_t)(i / PER) * 64 + 16 * g) * PER + i % PER];
+}
+
 template <typename T>
 void build_all(const float* theta, int kbar, std::vector<T>& out) {
     using B = VtBlobs<T>;
+    using L = VtLayout<T>;
     out.assign(B::size(kbar), (T)0);
     for (int k = 0; k < kbar; ++k) {
         const Wts w{theta + (size_t)k * BLOCK_W};
-        build_main<T>(w, out.data() + (size_t)k * B::MAIN);
-        build_sender<T>(w, out.data() + (size_t)kbar * B::MAIN + (size_t)k * B::Q);
+        std::vector<T> main(L::N_MAIN * 64, (T)0), sender(L::N_Q * 64, (T)0);
+        build_main<T>(w, main.data());
+        build_sender<T>(w, sender.data());
+        compact<T, L::N_MAIN, L::N_OPS>(main, out.data() + (size_t)k * B::MAIN);
+        compact<T, L::N_Q, L::N_QOPS>(sender, out.data() + (size_t)kbar * B::MAIN + (size_t)k * B::Q);
     }
     build_dec<T>(Wts{theta + (size_t)(kbar - 1) * BLOCK_W}, out.data() + (size_t)kbar * (B::MAIN + B::Q));
 }
@@ -667,11 +687,11 @@ void build_all(const float* theta, int kbar, std::vector<T>& out) {
 
 void build_vt_maps(const float* one_block, std::vector<float>& main, std::vector<float>& sender,
                    std::vector<float>& dec) {
-    using B = VtBlobs<float>;
+    using L = VtLayout<float>;
     const Wts w{one_block};
-    main.assign(B::MAIN, 0.0f);
-    sender.assign(B::Q, 0.0f);
-    dec.assign(B::DEC, 0.0f);
+    main.assign(L::N_MAIN * 64, 0.0f);
+    sender.assign(L::N_Q * 64, 0.0f);
+    dec.assign(L::N_DEC * 64, 0.0f);
     build_main<float>(w, main.data());
     build_sender<float>(w, sender.data());
     build_dec<float>(w, dec.data());
@@ -706,13 +726,13 @@ hipError_t launch_vt_fill(double* p, int64_t n, double v, hipStream_t s) { retur
 hipError_t launch_vt_fill(float* p, int64_t n, float v, hipStream_t s) { return fill<float>(p, n, v, s); }
 
 namespace {
-template <typename T, int BLOCK>
+template <typename T>
 void blocks(const DevProb* tab, const int4* tiles, int n_tiles, bool solo, int kbar, double alpha, int apply,
             const T* blobs, hipStream_t s) {
     using B = VtBlobs<T>;
     const T* q = blobs + (size_t)kbar * B::MAIN;
     const T* dec = blobs + (size_t)kbar * (B::MAIN + B::Q);
-    constexpr int W = BLOCK / 64, WG_MAX = N_CU * 2;
+    constexpr int W = BLOCK / 64, WG_MAX = N_CU * WG_PER_CU;
     int grid = (n_tiles + W - 1) / W;
     grid = grid > WG_MAX ? WG_MAX : grid;
     grid = (grid + N_XCD - 1) / N_XCD * N_XCD;
@@ -720,10 +740,10 @@ void blocks(const DevProb* tab, const int4* tiles, int n_tiles, bool solo, int k
         VtArgs<T> a{tab, tiles, n_tiles, solo ? 1 : 0, apply, k & 1, (T)alpha, blobs + (size_t)k * B::MAIN, nullptr};
         if (k + 1 < kbar) {
             a.next = q + (size_t)(k + 1) * B::Q;
-            hipLaunchKernelGGL((dss_block_kernel<T, false, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+            hipLaunchKernelGGL((dss_block_kernel<T, false>), dim3(grid), dim3(BLOCK), 0, s, a);
         } else {
             a.next = dec;
-            hipLaunchKernelGGL((dss_block_kernel<T, true, BLOCK>), dim3(grid), dim3(BLOCK), 0, s, a);
+            hipLaunchKernelGGL((dss_block_kernel<T, true>), dim3(grid), dim3(BLOCK), 0, s, a);
         }
     }
 }
@@ -736,13 +756,7 @@ hipError_t launch_dss_tiles(const DevProb* tab, const int2* subs, int n_subs, co
     using B = VtBlobs<T>;
     const T* q = blobs + (size_t)kbar * B::MAIN;
     hipLaunchKernelGGL(dss_restrict_kernel<T>, dim3(n_subs), dim3(RB), 0, s, tab, subs, q, apply);
-    // Up to two tiles per SIMD: workgroups of four wavefronts, so that they spread over
-    // more compute units. More: of eight, which share one copy of the weights, two per
-    // compute unit (LDS), each wavefront several tiles.
-    if (n_tiles <= N_CU * 8)
-        blocks<T, 256>(tab, tiles, n_tiles, solo, kbar, alpha, apply, blobs, s);
-    else
-        blocks<T, 512>(tab, tiles, n_tiles, solo, kbar, alpha, apply, blobs, s);
+    blocks<T>(tab, tiles, n_tiles, solo, kbar, alpha, apply, blobs, s);
     return check ? hipGetLastError() : hipSuccess;
 }
 template hipError_t launch_dss_tiles<double>(const DevProb*, const int2*, int, const int4*, int, bool, int, double,

@@ -64,6 +64,17 @@ struct LaneBlob {
     }
 };
 
+// The same of a VtBlob in LDS.
+template <typename T, int N, int N_OPS>
+struct WeightBlob {
+    const T* p;
+    int lane;
+    __device__ __forceinline__ T operator[](int i) const {
+        if (i < N_OPS) return LaneBlob<T>{p, lane}[i];
+        return p[VtBlob<T>::ops(N_OPS) + (lane >> 4) * VtBlob<T>::row(N, N_OPS) + (i - N_OPS)];
+    }
+};
+
 // The lane's values of the 4-row operands at the start of a blob (lane l holds row l % 4 and
 // the input of group l / 16, so 16 lanes' values serve all): pairs of operands.
 struct QuadBlob {
@@ -163,7 +174,7 @@ __device__ __forceinline__ void to_lds(const char* from, char* to) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
                                      (__attribute__((address_space(3))) void*)to, 16, 0, 0);
 }
-// Copies a blob of N values per lane to LDS, a chunk of 1 KB per wavefront at a time.
+// Copies N values per lane to LDS, a chunk of 1 KB per wavefront at a time.
 template <typename T, int N, int BLOCK>
 __device__ __forceinline__ void stage(const T* __restrict__ from, T* to) {
     constexpr int CH = N / Mx<T>::PER;
