@@ -7,8 +7,8 @@
 // over all compute units whatever the sub-meshes' sizes; the price is a launch
 // per block (1.7 us inside a captured graph) and the latent state and sender rows
 // in device memory. One forward of 30 blocks, one workgroup per sub-mesh before
-// and tiles now: 5k nodes in 8 parts, FP64 829 -> 168 us, FP32 421 -> 139; 100k
-// in 150, FP64 2,060 -> 601, FP32 580 -> 431; 1M in 1500, FP64 11.2 -> 6.2 ms.
+// and tiles now: 5k nodes in 8 parts, FP64 829 -> 168 us, FP32 421 -> 137; 100k
+// in 150, FP64 2,060 -> 563, FP32 580 -> 419; 1M in 1500, FP64 11.2 -> 6.2 ms.
 //
 // A wavefront takes a tile: lane l serves node l % 16 and group l / 16. The
 // twenty hidden units of the two message layers are spread over the groups,
@@ -192,6 +192,7 @@ struct VtArgs {
 // would halve the wavefronts in flight). The tiles are dealt to the eight dies in
 // contiguous slabs, so that a sub-mesh's sender rows are gathered through one
 // die's L2.
+//
 // Workgroups of a wavefront per SIMD, so that they spread evenly, as many as the LDS holds
 // (FP64: 40,960 bytes each; the last block's, with the decoder's weights, three). 100k nodes in 150
 // parts, one forward: FP32 419 us, FP64 563; two of eight wavefronts 439 and 584. More than 16
