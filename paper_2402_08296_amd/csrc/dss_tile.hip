@@ -371,14 +371,19 @@ __global__ __launch_bounds__(BLOCK, LAST && sizeof(T) == 8 ? WG_PER_CU - 1 : WG_
                     out[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(w4[L::OUT + 3 * s + q], M::relu(hid[s]), out[q], 0, 0, 0);
         } else {
             const T deg = info[2], c = info[3];
+            // An operand's entries against zero weights are zeroed: an overflowed one would be
+            // a NaN in the product, and relu drops NaN.
+            const T m4o = g < 2 ? m[4] : (T)0, m4i = g < 2 ? (T)0 : m[4];
             A4 fo = {w[L::CCO] * deg, w[L::CCO + 1] * deg, w[L::CCO + 2] * deg, 0};
             A4 fi = {w[L::CCI] * deg, w[L::CCI + 1] * deg, w[L::CCI + 2] * deg, 0};
             fo = M::mm(w[L::FO], m[0], fo);
             fi = M::mm(w[L::FI], m[2], fi);
             fo = M::mm(w[L::FO + 1], m[1], fo);
             fi = M::mm(w[L::FI + 1], m[3], fi);
-            fo = M::mm(w[L::FO + 2], m[4], fo);
-            fi = M::mm(w[L::FI + 2], m[4], fi);
+            fo = M::mm(w[L::FO + 2], m4o, fo);
+            fi = M::mm(w[L::FI + 2], m4i, fi);
+            fo[2] = g < 2 ? fo[2] : (T)0;
+            fi[2] = g < 2 ? fi[2] : (T)0;
             hid = M::mm(w[L::HID], h[0], hid);
             hid = M::mm(w[L::HID + 1], h[1], hid);
             hid = M::mm(w[L::HID + 2], g == 2 ? c : h[2], hid);
@@ -389,9 +394,13 @@ __global__ __launch_bounds__(BLOCK, LAST && sizeof(T) == 8 ? WG_PER_CU - 1 : WG_
 #pragma unroll
             for (int s = 0; s < 3; ++s) out = M::mm(w[L::OUT + s], M::relu(hid[s]), out);
         }
-        // rows past the last component are zero: FP64 keeps its coordinates there
+        // entries past the last component stay: FP64 keeps its coordinates there, FP32 zeros
+        // (their rows of the products are zero weights times values that may have overflowed)
 #pragma unroll
-        for (int r = 0; r < 3; ++r) h[r] = fma(a.alpha, out[r], h[r]);
+        for (int r = 0; r < 3; ++r) {
+            const T v = fma(a.alpha, out[r], h[r]);
+            if (r < 2 || g < 2) h[r] = v;
+        }
 
         if constexpr (!LAST) {
             store_h<T>(hout, t, lane, h, x4);

@@ -160,11 +160,15 @@ __device__ __forceinline__ void psi_hidden(const W& w, const float (&h)[3], cons
     fo = f4{w[L::CCO] * deg, w[L::CCO + 1] * deg, w[L::CCO + 2] * deg, 0};
     fi = f4{w[L::CCI] * deg, w[L::CCI + 1] * deg, w[L::CCI + 2] * deg, 0};
     z = f4{w[L::CH], w[L::CH + 1], w[L::CH + 2], 0};
+    // (entries against zero weights are zeroed, as in dss_block_kernel)
+    const float m4o = g < 2 ? m[4] : 0.0f, m4i = g < 2 ? 0.0f : m[4];
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
-        fo = Mx<float>::mm(w[L::FO + s], m[s < 2 ? s : 4], fo);
-        fi = Mx<float>::mm(w[L::FI + s], m[s < 2 ? 2 + s : 4], fi);
+        fo = Mx<float>::mm(w[L::FO + s], s < 2 ? m[s] : m4o, fo);
+        fi = Mx<float>::mm(w[L::FI + s], s < 2 ? m[2 + s] : m4i, fi);
     }
+    fo[2] = g < 2 ? fo[2] : 0.0f;
+    fi[2] = g < 2 ? fi[2] : 0.0f;
     z = Mx<float>::mm(w[L::HID], h[0], z);
     z = Mx<float>::mm(w[L::HID + 1], h[1], z);
     z = Mx<float>::mm(w[L::HID + 2], g == 2 ? c : h[2], z);
@@ -292,7 +296,10 @@ __global__ __launch_bounds__(EB, 4) void train_forward_kernel(TrainArgs a, int b
 #pragma unroll
         for (int s = 0; s < 3; ++s) out = Mx<float>::mm(w[L::OUT + s], fmaxf(z[s], 0.0f), out);
 #pragma unroll
-        for (int r = 0; r < 3; ++r) h[r] = fmaf(a.alpha, out[r], h[r]);
+        for (int r = 0; r < 3; ++r) {
+            const float v = fmaf(a.alpha, out[r], h[r]);
+            if (r < 2 || g < 2) h[r] = v;
+        }
         store_h<float>(a.h + (size_t)(b + 1) * a.n_tiles * 256, t, lane, h, 0.0f);
         float* M = a.m + m_at(a, b);
         reinterpret_cast<f4*>(M)[t * 64 + lane] = f4{m[0], m[1], m[2], m[3]};

@@ -107,3 +107,23 @@ def test_zero_residual_and_repeat(ctx):
         s, _, _, loc = prob.intermediates()
         assert torch.equal(z[0], z[1]) and s[1] == 0.0 and torch.isfinite(z[0]).all()
         assert not loc[hp.sub_ptr[1]:hp.sub_ptr[2]].any() and loc.any()
+
+
+def test_overflow_is_not_masked(ctx):
+    """With positive weights every layer adds values of one sign, so once the state overflows
+    every later value is +inf, whatever the order of the sums: the forward must say so (a relu
+    drops NaN, so one 0 * inf against an operand's padding turns the output finite again), and
+    a solve must end with the non-finite status."""
+    p = W.make_problem(206, 2500, 4, 0.2)
+    hp = oracle_problem(p)
+    rng = np.random.default_rng(5)
+    theta = (1e10 * rng.uniform(0.5, 1.0, W.xavier_theta(W.THETA_SEED).size)).astype(np.float32)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, theta))
+    c = torch.tensor(rng.uniform(0.01, 1.0, hp.sub_nodes.size), device="cuda")
+    u = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    for prec in ("fp64", "fp32"):
+        out = torch.empty_like(c)
+        prob.dss_forward(c, out, prec)
+        print(f"[gpu] overflow {prec}: {int(torch.isposinf(out).sum())} of {out.numel()} infinite", flush=True)
+        assert torch.isposinf(out).all()
+        assert prob.solve(u, dg.default_opts(precision=prec, max_it=5), check=False).status == -7
