@@ -41,11 +41,19 @@ struct DevBuf {
         p = nullptr;
         n = 0;
     }
+    // After a failure the buffer is empty (callers grow a buffer when n is too small), and
+    // the error is not left for the next launch's check.
     hipError_t alloc(size_t count) {
         reset();
-        n = count;
         if (count == 0) return hipSuccess;
-        return hipMalloc(&p, count * sizeof(T));
+        const hipError_t e = hipMalloc(&p, count * sizeof(T));
+        if (e == hipSuccess) {
+            n = count;
+        } else {
+            p = nullptr;
+            (void)hipGetLastError();
+        }
+        return e;
     }
     // Synchronous upload on stream s (the source may be pageable).
     hipError_t upload(const T* src, size_t count, hipStream_t s) {
