@@ -118,10 +118,9 @@ struct DevProb {
     const int32_t* node_slots;
     const int32_t* slot_sub;
     const double* a0inv;        // K x K
-    const double* lu_inv;       // local exact solves: the tiles of -(R_i A R_i^T)^{-1} per sub-mesh
-    const int64_t* lu_off;      // [K + 1] offsets into lu_inv (null until built)
-    double* lu_part;            // per sub-mesh and unit of its tiles, partial products (lu_units(k) x k)
-    const int64_t* lu_poff;     // [K + 1] offsets into lu_part
+    double* lu_inv;             // local exact solves: per sub-mesh (R_i A R_i^T)^{-1} (lu_dense), or the
+                                // tiles of its negative and their units' partial products
+    const int64_t* lu_off;      // [2 K] offsets of both in lu_inv (null until built)
     // iteration vectors
     double* u;
     double* r;                  // residual; input of the apply
@@ -183,13 +182,22 @@ hipError_t launch_dss_big(const DevProb* tab, const int2* work, int n_work, int 
                           double alpha, int apply, const float* theta32, const double* theta64, hipStream_t s,
                           bool check);
 // Exact local solves (DDM-LU): restriction as in the DSS kernels, then
-// local = (R_i A R_i^T)^{-1} R_i r per sub-mesh. A sub-mesh of nt rows of tiles is
-// shared by lu_units workgroups (unit u: rows u and nt - 1 - u, nt + 1 tiles), whose
-// partial products a second kernel adds. units: (problem, sub-mesh, unit); those of
-// sub-meshes of at most LU_LDS_K nodes, and the larger ones (big); max_k: largest
-// sub-mesh of each list (dynamic LDS). subs: (problem, sub-mesh).
+// local = (R_i A R_i^T)^{-1} R_i r per sub-mesh. A small one (lu_dense) is one workgroup's
+// (unit -1) and held as a square of row stride lu_ld(k). A larger one, of nt
+// rows of tiles, is shared by lu_units workgroups (unit u: rows u and nt - 1 - u, nt + 1
+// tiles), whose partial products a second kernel adds. units: (problem, sub-mesh, unit);
+// those of sub-meshes of at most LU_LDS_K nodes, and the larger ones (big); max_k: largest
+// sub-mesh of each list (dynamic LDS). subs: (problem, sub-mesh) of those in tiles.
 // prepare_lu_local raises the kernels' LDS limits (not allowed during capture).
-constexpr int LU_LDS_K = 2048;
+constexpr int LU_LDS_K = 2048, LU_DENSE_K = 256, LU_DENSE_MIXED = 202;
+// Whether the inverse of a sub-mesh of k nodes is held as a square; max_k: the problem's
+// largest. Up to LU_DENSE_MIXED nodes tiles may hold more bytes than the square (k <= 63,
+// 65-110, 129-156, 193-202: at 16 nodes 16 times, at 65 three times), and never beyond.
+// Where every sub-mesh of a problem is a square the second kernel is not needed either,
+// which pays to LU_DENSE_K. Per launch, squares against tiles: 40 sub-meshes of up to 64
+// nodes 5.3 and 7.5 us, of up to 248 8.3 and 9.8, of up to 326 11.6 and 10.9; 1200 of up to
+// 58 8.2 and 16.9, up to 202 26.4 and 30.0, of 40 to 540 (both forms) 143 and 141.
+inline bool lu_dense(int k, int max_k) { return k <= (max_k <= LU_DENSE_K ? LU_DENSE_K : LU_DENSE_MIXED); }
 __host__ __device__ inline int lu_units(int k) { return ((k + 63) / 64 + 1) / 2; }
 struct LuWork {
     const int4* units;
@@ -203,7 +211,10 @@ hipError_t prepare_lu_local();
 hipError_t launch_lu_local(const DevProb* tab, const LuWork& w, hipStream_t s, bool check);
 // Device factorisation (factor.hip) of symmetric matrices held as the SYM_TILE x
 // SYM_TILE tiles of their lower triangle. launch_lu_assemble: the tiles (zeroed
-// before) of A_i = R_i A R_i^T, sub-mesh i's at off[i] of inv. launch_coarse_assemble:
+// before) of A_i = R_i A R_i^T, those of sub-mesh subs[m] at base + off[m].
+// launch_lu_small: (R_i A R_i^T)^{-1} of sub-meshes of at most SYM_TILE nodes as squares
+// at out + lu_off[i]; launch_lu_pack: squares from the inverted tiles of larger ones.
+// launch_coarse_assemble:
 // A_0 = R_0 A R_0^T (K x K, deterministic summation order), symmetrised, its diagonal
 // copied to diag0. launch_gj_invert: in-place -A^{-1} of a batch of SPD matrices (matrix
 // m's tiles at base + off[m], orders and prefixes of plan.meta in meta) over the
@@ -215,7 +226,7 @@ constexpr int SYM_TILE = 64;
 __host__ __device__ inline int64_t sym_tile(int I, int J) {  // offset of tile (I, J), J <= I
     return ((int64_t)I * (I + 1) / 2 + J) * SYM_TILE * SYM_TILE;
 }
-inline int64_t sym_doubles(int64_t k) {
+__host__ __device__ inline int64_t sym_doubles(int64_t k) {
     const int64_t nt = (k + SYM_TILE - 1) / SYM_TILE;
     return nt * (nt + 1) / 2 * SYM_TILE * SYM_TILE;
 }
@@ -226,8 +237,19 @@ struct GjPlan {
     explicit GjPlan(const std::vector<int32_t>& k);
     size_t scratch_doubles() const;
 };
-hipError_t launch_lu_assemble(const int32_t* rowptr, const int32_t* col, const double* val, const int64_t* sub_ptr,
-                              const int32_t* sub_nodes, const int64_t* off, double* inv, int n_sub, hipStream_t s);
+struct LuMatrix {  // a problem's matrix and sub-meshes
+    const int32_t* rowptr;
+    const int32_t* col;
+    const double* val;
+    const int32_t* sub_ptr;
+    const int32_t* sub_nodes;
+};
+hipError_t launch_lu_assemble(const LuMatrix& a, const int32_t* subs, int n, const int64_t* off, double* base,
+                              hipStream_t s);
+hipError_t launch_lu_small(const LuMatrix& a, const int32_t* subs, int n, const int64_t* lu_off, double* out,
+                           int* status, hipStream_t s);
+hipError_t launch_lu_pack(const int32_t* sub_ptr, const int32_t* subs, int n, const int64_t* off, const double* base,
+                          const int64_t* lu_off, double* out, hipStream_t s);
 hipError_t launch_coarse_assemble(const int32_t* rowptr, const int32_t* col, const double* val,
                                   const int32_t* sub_ptr, const int32_t* sub_nodes, const double* weights,
                                   const int32_t* node_ptr, const int32_t* node_slots, const int32_t* slot_sub, int K,

@@ -56,19 +56,18 @@ __device__ inline int find_local(const int32_t* __restrict__ s, int k, int32_t g
     return lo < k && s[lo] == g ? lo : -1;
 }
 
-// A_i = R_i A R_i^T of sub-mesh blockIdx.x into its (zeroed) tiles.
-__global__ __launch_bounds__(GJ_THREADS) void lu_assemble_kernel(const int32_t* __restrict__ rowptr,
-                                                                  const int32_t* __restrict__ col,
-                                                                  const double* __restrict__ val,
-                                                                  const int64_t* __restrict__ sub_ptr,
-                                                                  const int32_t* __restrict__ sub_nodes,
+// A_i = R_i A R_i^T of sub-mesh subs[blockIdx.x] into its (zeroed) tiles.
+__global__ __launch_bounds__(GJ_THREADS) void lu_assemble_kernel(LuMatrix a, const int32_t* __restrict__ subs,
                                                                   const int64_t* __restrict__ off,
                                                                   double* __restrict__ inv) {
-    const int i = blockIdx.x;
-    const int64_t b = sub_ptr[i];
-    const int k = (int)(sub_ptr[i + 1] - b);
-    double* M = inv + off[i];
-    const int32_t* s = sub_nodes + b;
+    const int32_t* __restrict__ rowptr = a.rowptr;
+    const int32_t* __restrict__ col = a.col;
+    const double* __restrict__ val = a.val;
+    const int i = subs[blockIdx.x];
+    const int b = a.sub_ptr[i];
+    const int k = a.sub_ptr[i + 1] - b;
+    double* M = inv + off[blockIdx.x];
+    const int32_t* s = a.sub_nodes + b;
     auto at = [&](int r, int c) { return M + sym_tile(r / GJ_W, c / GJ_W) + (r % GJ_W) * GJ_W + c % GJ_W; };
     for (int j = threadIdx.x; j < (k + GJ_W - 1) / GJ_W * GJ_W; j += GJ_THREADS) {
         if (j >= k) {
@@ -311,13 +310,14 @@ __device__ __forceinline__ void product_rows(const double* L, const double* R, i
     }
 }
 
-// Inverse of the tile in LDS (swizzled) into inv (row-major): Gauss-Jordan with a
-// wavefront per 16 rows in registers (lane = column); the pivot row passes through
+// Inverse of the tile in LDS (swizzled), handed to out(row, column, value): Gauss-Jordan
+// with a wavefront per 16 rows in registers (lane = column); the pivot row passes through
 // LDS, one barrier per pivot. first: index of the tile's first row; rows from k on
-// are padding. About 0.5 us per pivot (2 us with the tile in LDS: two barriers and
-// 16 LDS updates per thread and pivot).
-__device__ void invert_tile(double* t, double (*row)[GJ_W], const GjBatch& b, int first, int k,
-                            double* __restrict__ inv) {
+// are padding with the identity, whose pivots change nothing and are left out. About 0.5 us
+// per pivot (2 us with the tile in LDS: two barriers and 16 LDS updates per thread and pivot).
+template <class F>
+__device__ __forceinline__ void invert_tile(double* t, double (*row)[GJ_W], const double* diag0, int* status,
+                                            int first, int k, F out) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     double a[16];
 #pragma unroll
@@ -326,12 +326,13 @@ __device__ void invert_tile(double* t, double (*row)[GJ_W], const GjBatch& b, in
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int q = 16 * o + i;
+            if (first + q >= k) break;  // uniform
             if (wave == o) row[i & 1][lane] = a[i];
             __syncthreads();
             const double rq = row[i & 1][lane], dq = row[i & 1][q];
-            if (threadIdx.x == 0 && first + q < k) {
-                const double floor = b.diag0 ? GJ_REL * fabs(b.diag0[first + q]) : 0.0;
-                if (!(dq > floor) || !isfinite(dq)) atomicOr(b.status, 1);
+            if (threadIdx.x == 0) {
+                const double floor = diag0 ? GJ_REL * fabs(diag0[first + q]) : 0.0;
+                if (!(dq > floor) || !isfinite(dq)) atomicOr(status, 1);
             }
             const double piv = 1.0 / dq;
             const bool me = lane == q;
@@ -349,7 +350,69 @@ __device__ void invert_tile(double* t, double (*row)[GJ_W], const GjBatch& b, in
         }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) inv[(16 * wave + r) * GJ_W + lane] = a[r];
+    for (int r = 0; r < 16; ++r) out(16 * wave + r, lane, a[r]);
+}
+// The same into a row-major tile.
+__device__ void invert_tile(double* t, double (*row)[GJ_W], const GjBatch& b, int first, int k,
+                            double* __restrict__ inv) {
+    invert_tile(t, row, b.diag0, b.status, first, k, [&](int r, int c, double v) { inv[r * GJ_W + c] = v; });
+}
+
+// (R_i A R_i^T)^{-1} of a sub-mesh of at most one tile, as a square of even row stride:
+// assembled and inverted in LDS, four threads per row of the matrix.
+__global__ __launch_bounds__(GJ_THREADS) void lu_small_kernel(LuMatrix a, const int32_t* __restrict__ subs,
+                                                             const int64_t* __restrict__ lu_off,
+                                                             double* __restrict__ inv, int* status) {
+    __shared__ __align__(16) double t[GJ_N];
+    __shared__ double row[2][GJ_W];
+    __shared__ int32_t nodes[GJ_W];
+    const int i = subs[blockIdx.x], b = a.sub_ptr[i], k = a.sub_ptr[i + 1] - b;
+    for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) t[e] = 0.0;
+    if ((int)threadIdx.x < k) nodes[threadIdx.x] = a.sub_nodes[b + threadIdx.x];
+    __syncthreads();
+    const int j = threadIdx.x / 4;
+    if (j < k) {
+        const int32_t g = nodes[j], e1 = a.rowptr[g + 1];
+        for (int32_t e = a.rowptr[g] + threadIdx.x % 4; e < e1; e += 4) {
+            const int q = find_local(nodes, k, a.col[e]);
+            if (q >= 0) el(t, j, q) = a.val[e];
+        }
+    } else if (threadIdx.x % 4 == 0) {
+        el(t, j, j) = 1.0;
+    }
+    __syncthreads();
+    const int ld = (k + 1) & ~1;
+    double* const M = inv + lu_off[i];
+    invert_tile(t, row, nullptr, status, 0, k, [&](int r, int c, double v) {
+        if (r < k && c < ld) M[r * ld + c] = c < k ? v : 0.0;
+    });
+}
+
+// Squares of the inverses from their tiles (which hold the negative): workgroup (x, y) takes
+// tile y of matrix x, transposed through LDS where the square holds it twice.
+__global__ __launch_bounds__(GJ_THREADS) void lu_pack_kernel(const int32_t* __restrict__ sub_ptr,
+                                                            const int32_t* __restrict__ subs,
+                                                            const int64_t* __restrict__ off,
+                                                            const double* __restrict__ base,
+                                                            const int64_t* __restrict__ lu_off,
+                                                            double* __restrict__ inv) {
+    __shared__ double t[GJ_W][GJ_W + 1];
+    const int i = subs[blockIdx.x], k = sub_ptr[i + 1] - sub_ptr[i], ld = (k + 1) & ~1;
+    int I = 0, J = blockIdx.y;
+    while (J > I) J -= ++I;
+    if (I * GJ_W >= k) return;
+    const double* T = base + off[blockIdx.x] + sym_tile(I, J);
+    double* M = inv + lu_off[i];
+    for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) t[e / GJ_W][e % GJ_W] = -T[e];
+    __syncthreads();
+    auto put = [&](int r, int c, double v) {
+        if (r < k && c < ld) M[r * ld + c] = c < k ? v : 0.0;
+    };
+    for (int e = threadIdx.x; e < GJ_N; e += GJ_THREADS) {
+        const int r = e / GJ_W, c = e % GJ_W;
+        put(I * GJ_W + r, J * GJ_W + c, t[r][c]);
+        if (I != J) put(J * GJ_W + r, I * GJ_W + c, t[c][r]);
+    }
 }
 
 // The first pivot block of every matrix.
@@ -610,11 +673,26 @@ hipError_t launch_coarse_invert(double* a0, int K, const double* diag0, double* 
     return hipGetLastError();
 }
 
-hipError_t launch_lu_assemble(const int32_t* rowptr, const int32_t* col, const double* val, const int64_t* sub_ptr,
-                              const int32_t* sub_nodes, const int64_t* off, double* inv, int n_sub, hipStream_t s) {
-    if (n_sub <= 0) return hipSuccess;
-    hipLaunchKernelGGL(lu_assemble_kernel, dim3(n_sub), dim3(GJ_THREADS), 0, s, rowptr, col, val, sub_ptr,
-                       sub_nodes, off, inv);
+hipError_t launch_lu_assemble(const LuMatrix& a, const int32_t* subs, int n, const int64_t* off, double* base,
+                              hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(lu_assemble_kernel, dim3(n), dim3(GJ_THREADS), 0, s, a, subs, off, base);
+    return hipGetLastError();
+}
+
+hipError_t launch_lu_small(const LuMatrix& a, const int32_t* subs, int n, const int64_t* lu_off, double* out,
+                           int* status, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(lu_small_kernel, dim3(n), dim3(GJ_THREADS), 0, s, a, subs, lu_off, out, status);
+    return hipGetLastError();
+}
+
+hipError_t launch_lu_pack(const int32_t* sub_ptr, const int32_t* subs, int n, const int64_t* off, const double* base,
+                          const int64_t* lu_off, double* out, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    constexpr int NT = (LU_DENSE_K + GJ_W - 1) / GJ_W;
+    hipLaunchKernelGGL(lu_pack_kernel, dim3(n, NT * (NT + 1) / 2), dim3(GJ_THREADS), 0, s, sub_ptr, subs, off, base,
+                       lu_off, out);
     return hipGetLastError();
 }
 

@@ -503,7 +503,7 @@ __global__ __launch_bounds__(BLOCK) void dss_kernel(DssArgs<T> a, const T* __res
 // DDM-LU (the paper's comparator, eq. (7)): local = (R_i A R_i^T)^{-1} R_i r with
 // the inverse formed at setup, symmetric, and held (negated) as the 64 x 64 tiles of its
 // lower triangle: a tile serves its rows and its columns, so half the matrix is
-// read. A sub-mesh is shared by lu_units(k) workgroups of equal work (unit u takes
+// read (small sub-meshes: lu_dense_solve). A sub-mesh is shared by lu_units(k) workgroups of equal work (unit u takes
 // rows u and nt - 1 - u of tiles), so that a launch of few sub-meshes fills the
 // chip and a large sub-mesh does not end last; each unit writes a partial vector,
 // and lu_sum_kernel adds a sub-mesh's in unit order. Unit 0 also writes
@@ -519,6 +519,55 @@ __global__ __launch_bounds__(BLOCK) void dss_kernel(DssArgs<T> a, const T* __res
 // own vector in LDS (YLDS), or
 // in the unit's partial vector (one wavefront per workgroup, sub-meshes whose four
 // vectors would not fit).
+// Sub-meshes held as squares of row stride lu_ld(k) (lu_dense): one workgroup each, which
+// writes the result itself. Bound by one chain of loads up to about 200 sub-meshes, then by HBM.
+// local_j = sum_c M[c][j] x_c: a wavefront owns a strip of 128 columns (two per lane) and walks
+// its part of the rows in order; the parts' sums are added in order through LDS.
+__device__ __forceinline__ void lu_dense_solve(const DevProb& P, int sub, int base, int k, double* xs, double* red) {
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) v2* gp;
+    constexpr int STRIP = 128, WAVES = 4;
+    static_assert(LU_DENSE_K <= STRIP * WAVES, "a wavefront per strip");
+    const double* __restrict__ r = P.r;
+    double ss = 0.0, yy = 0.0;
+    for (int j = threadIdx.x; j < k; j += 64 * WAVES) {
+        const double v = r[P.sub_nodes[base + j]];
+        xs[j] = v;
+        ss = fma(v, v, ss);
+        yy = fma(P.weights[base + j], v, yy);
+    }
+    // (the barriers of the sums also publish xs)
+    ss = block_sum<64 * WAVES>(ss, red);
+    yy = block_sum<64 * WAVES>(yy, red);
+    if (threadIdx.x == 0) {
+        P.s[sub] = sqrt(ss);
+        P.y0[sub] = yy;
+    }
+    double* const yp = xs + (k + 1) / 2 * 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ns = (k + STRIP - 1) / STRIP, parts = WAVES / ns, rpp = (k + parts - 1) / parts;
+    const int ld2 = (k + 1) / 2, j = wave % ns * STRIP + 2 * lane, part = wave / ns;
+    if (part < parts && j < k) {
+        const int c1 = min(k, (part + 1) * rpp);
+        gp col = (gp)(P.lu_inv + P.lu_off[sub] + j);
+        double a0 = 0.0, a1 = 0.0;  // column j + 1 may be the zero pad of an odd k
+#pragma unroll 16
+        for (int c = part * rpp; c < c1; ++c) {
+            const v2 v = col[(size_t)c * ld2];
+            a0 = fma(v[0], xs[c], a0);
+            a1 = fma(v[1], xs[c], a1);
+        }
+        yp[part * k + j] = a0;
+        if (j + 1 < k) yp[part * k + j + 1] = a1;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < k; i += 64 * WAVES) {
+        double acc = yp[i];
+        for (int q = 1; q < parts; ++q) acc += yp[q * k + i];
+        P.local[base + i] = acc;
+    }
+}
+
 template <bool YLDS>
 __global__ __launch_bounds__(YLDS ? 256 : 64, YLDS ? 3 : 2) void lu_local_kernel(const DevProb* __restrict__ tab,
                                                                   const int4* __restrict__ units) {
@@ -531,10 +580,12 @@ __global__ __launch_bounds__(YLDS ? 256 : 64, YLDS ? 3 : 2) void lu_local_kernel
     const int sub = wi.y, unit = wi.z;
     const int base = P.sub_ptr[sub];
     const int k = P.sub_ptr[sub + 1] - base;
+    if constexpr (YLDS)
+        if (unit < 0) return lu_dense_solve(P, sub, base, k, xs, red);
     const int nt = (k + 63) / 64, kp = nt * 64;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const double* __restrict__ r = P.r;
-    double* const part = P.lu_part + P.lu_poff[sub] + (size_t)unit * k;
+    double* const part = P.lu_inv + P.lu_off[P.K + sub] + (size_t)unit * k;
     double* const ys = YLDS ? xs + (size_t)(1 + wave) * kp : part;
     double ss = 0.0, yy = 0.0;
     for (int j = threadIdx.x; j < kp; j += BLOCK) {
@@ -658,7 +709,7 @@ __global__ __launch_bounds__(VEC_BLOCK) void lu_sum_kernel(const DevProb* __rest
     const int base = P.sub_ptr[wi.y], k = P.sub_ptr[wi.y + 1] - base, nu = lu_units(k);
     const int j = blockIdx.y * VEC_BLOCK + threadIdx.x;
     if (j >= k) return;
-    const double* __restrict__ part = P.lu_part + P.lu_poff[wi.y] + j;
+    const double* __restrict__ part = P.lu_inv + P.lu_off[P.K + wi.y] + j;
     double acc = 0.0;
 #pragma unroll 8
     for (int u = 0; u < nu; ++u) acc += part[(size_t)u * k];

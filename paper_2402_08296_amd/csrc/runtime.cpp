@@ -43,9 +43,11 @@ struct Batch {
     int n_mfma_small = 0;
     size_t lds_mfma = 0, lds_mfma_small = 0;
     int max_k_all = 0, max_k_rest = 0, max_k_valu = 0;
-    // units of work_valu's and work_big's sub-meshes in the exact local solves
+    // units of work_valu's and work_big's sub-meshes in the exact local solves, and the
+    // sub-meshes whose inverses are held in tiles
     DevBuf<int4> lu_small, lu_big;
-    int n_lu_small = 0, n_lu_big = 0;
+    DevBuf<int2> lu_subs;
+    int n_lu_small = 0, n_lu_big = 0, n_lu_subs = 0;
     // tiles of work_valu and work_rest for the tiled FP64 / FP32 forward (d = 10), by
     // problem and sub-mesh; built at the first use
     DevBuf<int4> tiles_valu, tiles_rest;
@@ -84,7 +86,7 @@ DevProb make_view(ddmgnn_problem* P) {
     v.vt64 = {P->vt64.rec.p, P->vt64.info.p, P->vt64.h.p, {P->vt64.q.p, P->vt64.q.p ? P->vt64.q.p + qn : nullptr}};
     v.vt32 = {P->vt32.rec.p, P->vt32.info.p, P->vt32.h.p, {P->vt32.q.p, P->vt32.q.p ? P->vt32.q.p + qn : nullptr}};
     v.node_ptr = P->node_ptr.p; v.node_slots = P->node_slots.p; v.slot_sub = P->slot_sub.p; v.a0inv = P->a0inv.p;
-    v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p; v.lu_part = P->lu_part.p; v.lu_poff = P->lu_poff.p;
+    v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p;
     v.gm_v = P->gm_v.p; v.gm_z = P->gm_z.p; v.gm_part = P->gm_part.p; v.gm_small = P->gm_small.p;
     v.u = P->u.p; v.r = P->r.p; v.z = P->z.p; v.c_in = nullptr;
     const int64_t n = P->hs.n;
@@ -137,6 +139,9 @@ int pivots_ok(const DevBuf<int>& status, hipStream_t s) {
     return bad ? DDMGNN_E_NOT_SPD : DDMGNN_OK;
 }
 
+// Most doubles of tiles and panels while inverses that are kept as squares are formed.
+constexpr int64_t LU_TEMP = 64 << 20;
+
 // Exact local solves: the inverses of R_i A R_i^T, assembled from the problem's
 // device matrix and inverted on the device.
 int prepare_lu(ddmgnn_problem* P) {
@@ -144,33 +149,92 @@ int prepare_lu(ddmgnn_problem* P) {
     if (P->lu_inv.p) return DDMGNN_OK;
     hipStream_t s = P->ctx->stream;
     const auto& hs = P->hs;
-    std::vector<int64_t> off((size_t)hs.K + 1, 0), poff((size_t)hs.K + 1, 0);
-    std::vector<int32_t> k((size_t)hs.K);
+    const LuMatrix A{P->rowptr.p, P->col.p, P->val.p, P->sub_ptr.p, P->sub_nodes.p};
+    std::vector<int64_t> off((size_t)hs.K * 2, 0);
+    int64_t total = 0;
+    // A group of sub-meshes inverted together: their tiles lie in lu_inv, or in a buffer from
+    // which their squares are packed.
+    struct Group {
+        std::vector<int32_t> subs, k;
+        std::vector<int64_t> at;  // offset of each one's tiles
+        int64_t doubles = 0, temp = 0;
+        size_t list = 0, meta = 0, off = 0;  // its arrays in the device lists
+    };
+    int max_k = 0;
+    for (int32_t i = 0; i < hs.K; ++i) max_k = std::max(max_k, (int)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]));
+    std::vector<int32_t> lists;  // the sub-meshes of one tile, then of every group its sub-meshes and plan
+    std::vector<Group> groups(1);  // the first: tiles in lu_inv
+    // Tiles, then squares, then partial products: tiles start on a cache line, and partial
+    // products between them cost a launch 2%.
     for (int32_t i = 0; i < hs.K; ++i) {
-        k[i] = (int32_t)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
-        off[i + 1] = off[i] + sym_doubles(k[i]);
-        poff[i + 1] = poff[i] + (int64_t)lu_units(k[i]) * k[i];
+        const int32_t k = (int32_t)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
+        if (lu_dense(k, max_k)) continue;
+        groups[0].subs.push_back(i);
+        groups[0].k.push_back(k);
+        groups[0].at.push_back(off[i] = total);
+        total += sym_doubles(k);
+    }
+    groups[0].doubles = total;
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int32_t k = (int32_t)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
+        if (!lu_dense(k, max_k)) continue;
+        off[i] = total;
+        total += k * lu_ld(k);
+        if (k <= SYM_TILE) {
+            lists.push_back(i);
+            continue;
+        }
+        const int64_t d = sym_doubles(k), t = d + (2 * ((k + SYM_TILE - 1) / SYM_TILE) + 1) * SYM_TILE * SYM_TILE;
+        if (groups.size() == 1 || groups.back().temp + t > LU_TEMP) groups.emplace_back();
+        Group& g = groups.back();
+        g.subs.push_back(i);
+        g.k.push_back(k);
+        g.at.push_back(g.doubles);
+        g.doubles += d;
+        g.temp += t;
+    }
+    for (size_t q = 0; q < groups[0].subs.size(); ++q) {
+        off[(size_t)hs.K + groups[0].subs[q]] = total;
+        total += (int64_t)lu_units(groups[0].k[q]) * groups[0].k[q];
+    }
+    const int n_small = (int)lists.size();
+    std::vector<GjPlan> plans;
+    size_t n_tiles = 0, n_scratch = 0;
+    for (Group& g : groups) {
+        plans.emplace_back(g.k);
+        const GjPlan& plan = plans.back();
+        g.list = lists.size();
+        lists.insert(lists.end(), g.subs.begin(), g.subs.end());
+        g.meta = lists.size();
+        lists.insert(lists.end(), plan.meta.begin(), plan.meta.end());
+        g.off = off.size();
+        off.insert(off.end(), g.at.begin(), g.at.end());
+        if (!g.subs.empty()) n_scratch = std::max(n_scratch, plan.scratch_doubles());
+        if (&g != &groups[0]) n_tiles = std::max(n_tiles, (size_t)g.doubles);
     }
     auto build = [&]() -> int {
-        DevBuf<int64_t> sub_ptr64;
-        const size_t n = (size_t)std::max<int64_t>(off[hs.K], 1);
-        HIP_TRY(sub_ptr64.upload(hs.sub_ptr.data(), hs.sub_ptr.size(), s));
-        HIP_TRY(P->lu_off.upload(off.data(), off.size(), s));
-        HIP_TRY(P->lu_poff.upload(poff.data(), poff.size(), s));
-        HIP_TRY(P->lu_part.alloc((size_t)std::max<int64_t>(poff[hs.K], 1)));
-        HIP_TRY(P->lu_inv.alloc(n));
-        HIP_TRY(hipMemsetAsync(P->lu_inv.p, 0, n * sizeof(double), s));
-        HIP_TRY(launch_lu_assemble(P->rowptr.p, P->col.p, P->val.p, sub_ptr64.p, P->sub_nodes.p, P->lu_off.p,
-                                   P->lu_inv.p, hs.K, s));
-        const GjPlan plan(k);
-        DevBuf<int32_t> meta;
-        DevBuf<double> scratch;
+        DevBuf<int32_t> d_lists;
+        DevBuf<double> temp;  // panels, then the tiles of a packed group
         DevBuf<int> status;
-        HIP_TRY(meta.upload(plan.meta.data(), plan.meta.size(), s));
-        HIP_TRY(scratch.alloc(plan.scratch_doubles()));
+        HIP_TRY(P->lu_off.upload(off.data(), off.size(), s));
+        HIP_TRY(d_lists.upload(lists.data(), lists.size(), s));
+        HIP_TRY(P->lu_inv.alloc((size_t)std::max<int64_t>(total, 1)));
+        HIP_TRY(temp.alloc(n_scratch + n_tiles));
         HIP_TRY(status.alloc(1));
         HIP_TRY(hipMemsetAsync(status.p, 0, sizeof(int), s));
-        HIP_TRY(launch_gj_invert(plan, meta.p, P->lu_inv.p, P->lu_off.p, scratch.p, status.p, s));
+        for (size_t q = 0; q < groups.size(); ++q) {
+            const Group& g = groups[q];
+            const int n = (int)g.subs.size();
+            if (n == 0) continue;
+            double* const base = q ? temp.p + n_scratch : P->lu_inv.p;
+            const int32_t* subs = d_lists.p + g.list;
+            const int64_t* at = P->lu_off.p + g.off;
+            HIP_TRY(hipMemsetAsync(base, 0, (size_t)g.doubles * sizeof(double), s));
+            HIP_TRY(launch_lu_assemble(A, subs, n, at, base, s));
+            HIP_TRY(launch_gj_invert(plans[q], d_lists.p + g.meta, base, at, temp.p, status.p, s));
+            if (q) HIP_TRY(launch_lu_pack(P->sub_ptr.p, subs, n, at, base, P->lu_off.p, P->lu_inv.p, s));
+        }
+        HIP_TRY(launch_lu_small(A, d_lists.p, n_small, P->lu_off.p, P->lu_inv.p, status.p, s));
         const int rc = pivots_ok(status, s);
         if (rc == DDMGNN_E_NOT_SPD) return fail(rc, "a local matrix R_i A R_i^T is not positive definite");
         return rc;
@@ -178,8 +242,6 @@ int prepare_lu(ddmgnn_problem* P) {
     if (int rc = build()) {  // leave no half-built inverses behind
         P->lu_inv.reset();
         P->lu_off.reset();
-        P->lu_part.reset();
-        P->lu_poff.reset();
         return rc;
     }
     P->device_bytes += lu_bytes(hs);
@@ -504,7 +566,7 @@ int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool cap
     const bool check = !capturing;
     if (local == DDMGNN_LOCAL_LU) {
         const LuWork w{B.lu_small.p, B.n_lu_small, B.max_k_valu, B.lu_big.p, B.n_lu_big, B.max_k_all,
-                       B.work_all.p, B.n_all};
+                       B.lu_subs.p, B.n_lu_subs};
         HIP_TRY(launch_lu_local(tab, w, s, check));
         return DDMGNN_OK;
     }
@@ -798,10 +860,14 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     };
     std::vector<W> all;
     std::vector<int2> vec, rows;
+    std::vector<int> max_k((size_t)n, 0);  // largest sub-mesh of each problem
     for (int i = 0; i < n; ++i) {
         const ddmgnn_problem* P = probs[i];
         const auto& sp = P->hs.sub_ptr;
-        for (int j = 0; j < P->hs.K; ++j) all.push_back({(int)(sp[j + 1] - sp[j]), i, j});
+        for (int j = 0; j < P->hs.K; ++j) {
+            all.push_back({(int)(sp[j + 1] - sp[j]), i, j});
+            max_k[i] = std::max(max_k[i], all.back().k);
+        }
         const int nb = problem_vec_blocks(P);
         for (int b = 0; b < nb; ++b) vec.push_back(make_int2(i, b));
         for (int r = 0; r < P->hs.K; ++r) rows.push_back(make_int2(i, r));
@@ -812,15 +878,20 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         if (a.p != b.p) return a.p < b.p;
         return a.sub < b.sub;
     });
-    std::vector<int2> wa, wm, wms, wr, wv, wb;
+    std::vector<int2> wa, wm, wms, wr, wv, wb, ls;
     std::vector<int4> lus, lub;
     size_t lds_sb = 0, lds_db = 0, lds_small_sb = 0, lds_small_db = 0;
     for (const W& w : all) {
         wa.push_back(make_int2(w.p, w.sub));
         B->max_k_all = std::max(B->max_k_all, w.k);
         static_assert(LU_LDS_K == kMaxSubNodes, "work_valu holds the sub-meshes of the exact solves' LDS form");
-        for (int u = 0; u < lu_units(w.k); ++u)
-            (w.k > kMaxSubNodes ? lub : lus).push_back(make_int4(w.p, w.sub, u, 0));
+        if (lu_dense(w.k, max_k[w.p])) {
+            lus.push_back(make_int4(w.p, w.sub, -1, 0));
+        } else {
+            ls.push_back(make_int2(w.p, w.sub));
+            for (int u = 0; u < lu_units(w.k); ++u)
+                (w.k > kMaxSubNodes ? lub : lus).push_back(make_int4(w.p, w.sub, u, 0));
+        }
         const ddmgnn_problem* Q = probs[w.p];
         if (w.k > kMaxSubNodes) {
             wb.push_back(make_int2(w.p, w.sub));
@@ -855,6 +926,8 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     B->lds_mfma_small = std::max(lds_small_sb, lds_small_db);
     hipStream_t s = ctx->stream;
     if (int rc = upload_list(B->work_all, wa, s)) return rc;
+    if (int rc = upload_list(B->lu_subs, ls, s)) return rc;
+    B->n_lu_subs = (int)ls.size();
     if (int rc = upload_list(B->lu_small, lus, s)) return rc;
     if (int rc = upload_list(B->lu_big, lub, s)) return rc;
     B->n_lu_small = (int)lus.size();
@@ -1022,17 +1095,16 @@ int check_opts(const ddmgnn_solve_opts& o) {
     return DDMGNN_OK;
 }
 
-// Bytes a problem counts for its exact local solves: k_i^2 doubles per sub-mesh, which
-// covers the tiles (about half), the partial products and the panels of the
-// factorisation, or the tiles and partial products where those are more (small k_i).
+// Bytes a problem counts for its exact local solves: a square per sub-mesh, which is what
+// the small ones hold and covers the tiles (about half), the partial products and most of
+// the panels of the factorisation of the others.
 size_t lu_bytes(const HostSetup& hs) {
-    size_t dense = 0, held = 0;
+    size_t b = 0;
     for (int32_t i = 0; i < hs.K; ++i) {
         const int64_t k = hs.sub_ptr[i + 1] - hs.sub_ptr[i];
-        dense += (size_t)(k * lu_ld(k)) * 8 + 8;
-        held += (size_t)(sym_doubles(k) + lu_units((int)k) * k) * 8 + 16;
+        b += (size_t)(k * lu_ld(k)) * 8 + 8;
     }
-    return std::max(dense, held);
+    return b;
 }
 
 // Bytes of the tiled DSS forward's arrays of a problem in one precision (`tiles` tiles,

@@ -220,8 +220,8 @@ struct ddmgnn_problem {
     ddmgnn::DevBuf<float> hglobal32;  // FP32 h of the sub-meshes beyond kMaxSubNodes
     ddmgnn::DevBuf<double> cglobal;   // their c (FP64, or FP32 in the same storage)
     // exact local solves (built on the first solve with local_solver = LU)
-    ddmgnn::DevBuf<double> lu_inv, lu_part;
-    ddmgnn::DevBuf<int64_t> lu_off, lu_poff;
+    ddmgnn::DevBuf<double> lu_inv;
+    ddmgnn::DevBuf<int64_t> lu_off;
     // FGMRES basis, preconditioned vectors, partial sums and small arrays (built on
     // the first FGMRES solve, for cycles of up to gm_R steps)
     ddmgnn::DevBuf<double> gm_v, gm_z, gm_part, gm_small;

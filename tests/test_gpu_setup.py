@@ -189,3 +189,48 @@ def test_coarse_inverse_at_tile_edges(ctx, K):
     y = prob.intermediates()[2].cpu().numpy()
     ref = np.linalg.solve(co.A0, co.Z.T @ r)
     assert np.abs(y - ref).max() <= K * np.finfo(float).eps * np.linalg.cond(co.A0) * np.abs(ref).max()
+
+
+def _local_terms_match(ctx, n, seed, sizes, which):
+    p = W.make_problem(seed, n, 4, 0.2)
+    hp = oracle_problem(p)
+    nodes = np.argsort(p.mesh.dirichlet, kind="stable")
+    sp = np.concatenate([[0], np.cumsum(sizes), [p.n]]) if sum(sizes) < p.n else np.concatenate([[0], np.cumsum(sizes)])
+    for a, b in zip(sp[:-1], sp[1:]):
+        nodes[a:b].sort()
+    w = np.where(p.mesh.dirichlet[nodes], 0.0, 1.0)
+    hp = dg.HostProblem(hp.xy, hp.tri, hp.dirichlet, hp.rowptr, hp.col, hp.val, hp.b, hp.u0, sp, nodes, w)
+    prob = dg.Problem(ctx, hp, dg.Model(ctx, SMOOTHER))
+    before = prob.device_bytes()
+    A = p.A.to_scipy().tocsr()
+    r = p.b - A @ p.u0
+    z = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    prob.apply(torch.from_numpy(r).cuda(), z, dg.default_opts(local_solver=dg.LOCAL_LU, prolong=dg.PROLONG_UNWEIGHTED))
+    s, _, _, loc = [t.cpu().numpy() for t in prob.intermediates()]
+    for i in which:
+        idx = hp.sub_nodes[sp[i]:sp[i + 1]]
+        Ai = A[idx][:, idx].toarray()
+        ref = np.linalg.solve(Ai, r[idx])
+        err = np.abs(loc[sp[i]:sp[i + 1]] - ref).max() / np.abs(ref).max()
+        assert err <= idx.size * np.finfo(float).eps * np.linalg.cond(Ai), idx.size
+        assert s[i] == pytest.approx(np.linalg.norm(r[idx]), rel=1e-13)
+    # a square per sub-mesh is counted, whatever form it is held in
+    k = np.diff(sp).astype(np.int64)
+    assert prob.device_bytes() - before == int((8 * k * ((k + 1) // 2 * 2) + 8).sum())
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("sizes", [[1, 1, 3, 16, 61, 64], [66, 127, 128, 129, 131, 192, 193], [201, 255, 256, 257], [7, 2048, 64]])
+def test_small_local_inverses(ctx, sizes):
+    """Local terms of a DDM-LU apply where inverses are held as squares (up to 256 nodes: one
+    tile inverted in LDS, or packed from tiles; one or two strips of 128 columns), beside
+    sub-meshes held in tiles."""
+    print(f"[gpu] small local inverses of orders {sizes}", flush=True)
+    _local_terms_match(ctx, 9000, 16, sizes, range(len(sizes)))
+
+
+@pytest.mark.timeout(300)
+def test_many_small_local_inverses(ctx):
+    """More squares than are packed from one buffer of tiles (2048 of 65 nodes)."""
+    print("[gpu] 2060 local inverses of order 65", flush=True)
+    _local_terms_match(ctx, 140_000, 17, [65] * 2060, [0, 1, 2046, 2047, 2048, 2049, 2059])
