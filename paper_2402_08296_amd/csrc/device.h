@@ -110,7 +110,7 @@ struct DevProb {
     const double* xy64;         // per slot, raw coordinates
     const float* xyc32;         // per slot, sub-mesh-centred coordinates
     // tiles of 16 nodes of the FP64 and FP32 DSS forward (width 10; null until its first use)
-    const int32_t* vt_ptr;      // [K + 1] tiles of each sub-mesh
+    const int32_t* vt_first;    // [K] first tile of each sub-mesh
     const int2* vt_node;        // per tile and lane: slot (-1: none), in-degree
     VtVecs<double> vt64;
     VtVecs<float> vt32;

@@ -147,7 +147,7 @@ __global__ __launch_bounds__(RB) void dss_restrict_kernel(const DevProb* __restr
     __syncthreads();
     const VtVecs<T>& V = vecs<T>(P);
     const int lane = tid & 63, n = lane & 15, g = lane >> 4;
-    const int t0 = P.vt_ptr[sub], t1 = P.vt_ptr[sub + 1];
+    const int t0 = P.vt_first[sub], t1 = t0 + (k + VT_TILE - 1) / VT_TILE;
     for (int t = t0 + (tid >> 6); t < t1; t += RB / 64) {
         const int2 nd = P.vt_node[(size_t)t * VT_TILE + n];
         const size_t sl = nd.x >= 0 ? (size_t)nd.x : (size_t)base;

@@ -81,10 +81,7 @@ DevProb make_view(ddmgnn_problem* P) {
     v.edge_ptr = P->edge_ptr.p; v.edge_src = P->edge_src.p; v.edge_nd = P->edge_nd.p; v.erec = P->erec.p;
     v.epad_sub = P->epad_sub.p;
     v.tiles = P->tiles.p; v.xy64 = P->xy64.p; v.xyc32 = P->xyc32.p;
-    v.vt_ptr = P->vt_ptr.p; v.vt_node = P->vt_node.p;
-    const size_t qn = (P->vt_tiles.size() * VT_TILE + 1) * 2 * D;
-    v.vt64 = {P->vt64.rec.p, P->vt64.info.p, P->vt64.h.p, {P->vt64.q.p, P->vt64.q.p ? P->vt64.q.p + qn : nullptr}};
-    v.vt32 = {P->vt32.rec.p, P->vt32.info.p, P->vt32.h.p, {P->vt32.q.p, P->vt32.q.p ? P->vt32.q.p + qn : nullptr}};
+    v.vt_first = P->vt_first_dev; v.vt_node = P->vt_node; v.vt64 = P->vt64.v; v.vt32 = P->vt32.v;
     v.node_ptr = P->node_ptr.p; v.node_slots = P->node_slots.p; v.slot_sub = P->slot_sub.p; v.a0inv = P->a0inv.p;
     v.lu_inv = P->lu_inv.p; v.lu_off = P->lu_off.p;
     v.gm_v = P->gm_v.p; v.gm_z = P->gm_z.p; v.gm_part = P->gm_part.p; v.gm_small = P->gm_small.p;
@@ -292,26 +289,41 @@ bool runs_tiled(int d, int precision, int64_t tiles) {
     return d == D && (precision == DDMGNN_FP64 || tiles <= VT_MAX_FP32);
 }
 
+// Parts of one allocation, each on a cache line; a first pass without a base measures it.
+struct Carver {
+    char* base;
+    size_t used = 0;
+    template <typename T>
+    T* take(size_t n) {
+        T* p = base ? reinterpret_cast<T*>(base + used) : nullptr;
+        used += (n * sizeof(T) + 255) / 256 * 256;
+        return p;
+    }
+};
+
 // Tiles of the sub-meshes of at most kMaxSubNodes nodes: their nodes by decreasing
 // in-degree (tnode), so a tile's edge rows are its first node's in-degree (made even: rows
-// are summed in pairs).
+// are summed in pairs). The sub-meshes that the BF16 kernel does not run come first: BF16
+// keeps arrays for those only.
 void list_tiles(ddmgnn_problem* P) {
     if (!P->vt_first.empty()) return;
     const auto& hs = P->hs;
-    P->vt_first.assign((size_t)hs.K + 1, 0);
-    int64_t rows = 0;
-    for (int32_t i = 0; i < hs.K; ++i) {
-        const int64_t b = hs.sub_ptr[i], k = hs.sub_ptr[i + 1] - b;
-        if (k <= kMaxSubNodes)
+    P->vt_first.assign((size_t)hs.K, 0);
+    for (int side = 0; side < 2; ++side) {
+        for (int32_t i = 0; i < hs.K; ++i) {
+            const int64_t b = hs.sub_ptr[i], k = hs.sub_ptr[i + 1] - b;
+            if (mfma_runs_sub(P, i) != (side == 1) || k > kMaxSubNodes) continue;
+            P->vt_first[i] = (int32_t)P->vt_tiles.size();
             for (int64_t q = 0; q < k; q += VT_TILE) {
                 const int64_t slot = b + hs.tnode[b + q];
                 const int64_t deg = (hs.edge_ptr[slot + 1] - hs.edge_ptr[slot] + 1) & ~int64_t(1);
-                P->vt_tiles.push_back(make_int4((int)b, (int)q, (int)rows, (int)deg));
-                rows += deg;
+                P->vt_tiles.push_back(make_int4((int)b, (int)q, (int)P->vt_all.rows, (int)deg));
+                P->vt_all.rows += deg;
             }
-        P->vt_first[i + 1] = (int32_t)P->vt_tiles.size();
+        }
+        P->vt_all.tiles = (int64_t)P->vt_tiles.size();
+        if (side == 0) P->vt_rest = P->vt_all;
     }
-    P->vt_rows = rows;
 }
 
 // The nodes of P's tiles and the slots' tile lanes (hook: a one-problem table to build
@@ -319,49 +331,77 @@ void list_tiles(ddmgnn_problem* P) {
 int prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
     hipStream_t s = P->ctx->stream;
     list_tiles(P);
-    const size_t nt = P->vt_tiles.size();
+    const size_t nt = P->vt_tiles.size(), K = (size_t)P->hs.K;
     const DevProb v = make_view(P);
     HIP_TRY(launch_set_view(hook.p, v, s));
-    if (P->vt_pos.p) return DDMGNN_OK;
-    HIP_TRY(P->vt_info.upload(P->vt_tiles.data(), nt, s));
-    HIP_TRY(P->vt_ptr.upload(P->vt_first.data(), P->vt_first.size(), s));
-    HIP_TRY(P->vt_node.alloc(nt * VT_TILE));
-    DevBuf<int32_t> pos;  // moved in last: a failed build is retried whole
-    HIP_TRY(pos.alloc((size_t)P->hs.sk));
-    HIP_TRY(launch_vt_nodes(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, pos.p, s));
-    std::swap(P->vt_pos.p, pos.p);
-    std::swap(P->vt_pos.n, pos.n);
+    if (P->vt_pos) return DDMGNN_OK;
+    // the tiles and the first of every sub-mesh: one copy
+    std::vector<VtTile> host(P->vt_tiles);
+    host.resize(nt + (K + 3) / 4);
+    std::memcpy(host.data() + nt, P->vt_first.data(), K * sizeof(int32_t));
+    auto carve = [&](Carver c, bool set) {
+        VtTile* info = c.take<VtTile>(host.size());
+        int2* node = c.take<int2>(nt * VT_TILE);
+        int32_t* pos = c.take<int32_t>((size_t)P->hs.sk);
+        if (set) {
+            P->vt_info = info;
+            P->vt_first_dev = reinterpret_cast<int32_t*>(info + nt);
+            P->vt_node = node;
+            P->vt_pos = pos;
+        }
+        return c.used;
+    };
+    HIP_TRY(P->vt_mem.alloc(carve(Carver{nullptr}, false)));
+    HIP_TRY(upload_async(P->vt_mem.p, host.data(), host.size() * sizeof(VtTile), s));
+    carve(Carver{P->vt_mem.p}, true);
+    const hipError_t e = launch_vt_nodes(hook.p, P->vt_info, (int)nt, P->vt_node, P->vt_pos, s);
+    if (e != hipSuccess) P->vt_pos = nullptr;  // a failed build is retried whole
+    HIP_TRY(e);
+    P->device_bytes += tile_node_bytes((int64_t)nt, P->hs.sk, P->hs.K);
     return DDMGNN_OK;
 }
 
-// Builds the arrays of P's tiled forward in type T (hook: a one-problem table to build with).
+// Builds the arrays of P's tiled forward in type T for its first n.tiles tiles (hook: a
+// one-problem table to build with).
 template <typename T>
-int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, DevBuf<DevProb>& hook, bool& changed) {
-    if (V.q.p) return DDMGNN_OK;
+int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, const TileCount& n, DevBuf<DevProb>& hook, bool& changed) {
+    if (V.mem.p && V.n.tiles >= n.tiles) return DDMGNN_OK;
     hipStream_t s = P->ctx->stream;
-    list_tiles(P);
-    const int64_t sk = P->hs.sk, nt = (int64_t)P->vt_tiles.size(), rows = P->vt_rows + VT_ROWS;
+    const int64_t nt = n.tiles, rows = n.rows + VT_ROWS;
     if (rows * VT_TILE >= INT32_MAX || nt * VT_TILE >= INT32_MAX)
         return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
-    const size_t er = (size_t)rows * VT_TILE, pad = (size_t)VT_ROWS * VT_TILE, qn = (size_t)(nt * VT_TILE + 1) * 2 * D;
     if (int rc = prepare_tile_nodes(P, hook)) return rc;
     constexpr bool f64 = sizeof(T) == 8;
-    HIP_TRY(V.rec.alloc(er));
-    HIP_TRY(hipMemsetAsync(V.rec.p + er - pad, 0, pad * sizeof(VtRec<T>), s));
-    if (!f64) HIP_TRY(V.info.alloc((size_t)nt * VT_TILE * 4));
-    HIP_TRY(V.h.alloc((size_t)nt * 64 * 4));
-    DevBuf<T> q;  // moved in last: a failed build is retried whole
-    HIP_TRY(q.alloc(2 * qn));
-    const T inf = std::numeric_limits<T>::infinity();
-    HIP_TRY(launch_vt_fill(q.p + qn - 2 * D, 2 * D, -inf, s));
-    HIP_TRY(launch_vt_fill(q.p + 2 * qn - 2 * D, 2 * D, -inf, s));
-    HIP_TRY(launch_vt_edges(hook.p, P->vt_info.p, (int)nt, P->vt_node.p, P->vt_pos.p,
-                            f64 ? nullptr : reinterpret_cast<VtRec<float>*>(V.rec.p),
-                            f64 ? reinterpret_cast<VtRec<double>*>(V.rec.p) : nullptr, s));
-    std::swap(V.q.p, q.p);
-    std::swap(V.q.n, q.n);
-    P->device_bytes += tile_bytes(sk, nt, P->vt_rows, f64);
+    const size_t er = (size_t)rows * VT_TILE, pad = (size_t)VT_ROWS * VT_TILE, qn = (size_t)(nt * VT_TILE + 1) * 2 * D;
+    VtRec<T>* rec = nullptr;
+    VtVecs<T> v{};
+    auto carve = [&](Carver c) {
+        rec = c.take<VtRec<T>>(er);
+        v.info = f64 ? nullptr : c.take<T>((size_t)nt * VT_TILE * 4);
+        v.h = c.take<T>((size_t)nt * 64 * 4);
+        for (T*& q : v.q) q = c.take<T>(qn);
+        v.rec = rec;
+        return c.used;
+    };
+    if (V.mem.p) P->device_bytes -= tile_bytes(V.n, f64);
+    V.v = VtVecs<T>{};
+    V.n = TileCount{};
     changed = true;
+    DevBuf<char> mem;  // moved in last: a failed build is retried whole
+    V.mem.reset();
+    HIP_TRY(mem.alloc(carve(Carver{nullptr})));
+    carve(Carver{mem.p});
+    HIP_TRY(hipMemsetAsync(rec + er - pad, 0, pad * sizeof(VtRec<T>), s));
+    const T inf = std::numeric_limits<T>::infinity();
+    for (T* q : v.q) HIP_TRY(launch_vt_fill(q + qn - 2 * D, 2 * D, -inf, s));
+    HIP_TRY(launch_vt_edges(hook.p, P->vt_info, (int)nt, P->vt_node, P->vt_pos,
+                            f64 ? nullptr : reinterpret_cast<VtRec<float>*>(rec),
+                            f64 ? reinterpret_cast<VtRec<double>*>(rec) : nullptr, s));
+    std::swap(V.mem.p, mem.p);
+    std::swap(V.mem.n, mem.n);
+    V.v = v;
+    V.n = n;
+    P->device_bytes += tile_bytes(n, f64);
     return DDMGNN_OK;
 }
 
@@ -432,7 +472,7 @@ int prepare_train(ddmgnn_problem* P) {
         out_rows[t] = make_int2((int)rows, deg);
         rows += deg;
     }
-    if ((rows + VT_ROWS) * VT_TILE >= INT32_MAX || (P->vt_rows + VT_ROWS) * VT_TILE >= INT32_MAX)
+    if ((rows + VT_ROWS) * VT_TILE >= INT32_MAX || (P->vt_all.rows + VT_ROWS) * VT_TILE >= INT32_MAX)
         return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
     if (int rc = solo_batch(P)) return rc;
     if (int rc = prepare_tile_nodes(P, P->solo->hook)) return rc;
@@ -447,13 +487,13 @@ int prepare_train(ddmgnn_problem* P) {
     HIP_TRY(P->tr_map.upload(map.data(), map.size(), s));
     HIP_TRY(P->tr_ent.upload(ent.data(), ent.size(), s));
     HIP_TRY(P->tr_orows.upload(out_rows.data(), nt, s));
-    const size_t ni = (size_t)(P->vt_rows + VT_ROWS) * VT_TILE, no = (size_t)(rows + VT_ROWS) * VT_TILE;
+    const size_t ni = (size_t)(P->vt_all.rows + VT_ROWS) * VT_TILE, no = (size_t)(rows + VT_ROWS) * VT_TILE;
     HIP_TRY(P->tr_rin.alloc(ni));
     HIP_TRY(P->tr_rout.alloc(no));
     // the rows past the last tile are read, not looked at
     HIP_TRY(hipMemsetAsync(P->tr_rin.p, 0, ni * sizeof(TrainEdge), s));
     HIP_TRY(hipMemsetAsync(P->tr_rout.p, 0, no * sizeof(TrainEdge), s));
-    const TrainEdgeArgs ea{P->vt_info.p, P->tr_orows.p, (int)nt, P->vt_node.p, P->vt_pos.p, P->edge_ptr.p,
+    const TrainEdgeArgs ea{P->vt_info, P->tr_orows.p, (int)nt, P->vt_node, P->vt_pos, P->edge_ptr.p,
                            P->edge_src.p, P->edge_nd.p, oe_ptr_d.p, oe_edge_d.p, oe_recv_d.p, P->xy64.p,
                            P->tr_rin.p, P->tr_rout.p};
     HIP_TRY(launch_train_edges(ea, s));
@@ -467,6 +507,10 @@ int prepare_train(ddmgnn_problem* P) {
     return DDMGNN_OK;
 }
 
+int32_t sub_tiles(const ddmgnn_problem* P, int32_t i) {
+    return (int32_t)((P->hs.sub_ptr[i + 1] - P->hs.sub_ptr[i] + VT_TILE - 1) / VT_TILE);
+}
+
 // Tile list of a batch: the tiles of the sub-meshes `take` accepts, by problem and sub-mesh.
 template <class F>
 int upload_tiles(Batch& B, DevBuf<int4>& buf, int& n, F take) {
@@ -475,8 +519,8 @@ int upload_tiles(Batch& B, DevBuf<int4>& buf, int& n, F take) {
     for (size_t p = 0; p < B.probs.size(); ++p) {
         const ddmgnn_problem* P = B.probs[p];
         for (int32_t i = 0; i < P->hs.K; ++i) {
-            if (!take(P, i)) continue;
-            for (int32_t t = P->vt_first[i]; t < P->vt_first[i + 1]; ++t)
+            if (!take(P, i) || P->hs.sub_ptr[i + 1] - P->hs.sub_ptr[i] > kMaxSubNodes) continue;
+            for (int32_t t = P->vt_first[i], e = t + sub_tiles(P, i); t < e; ++t)
                 v.push_back(make_int4((int)p, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
         }
     }
@@ -527,7 +571,9 @@ int prepare_dss(Batch& B, int precision, bool& changed) {
     if (runs_tiled(d, valu_prec, bf16 ? B.vt_rest : B.vt_valu)) {
         for (ddmgnn_problem* P : B.probs) {
             if (bf16 && !any_valu_bf16(P)) continue;
-            const int rc = f64 ? prepare_tiles(P, P->vt64, B.hook, changed) : prepare_tiles(P, P->vt32, B.hook, changed);
+            list_tiles(P);
+            const TileCount& n = bf16 ? P->vt_rest : P->vt_all;
+            const int rc = f64 ? prepare_tiles(P, P->vt64, n, B.hook, changed) : prepare_tiles(P, P->vt32, n, B.hook, changed);
             if (rc) return rc;
         }
         if (bf16)
@@ -1107,20 +1153,24 @@ size_t lu_bytes(const HostSetup& hs) {
     return b;
 }
 
-// Bytes of the tiled DSS forward's arrays of a problem in one precision (`tiles` tiles,
-// `rows` edge rows).
-size_t tile_bytes(int64_t sk, int64_t tiles, int64_t rows, bool f64) {
+// Bytes of the nodes of a problem's tiles, and of the tiled forward's arrays in one precision.
+size_t tile_node_bytes(int64_t tiles, int64_t sk, int32_t K) {
+    return (size_t)tiles * (sizeof(VtTile) + VT_TILE * sizeof(int2)) + 4 * ((size_t)sk + K);
+}
+size_t tile_bytes(const TileCount& n, bool f64) {
     const size_t e = f64 ? 8 : 4;
-    return (size_t)tiles * (16 + VT_TILE * 8 + (f64 ? 0 : 16 * VT_TILE) + 256 * e) + (size_t)sk * 4 +
-           (size_t)(rows + VT_ROWS) * VT_TILE * 2 * e + (size_t)(tiles * VT_TILE + 1) * 4 * D * e;
+    return (size_t)n.tiles * ((f64 ? 0 : 16 * VT_TILE) + 256 * e) + (size_t)(n.rows + VT_ROWS) * VT_TILE * 2 * e +
+           (size_t)(n.tiles * VT_TILE + 1) * 4 * D * e;
 }
 
 // The same for a problem that has not listed its tiles: a tile has at most 15 empty
 // lanes per sub-mesh, and its edge rows at most one more than its nodes' largest
 // in-degree, which its nodes (by decreasing in-degree) have but for the last few.
 size_t tile_bytes_bound(const HostSetup& hs, bool f64) {
-    const int64_t tiles = hs.sk / VT_TILE + hs.K;
-    return tile_bytes(hs.sk, tiles, hs.n_edges / VT_TILE + 3 * tiles, f64);
+    TileCount n;
+    n.tiles = hs.sk / VT_TILE + hs.K;
+    n.rows = hs.n_edges / VT_TILE + 3 * n.tiles;
+    return tile_node_bytes(n.tiles, hs.sk, hs.K) + tile_bytes(n, f64);
 }
 
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t ne) {
@@ -1784,7 +1834,7 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
         HIP_TRY(launch_dss_mfma(a, 1, shmem, MFMA_BLOCK, s, true));
     } else if (runs_tiled(M.d, vprec, precision == DDMGNN_BF16 ? B.vt_rest : B.vt_valu)) {  // as prepare_dss
         std::vector<int4> tl;
-        for (int32_t t = P->vt_first[sub]; t < P->vt_first[sub + 1]; ++t)
+        for (int32_t t = P->vt_first[sub], e = t + sub_tiles(P, sub); t < e; ++t)
             tl.push_back(make_int4(0, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
         if (int rc = upload_list(P->one_tiles, tl, s)) return rc;
         if (vprec == DDMGNN_FP64)
@@ -2068,7 +2118,7 @@ int ddmgnn_train_grad(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_model_des
     std::vector<int32_t> chunk{0};  // first tile of each chunk, and the end
     int64_t most = 0;
     for (int32_t i = 0; i < n; ++i) {
-        const int32_t t0 = P->vt_first[subs[i]], t1 = P->vt_first[subs[i] + 1];
+        const int32_t t0 = P->vt_first[subs[i]], t1 = t0 + sub_tiles(P, subs[i]);
         int64_t first = (int64_t)items.size() / 2;
         if (first + (t1 - t0) >= INT32_MAX / 2) return fail(DDMGNN_E_INVALID, "too many samples");
         if (first > chunk.back() && first - chunk.back() + (t1 - t0) > TRAIN_TILES) chunk.push_back((int32_t)first);
@@ -2107,9 +2157,9 @@ int ddmgnn_train_grad(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_model_des
     a.kbar = kb;
     a.ks = ks;
     a.alpha = (float)md->alpha;
-    a.info = P->vt_info.p;
-    a.node = P->vt_node.p;
-    a.pos = P->vt_pos.p;
+    a.info = P->vt_info;
+    a.node = P->vt_node;
+    a.pos = P->vt_pos;
     a.rin = P->tr_rin.p;
     a.rout = P->tr_rout.p;
     a.lm_ptr = P->lm_ptr.p;

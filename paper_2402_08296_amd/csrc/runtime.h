@@ -81,11 +81,18 @@ struct ModelDev {
     DevBuf<float> vt32;
 };
 
-// Device arrays of a problem's tiled DSS forward in one precision.
+// Tiles of 16 nodes, and their edge rows.
+struct TileCount {
+    int64_t tiles = 0, rows = 0;
+};
+
+// Device arrays of a problem's tiled DSS forward in one precision, for its first n.tiles
+// tiles, in one allocation.
 template <typename T>
 struct VtBufs {
-    DevBuf<VtRec<T>> rec;
-    DevBuf<T> info, h, q;
+    DevBuf<char> mem;
+    VtVecs<T> v{};
+    TileCount n;
 };
 
 struct Batch;
@@ -99,9 +106,10 @@ using BatchPtr = std::unique_ptr<Batch, BatchDeleter>;
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t n_edges);
 // Bytes counted for the exact local solves.
 size_t lu_bytes(const HostSetup& hs);
-// Bytes of the tiled DSS forward's arrays in one precision: exactly, and an estimate
-// before the tiles are listed.
-size_t tile_bytes(int64_t sk, int64_t tiles, int64_t rows, bool f64);
+// Bytes of the nodes of a problem's tiles, of the tiled forward's arrays in one precision,
+// and an estimate of both before the tiles are listed.
+size_t tile_node_bytes(int64_t tiles, int64_t sk, int32_t K);
+size_t tile_bytes(const TileCount& n, bool f64);
 size_t tile_bytes_bound(const HostSetup& hs, bool f64);
 
 // Creates a problem from a validated descriptor and its host setup (moved in).
@@ -205,12 +213,14 @@ struct ddmgnn_problem {
     ddmgnn::DevBuf<double> fwd_in, fwd_out;
     ddmgnn::DevBuf<int2> one_work;
     // tiles of the FP64 and FP32 DSS forward (built at the first use of either)
-    std::vector<ddmgnn::VtTile> vt_tiles;  // host: per tile
-    std::vector<int32_t> vt_first;         // host: [K + 1] tiles of each sub-mesh
-    int64_t vt_rows = 0;                   // edge rows of all tiles
-    ddmgnn::DevBuf<ddmgnn::VtTile> vt_info;
-    ddmgnn::DevBuf<int32_t> vt_ptr, vt_pos;
-    ddmgnn::DevBuf<int2> vt_node;
+    std::vector<ddmgnn::VtTile> vt_tiles;  // host: per tile, those of the sub-meshes that BF16 leaves first
+    std::vector<int32_t> vt_first;         // host: [K] first tile of each sub-mesh
+    ddmgnn::TileCount vt_rest, vt_all;     // those, and all
+    ddmgnn::DevBuf<char> vt_mem;           // the following, in one allocation
+    ddmgnn::VtTile* vt_info = nullptr;
+    int32_t* vt_first_dev = nullptr;
+    int32_t* vt_pos = nullptr;
+    int2* vt_node = nullptr;
     ddmgnn::VtBufs<double> vt64;
     ddmgnn::VtBufs<float> vt32;
     ddmgnn::DevBuf<int4> one_tiles;        // tiles of the one-sub-mesh forward entry

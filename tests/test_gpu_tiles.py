@@ -127,3 +127,47 @@ def test_overflow_is_not_masked(ctx):
         print(f"[gpu] overflow {prec}: {int(torch.isposinf(out).sum())} of {out.numel()} infinite", flush=True)
         assert torch.isposinf(out).all()
         assert prob.solve(u, dg.default_opts(precision=prec, max_it=5), check=False).status == -7
+
+
+def _runs(ctx, sizes, theta):
+    """A problem whose sub-meshes are consecutive runs of the given sizes of a 9k-node mesh's
+    nodes (free nodes first), and one of the rest."""
+    p = W.make_problem(16, 9000, 4, 0.2)
+    hp = oracle_problem(p)
+    nodes = np.argsort(p.mesh.dirichlet, kind="stable")
+    sp = np.concatenate([[0], np.cumsum(sizes), [p.n]])
+    for a, b in zip(sp[:-1], sp[1:]):
+        nodes[a:b].sort()
+    w = np.where(p.mesh.dirichlet[nodes], 0.0, 1.0)
+    hp = dg.HostProblem(hp.xy, hp.tri, hp.dirichlet, hp.rowptr, hp.col, hp.val, hp.b, hp.u0, sp, nodes, w)
+    return p, hp, dg.Problem(ctx, hp, dg.Model(ctx, theta))
+
+
+@pytest.mark.parametrize("first", ["bf16", "fp32"])
+def test_bf16_remainder_runs_tiled(ctx, first):
+    """A BF16 problem with one sub-mesh that fits 2048 nodes but not the matrix-core kernel's
+    LDS: the FP32 forward in tiles runs that one (the bits of an FP32 call), whichever call
+    comes first, and BF16 alone keeps tile arrays for it only."""
+    p, hp, prob = _runs(ctx, [300, 2048, 700, 1500], XAVIER)
+    c = torch.tensor(np.random.default_rng(2).standard_normal(hp.sub_nodes.size) * 0.02, device="cuda")
+    out = {q: torch.empty_like(c) for q in ("bf16", "fp32")}
+    base = prob.device_bytes()
+    prob.dss_forward(c, out[first], first)
+    grown = prob.device_bytes() - base
+    other = "fp32" if first == "bf16" else "bf16"
+    prob.dss_forward(c, out[other], other)
+    again = torch.empty_like(c)
+    prob.dss_forward(c, again, first)
+    assert torch.equal(again, out[first])
+    st = prob.solve(torch.empty(p.n, dtype=torch.float64, device="cuda"), dg.default_opts(precision="bf16", max_it=2), check=False)
+    same = [bool(torch.equal(out["bf16"][a:b], out["fp32"][a:b])) for a, b in zip(hp.sub_ptr[:-1], hp.sub_ptr[1:])]
+    print(f"[gpu] {first} first: {grown} bytes, kernel {st.dss_kernel}, equal to FP32 {same}", flush=True)
+    assert st.dss_kernel == 4 and same[1] and not same[0] and not same[2]
+    for i in (0, 1):
+        one = torch.empty(int(hp.sub_ptr[i + 1] - hp.sub_ptr[i]), dtype=torch.float64, device="cuda")
+        prob.dss_forward_sub(i, c[hp.sub_ptr[i]:hp.sub_ptr[i + 1]].contiguous(), one, "bf16")
+        assert torch.equal(one, out["bf16"][hp.sub_ptr[i]:hp.sub_ptr[i + 1]])
+    rest = sum(int(hp.sub_ptr[i + 1] - hp.sub_ptr[i]) for i in range(hp.K) if same[i] and hp.sub_ptr[i + 1] - hp.sub_ptr[i] <= 2048)
+    small = sum(int(b - a) for a, b in zip(hp.sub_ptr[:-1], hp.sub_ptr[1:]) if b - a <= 2048)
+    # 16 + 8 + 4 bytes per slot for the tiles' nodes, and about 300 of FP32 arrays where they are kept
+    assert grown <= 20 * hp.sub_nodes.size + 400 * (rest if first == "bf16" else small) + 8192
