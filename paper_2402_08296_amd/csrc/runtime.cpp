@@ -32,19 +32,21 @@ struct Batch {
     DevBuf<DevProb> tab;               // table of the solve
     DevBuf<DevProb> hook;              // one-problem table of the entry points that redirect vectors
     // DSS work lists, (problem, sub-mesh) by decreasing sub-mesh size:
-    // all sub-meshes; those of problems that fit the MFMA kernel; the others.
+    // those that fit the MFMA kernel; the others; of all, those of at most kMaxSubNodes.
     // (the VALU lists hold sub-meshes of at most kMaxSubNodes nodes; work_big the larger ones,
     // which run the global-memory form of the VALU kernel in every precision)
-    DevBuf<int2> work_all, work_mfma, work_rest, work_valu, work_big;
-    int n_all = 0, n_mfma = 0, n_rest = 0, n_valu = 0, n_big = 0;
+    DevBuf<int2> work_mfma, work_rest, work_valu, work_big;
+    std::vector<int2> all;             // host: every sub-mesh
+    int n_mfma = 0, n_rest = 0, n_valu = 0, n_big = 0;
     // the MFMA list split by workgroup size: sub-meshes that run two per compute
     // unit in MFMA_SMALL_BLOCK-thread workgroups, and the rest; dynamic LDS of each launch
     DevBuf<int2> work_mfma_small;
     int n_mfma_small = 0;
     size_t lds_mfma = 0, lds_mfma_small = 0;
     int max_k_all = 0, max_k_rest = 0, max_k_valu = 0;
-    // units of work_valu's and work_big's sub-meshes in the exact local solves, and the
-    // sub-meshes whose inverses are held in tiles
+    // exact local solves (built at the first one): units of work_valu's and work_big's
+    // sub-meshes, and the sub-meshes whose inverses are held in tiles
+    bool lu_ready = false;
     DevBuf<int4> lu_small, lu_big;
     DevBuf<int2> lu_subs;
     int n_lu_small = 0, n_lu_big = 0, n_lu_subs = 0;
@@ -242,6 +244,42 @@ int prepare_lu(ddmgnn_problem* P) {
         return rc;
     }
     P->device_bytes += lu_bytes(hs);
+    return DDMGNN_OK;
+}
+
+// The inverses of a batch's problems and the lists of its launches.
+int prepare_exact(Batch& B, bool& changed) {
+    for (ddmgnn_problem* P : B.probs) {
+        changed = changed || !P->lu_inv.p;
+        if (int rc = prepare_lu(P)) return rc;
+    }
+    if (B.lu_ready) return DDMGNN_OK;
+    std::vector<int2> subs;
+    std::vector<int4> small, big;
+    std::vector<int> max_k(B.probs.size(), 0);
+    auto size = [&](const int2& w) {
+        const auto& sp = B.probs[w.x]->hs.sub_ptr;
+        return (int)(sp[w.y + 1] - sp[w.y]);
+    };
+    for (const int2& w : B.all) max_k[w.x] = std::max(max_k[w.x], size(w));
+    static_assert(LU_LDS_K == kMaxSubNodes, "work_valu holds the sub-meshes of the exact solves' LDS form");
+    for (const int2& w : B.all) {
+        const int k = size(w);
+        if (lu_dense(k, max_k[w.x])) {
+            small.push_back(make_int4(w.x, w.y, -1, 0));
+            continue;
+        }
+        subs.push_back(w);
+        for (int u = 0; u < lu_units(k); ++u) (k > LU_LDS_K ? big : small).push_back(make_int4(w.x, w.y, u, 0));
+    }
+    hipStream_t s = B.ctx->stream;
+    if (int rc = upload_list(B.lu_subs, subs, s)) return rc;
+    if (int rc = upload_list(B.lu_small, small, s)) return rc;
+    if (int rc = upload_list(B.lu_big, big, s)) return rc;
+    B.n_lu_subs = (int)subs.size();
+    B.n_lu_small = (int)small.size();
+    B.n_lu_big = (int)big.size();
+    B.lu_ready = true;
     return DDMGNN_OK;
 }
 
@@ -906,14 +944,10 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     };
     std::vector<W> all;
     std::vector<int2> vec, rows;
-    std::vector<int> max_k((size_t)n, 0);  // largest sub-mesh of each problem
     for (int i = 0; i < n; ++i) {
         const ddmgnn_problem* P = probs[i];
         const auto& sp = P->hs.sub_ptr;
-        for (int j = 0; j < P->hs.K; ++j) {
-            all.push_back({(int)(sp[j + 1] - sp[j]), i, j});
-            max_k[i] = std::max(max_k[i], all.back().k);
-        }
+        for (int j = 0; j < P->hs.K; ++j) all.push_back({(int)(sp[j + 1] - sp[j]), i, j});
         const int nb = problem_vec_blocks(P);
         for (int b = 0; b < nb; ++b) vec.push_back(make_int2(i, b));
         for (int r = 0; r < P->hs.K; ++r) rows.push_back(make_int2(i, r));
@@ -924,20 +958,11 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         if (a.p != b.p) return a.p < b.p;
         return a.sub < b.sub;
     });
-    std::vector<int2> wa, wm, wms, wr, wv, wb, ls;
-    std::vector<int4> lus, lub;
+    std::vector<int2> wm, wms, wr, wv, wb;
     size_t lds_sb = 0, lds_db = 0, lds_small_sb = 0, lds_small_db = 0;
     for (const W& w : all) {
-        wa.push_back(make_int2(w.p, w.sub));
+        B->all.push_back(make_int2(w.p, w.sub));
         B->max_k_all = std::max(B->max_k_all, w.k);
-        static_assert(LU_LDS_K == kMaxSubNodes, "work_valu holds the sub-meshes of the exact solves' LDS form");
-        if (lu_dense(w.k, max_k[w.p])) {
-            lus.push_back(make_int4(w.p, w.sub, -1, 0));
-        } else {
-            ls.push_back(make_int2(w.p, w.sub));
-            for (int u = 0; u < lu_units(w.k); ++u)
-                (w.k > kMaxSubNodes ? lub : lus).push_back(make_int4(w.p, w.sub, u, 0));
-        }
         const ddmgnn_problem* Q = probs[w.p];
         if (w.k > kMaxSubNodes) {
             wb.push_back(make_int2(w.p, w.sub));
@@ -971,13 +996,6 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     B->lds_mfma = std::max(lds_sb, lds_db);
     B->lds_mfma_small = std::max(lds_small_sb, lds_small_db);
     hipStream_t s = ctx->stream;
-    if (int rc = upload_list(B->work_all, wa, s)) return rc;
-    if (int rc = upload_list(B->lu_subs, ls, s)) return rc;
-    B->n_lu_subs = (int)ls.size();
-    if (int rc = upload_list(B->lu_small, lus, s)) return rc;
-    if (int rc = upload_list(B->lu_big, lub, s)) return rc;
-    B->n_lu_small = (int)lus.size();
-    B->n_lu_big = (int)lub.size();
     if (int rc = upload_list(B->work_mfma, wm, s)) return rc;
     if (int rc = upload_list(B->work_mfma_small, wms, s)) return rc;
     if (int rc = upload_list(B->work_rest, wr, s)) return rc;
@@ -985,7 +1003,6 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     if (int rc = upload_list(B->work_big, wb, s)) return rc;
     if (int rc = upload_list(B->vec_blk, vec, s)) return rc;
     if (int rc = upload_list(B->coarse_rows, rows, s)) return rc;
-    B->n_all = (int)wa.size();
     B->n_mfma = (int)wm.size();
     B->n_mfma_small = (int)wms.size();
     B->n_rest = (int)wr.size();
@@ -1005,10 +1022,7 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
 int batch_begin(Batch& B, const ddmgnn_solve_opts& o, const std::vector<uint8_t>* init) {
     bool changed = false;
     if (o.krylov != DDMGNN_CG && o.local_solver == DDMGNN_LOCAL_LU) {
-        for (ddmgnn_problem* P : B.probs) {
-            changed = changed || !P->lu_inv.p;
-            if (int rc = prepare_lu(P)) return rc;
-        }
+        if (int rc = prepare_exact(B, changed)) return rc;
     } else if (o.krylov != DDMGNN_CG) {
         if (int rc = prepare_dss(B, o.precision, changed)) return rc;
     }
@@ -1864,7 +1878,7 @@ int ddmgnn_time_apply_stages(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_so
     Batch& B = *P->solo;
     bool changed = false;
     if (opts->local_solver == DDMGNN_LOCAL_LU) {
-        if (int rc = prepare_lu(P)) return rc;
+        if (int rc = prepare_exact(B, changed)) return rc;
     } else if (int rc = prepare_dss(B, opts->precision, changed)) {
         return rc;
     }
@@ -1932,7 +1946,7 @@ int ddmgnn_precond_apply(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_solve_
     Batch& B = *P->solo;
     bool changed = false;
     if (opts->local_solver == DDMGNN_LOCAL_LU) {
-        if (int rc = prepare_lu(P)) return rc;
+        if (int rc = prepare_exact(B, changed)) return rc;
     } else if (int rc = prepare_dss(B, opts->precision, changed)) {
         return rc;
     }
