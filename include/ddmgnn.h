@@ -177,7 +177,8 @@ typedef struct {
     int32_t coarse;      /* 1: add the coarse correction (step 1), 0: one-level */
     int32_t check_every; /* iterations between host checks of the converged flag */
     int32_t profile;     /* 1: time every stage with HIP events on the context stream */
-    int32_t graph;       /* 1: replay chunks of check_every iterations as one captured HIP graph
+    int32_t graph;       /* 1: replay captured HIP graphs, of check_every iterations or, where an
+                          * iteration is many launches and solves are short, of four
                           * (ignored when profile = 1) */
     int32_t local_solver;/* DDMGNN_LOCAL_GNN, or DDMGNN_LOCAL_LU: exact local solves with the
                           * inverses of R_i A R_i^T (FP64, one triangle in 64 x 64 tiles; counted

@@ -65,10 +65,20 @@ struct Batch {
     int n_sub_list = 0;
     DevBuf<KState> st_gather;
     KState* host_st = nullptr;         // pinned, one per problem
-    hipGraphExec_t graph = nullptr;    // captured chunk of iterations
-    uint64_t graph_key = 0;
+    // captured chunks of iterations: of check_every of them, and a short one (brief_chunk)
+    struct Graph {
+        hipGraphExec_t exec = nullptr;
+        uint64_t key = 0;
+        void reset() {
+            if (exec) (void)hipGraphExecDestroy(exec);
+            exec = nullptr;
+            key = 0;
+        }
+    } graph, brief;
+    int last_it = 0;                   // iterations of the last solve
     ~Batch() {
-        if (graph) (void)hipGraphExecDestroy(graph);
+        graph.reset();
+        brief.reset();
         if (host_st) (void)hipHostFree(host_st);
     }
 };
@@ -756,15 +766,30 @@ uint64_t graph_key(const ddmgnn_solve_opts& o, int count) {
            (uint64_t)(uint32_t)count;
 }
 
-// Captures `count` iterations of the batch into B.graph (on the context's own
+// Iterations of a solve's captured graph. A tiled forward is a launch per block, so an iteration
+// after the last one, in which every kernel returns at once, costs some 50 us, and capturing
+// one 40. A solve whose batch's last one took at most two graphs of four (or the first)
+// therefore replays such a graph, its flags read after 4, 8, 16 and then every check_every
+// of them; a longer one's successor has the whole chunk as one graph, which saves 1%. FP32
+// solves of two iterations, with chunks of 16 and now: 5k nodes 1,200 and 530 us, the first on
+// its problem 2,110 and 910 (one workgroup per sub-mesh: 1,170 and 1,480); 300 nodes 1,175 and
+// 510, 2,050 and 850 (845 and 1,115).
+constexpr int BRIEF_CHUNK = 4;
+int brief_chunk(const Batch& B, const ddmgnn_solve_opts& o) {
+    const int check = std::max(1, o.check_every);
+    if (o.krylov == DDMGNN_CG || o.local_solver == DDMGNN_LOCAL_LU || B.last_it > 2 * BRIEF_CHUNK) return check;
+    const bool bf16 = o.precision == DDMGNN_BF16;
+    const bool tiled = (bf16 ? B.n_rest : B.n_valu) > 0 &&
+                       runs_tiled(B.model->d, bf16 ? DDMGNN_FP32 : o.precision, bf16 ? B.vt_rest : B.vt_valu);
+    return tiled ? std::min(check, BRIEF_CHUNK) : check;
+}
+
+// Captures `count` iterations of the batch into G, unless it holds them (on the context's own
 // stream: the caller's stream may be the null stream, which cannot be captured).
-int capture_chunk(Batch& B, const ddmgnn_solve_opts& o, int count) {
+int capture_chunk(Batch& B, Batch::Graph& G, const ddmgnn_solve_opts& o, int count) {
     ddmgnn_ctx* ctx = B.ctx;
-    if (B.graph) {
-        (void)hipGraphExecDestroy(B.graph);
-        B.graph = nullptr;
-        B.graph_key = 0;
-    }
+    if (G.exec && G.key == graph_key(o, count)) return DDMGNN_OK;
+    G.reset();
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeRelaxed));
     ctx->launch = ctx->cap;
@@ -784,10 +809,11 @@ int capture_chunk(Batch& B, const ddmgnn_solve_opts& o, int count) {
         HIP_TRY(ce);
     }
     HIP_TRY(hipGetLastError());
-    hipError_t ie = hipGraphInstantiate(&B.graph, g, nullptr, nullptr, 0);
+    hipError_t ie = hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
+    if (ie != hipSuccess) G.exec = nullptr;
     HIP_TRY(ie);
-    B.graph_key = graph_key(o, count);
+    G.key = graph_key(o, count);
     return DDMGNN_OK;
 }
 
@@ -846,6 +872,7 @@ int solve_batch(ddmgnn_ctx* ctx, Batch& B, const ddmgnn_solve_opts& o, double* c
     // is replayed as a whole (problems that finish inside it idle).
     const int check = std::max(1, o.check_every);
     const bool use_graph = o.graph && !o.profile;
+    const int brief = brief_chunk(B, o);
     if (o.profile) {
         guard.v.resize((size_t)check * 5);
         for (auto& e : guard.v) HIP_TRY(hipEventCreate(&e));
@@ -854,11 +881,15 @@ int solve_batch(ddmgnn_ctx* ctx, Batch& B, const ddmgnn_solve_opts& o, double* c
     int n_dss = 0, it = 0, it_seen = 0;
     bool done = o.max_it <= 0;
     while (!done) {
-        const int n_chunk = use_graph ? check : std::min(check, o.max_it - it);
-        if (use_graph) {
-            if (!B.graph || B.graph_key != graph_key(o, n_chunk))
-                if (int rc = capture_chunk(B, o, n_chunk)) return rc;
-            HIP_TRY(hipGraphLaunch(B.graph, s));
+        int n_chunk = use_graph ? check : std::min(check, o.max_it - it);
+        if (use_graph && brief < check) {
+            if (int rc = capture_chunk(B, B.brief, o, brief)) return rc;
+            const int replays = std::max(1, std::min(it, check) / brief);  // up to 4, 8, 16, ... iterations
+            for (int q = 0; q < replays; ++q) HIP_TRY(hipGraphLaunch(B.brief.exec, s));
+            n_chunk = replays * brief;
+        } else if (use_graph) {
+            if (int rc = capture_chunk(B, B.graph, o, check)) return rc;
+            HIP_TRY(hipGraphLaunch(B.graph.exec, s));
         } else {
             for (int c = 0; c < n_chunk; ++c)
                 if (int rc = enqueue_iteration(B, o, o.profile ? &guard.v[(size_t)c * 5] : nullptr, false)) return rc;
@@ -891,6 +922,7 @@ int solve_batch(ddmgnn_ctx* ctx, Batch& B, const ddmgnn_solve_opts& o, double* c
         }
         it_seen = max_it_done;
     }
+    B.last_it = it_seen;
     HIP_TRY(hipEventRecord(ev1, s));
     if (int rc = batch_true_residual(B, nullptr)) return rc;
     for (int i = 0; i < nb; ++i)
@@ -1028,10 +1060,9 @@ int batch_begin(Batch& B, const ddmgnn_solve_opts& o, const std::vector<uint8_t>
     }
     if (o.krylov == DDMGNN_FGMRES)
         if (int rc = prepare_fgmres(B, o.restart, changed)) return rc;
-    if (changed && B.graph) {  // captured launches point at moved buffers
-        (void)hipGraphExecDestroy(B.graph);
-        B.graph = nullptr;
-        B.graph_key = 0;
+    if (changed) {  // captured launches point at moved buffers
+        B.graph.reset();
+        B.brief.reset();
     }
     if (int rc = upload_table(B)) return rc;
     if (init) {
@@ -1044,9 +1075,8 @@ int batch_begin(Batch& B, const ddmgnn_solve_opts& o, const std::vector<uint8_t>
 
 int batch_iterate(Batch& B, const ddmgnn_solve_opts& o, int count, bool use_graph) {
     if (use_graph) {
-        if (!B.graph || B.graph_key != graph_key(o, count))
-            if (int rc = capture_chunk(B, o, count)) return rc;
-        HIP_TRY(hipGraphLaunch(B.graph, B.ctx->stream));
+        if (int rc = capture_chunk(B, B.graph, o, count)) return rc;
+        HIP_TRY(hipGraphLaunch(B.graph.exec, B.ctx->stream));
         return DDMGNN_OK;
     }
     for (int c = 0; c < count; ++c)

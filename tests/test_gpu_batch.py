@@ -306,3 +306,21 @@ def test_server_admission_failure_beside_running_chunks(ctx, mix):
         assert rc == 0 and st.converged and st.iterations == solo[i][1]
         assert np.array_equal(u, solo[i][0])
     srv.close()
+
+
+@pytest.mark.parametrize("check_every", [1, 3, 4, 6, 16])
+def test_short_and_long_graphs_agree(ctx, mix, check_every):
+    """A solve starts with replays of a four-iteration graph and has the whole chunk as one
+    graph once a solve of its problem got past eight iterations: short, long and short again,
+    with a max_it inside a chunk, the iterates are those of eager launches."""
+    print(f"[gpu] captured chunks, flags read every {check_every}", flush=True)
+    model = dg.Model(ctx, SMOOTHER)
+    p, hp = mix[0]
+    prob = dg.Problem(ctx, hp, model)
+    eager = dg.Problem(ctx, hp, model)
+    u, v = (torch.empty(p.n, dtype=torch.float64, device="cuda") for _ in range(2))
+    for max_it in (2, 5, 3000, 3000, 7, 3000):
+        o = dict(precision="fp32", rtol=1e-6, max_it=max_it, check_every=check_every)
+        a = prob.solve(u, dg.default_opts(graph=1, **o), check=False)
+        b = eager.solve(v, dg.default_opts(graph=0, **o), check=False)
+        assert a.iterations == b.iterations and a.status == b.status and torch.equal(u, v), max_it
