@@ -350,7 +350,9 @@ int ddmgnn_train_rhs(ddmgnn_ctx* ctx, ddmgnn_problem* prob, const double* u, flo
  * residuals) and |grad|_2. The first call builds the local matrices and edge
  * records on the device. Samples run in chunks of up to 32768 tiles of 16 nodes
  * (about 500 samples of 1000 nodes) that share one scratch region of about
- * 4 kbar kilobytes per tile. The
+ * 4 kbar kilobytes per tile, kept with the problem and counted in
+ * ddmgnn_problem_device_bytes (smaller chunks where it cannot be allocated; the
+ * gradient then differs by the rounding of another order of sums). The
  * problem's training buffers serve one call at a time: calls on one problem from
  * several threads must be serialised. E_NONFINITE when the loss or the gradient
  * overflows. */

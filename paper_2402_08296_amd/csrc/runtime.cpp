@@ -2157,44 +2157,58 @@ int ddmgnn_train_grad(ddmgnn_ctx* ctx, ddmgnn_problem* P, const ddmgnn_model_des
         if (c_off[i] < 0) return fail(DDMGNN_E_INVALID, "negative right-hand side offset");
     }
     if (int rc = prepare_train(P)) return rc;
-    // Tiles of all samples; chunks of whole samples share the scratch region.
-    std::vector<int4> items;
-    std::vector<int32_t> chunk{0};  // first tile of each chunk, and the end
-    int64_t most = 0;
-    for (int32_t i = 0; i < n; ++i) {
-        const int32_t t0 = P->vt_first[subs[i]], t1 = t0 + sub_tiles(P, subs[i]);
-        int64_t first = (int64_t)items.size() / 2;
-        if (first + (t1 - t0) >= INT32_MAX / 2) return fail(DDMGNN_E_INVALID, "too many samples");
-        if (first > chunk.back() && first - chunk.back() + (t1 - t0) > TRAIN_TILES) chunk.push_back((int32_t)first);
-        first -= chunk.back();  // within the chunk
-        for (int32_t t = t0; t < t1; ++t) {
-            const VtTile f = P->vt_tiles[t];
-            const int2 o = P->tr_out_rows[t];
-            items.push_back(make_int4(t, (int)(first - t0) * VT_TILE, f.z, f.w));
-            items.push_back(make_int4(o.x, o.y, (int)(uint32_t)(uint64_t)c_off[i], (int)(uint32_t)((uint64_t)c_off[i] >> 32)));
-        }
-        most = std::max(most, first + (t1 - t0));
-    }
-    chunk.push_back((int32_t)(items.size() / 2));
     const int kb = md->kbar, ks = (kb + 3) / 4 * 4;
     hipStream_t s = ctx->stream;
+    auto grow = [&](auto& buf, size_t n) {
+        if (buf.n >= n) return hipSuccess;
+        P->device_bytes -= buf.n * sizeof(*buf.p);
+        const hipError_t e = buf.alloc(n);
+        P->device_bytes += buf.n * sizeof(*buf.p);
+        return e;
+    };
+    // Tiles of all samples; chunks of whole samples share the scratch region.
+    std::vector<int4> items;
+    std::vector<int32_t> chunk;  // first tile of each chunk, and the end
     // scratch, in floats: blobs, inputs, states, sender rows, sums, r, rho, gr, receiver rows, own values, accumulators
-    const size_t T = (size_t)most, lanes = T * VT_TILE;
-    const size_t parts[] = {(size_t)kb * TRAIN_BLOB, 2 * lanes, (size_t)(kb + 1) * T * 256,
-                            (size_t)kb * (lanes + 1) * 2 * D, (size_t)kb * T * 320, lanes * ks, lanes * ks, lanes * ks,
-                            (lanes + 1) * 4 * D, (lanes + 1) * 4 * D, T * 1024,
-                            (size_t)(kb + 1) * train_workgroups(most) * TRAIN_ACC * 64};
-    constexpr int NP = sizeof(parts) / sizeof(parts[0]);
+    constexpr int NP = 12;
     size_t off[NP + 1] = {0};
-    for (int i = 0; i < NP; ++i) off[i + 1] = off[i] + (parts[i] + 63) / 64 * 64;
-    if (P->tr_scratch.n < off[NP]) HIP_TRY(P->tr_scratch.alloc(off[NP]));
-    if (P->tr_items.n < items.size()) HIP_TRY(P->tr_items.alloc(items.size()));
+    for (int64_t cap = TRAIN_TILES;; cap /= 2) {
+        items.clear();
+        chunk.assign(1, 0);
+        int64_t most = 0;
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t t0 = P->vt_first[subs[i]], t1 = t0 + sub_tiles(P, subs[i]);
+            int64_t first = (int64_t)items.size() / 2;
+            if (first + (t1 - t0) >= INT32_MAX / 2) return fail(DDMGNN_E_INVALID, "too many samples");
+            if (first > chunk.back() && first - chunk.back() + (t1 - t0) > cap) chunk.push_back((int32_t)first);
+            first -= chunk.back();  // within the chunk
+            for (int32_t t = t0; t < t1; ++t) {
+                const VtTile f = P->vt_tiles[t];
+                const int2 o = P->tr_out_rows[t];
+                items.push_back(make_int4(t, (int)(first - t0) * VT_TILE, f.z, f.w));
+                items.push_back(make_int4(o.x, o.y, (int)(uint32_t)(uint64_t)c_off[i],
+                                          (int)(uint32_t)((uint64_t)c_off[i] >> 32)));
+            }
+            most = std::max(most, first + (t1 - t0));
+        }
+        chunk.push_back((int32_t)(items.size() / 2));
+        const size_t T = (size_t)most, lanes = T * VT_TILE;
+        const size_t parts[NP] = {(size_t)kb * TRAIN_BLOB, 2 * lanes, (size_t)(kb + 1) * T * 256,
+                                  (size_t)kb * (lanes + 1) * 2 * D, (size_t)kb * T * 320, lanes * ks, lanes * ks,
+                                  lanes * ks, (lanes + 1) * 4 * D, (lanes + 1) * 4 * D, T * 1024,
+                                  (size_t)(kb + 1) * train_workgroups(most) * TRAIN_ACC * 64};
+        for (int i = 0; i < NP; ++i) off[i + 1] = off[i] + (parts[i] + 63) / 64 * 64;
+        const hipError_t e = grow(P->tr_scratch, off[NP]);
+        if (e == hipSuccess) break;
+        if (e != hipErrorOutOfMemory || chunk.size() > (size_t)n) HIP_TRY(e);  // not one sample fits
+    }
     const size_t n_red = (size_t)(kb + 1) * TRAIN_ACC * 64;
-    if (P->tr_red.n < n_red) HIP_TRY(P->tr_red.alloc(n_red));
     size_t n_sse = 0;
     for (size_t q = 0; q + 1 < chunk.size(); ++q) n_sse += (size_t)train_sse_count(chunk[q + 1] - chunk[q], ks);
-    if (P->tr_sse.n < n_sse) HIP_TRY(P->tr_sse.alloc(n_sse));
-    if (!P->tr_out.p) HIP_TRY(P->tr_out.alloc(2));
+    HIP_TRY(grow(P->tr_items, items.size()));
+    HIP_TRY(grow(P->tr_red, n_red));
+    HIP_TRY(grow(P->tr_sse, n_sse));
+    HIP_TRY(grow(P->tr_out, 2));
     HIP_TRY(upload_async(P->tr_items.p, items.data(), items.size() * sizeof(int4), s));
     float* f = P->tr_scratch.p;
     TrainArgs a{};

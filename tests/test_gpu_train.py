@@ -270,3 +270,41 @@ def test_chunks_and_tile_edges_match_oracle_sums(setup):
     assert loss == pytest.approx(total, rel=1e-6)
     # FP32 sums over the nodes in another order: the bar of the oracle comparison
     assert float((g.double() - want).abs().max()) <= GRAD_ATOL * float(want.abs().max())
+
+
+def test_scratch_is_counted_and_kept(setup):
+    """The scratch of a gradient call stays with the problem and shows in its device bytes: 4 bytes
+    for about 1,000 kbar values per tile; a smaller call after it needs nothing more."""
+    p, hp, ctx, prob, subs, torch = setup
+    fresh = dg.Problem(ctx, hp, dg.Model(ctx, W.xavier_theta(0, 30, 10)))
+    kbar = 4
+    theta = torch.tensor(_theta(5, kbar), device="cuda")
+    cs = [_rhs(subs[i][1], 60 + i) for i in range(hp.K)]
+    cdev = torch.tensor(np.concatenate(cs), device="cuda")
+    off = np.cumsum([0] + [c.size for c in cs[:-1]])
+    order = np.arange(3 * hp.K) % hp.K
+    g = torch.empty_like(theta)
+    base = fresh.device_bytes()
+    fresh.train_grad(theta, order, cdev, off[order], g, kbar=kbar, alpha=0.3)
+    tiles = sum((cs[i].size + 15) // 16 for i in order)
+    used = fresh.device_bytes() - base
+    assert used >= 4 * 1000 * kbar * tiles
+    fresh.train_grad(theta, [0], cdev, [off[0]], g, kbar=kbar, alpha=0.3)
+    assert fresh.device_bytes() == base + used
+
+
+def test_repeated_sample_gives_its_gradient(setup):
+    """A batch of one sample repeated, with scale 1/n, gives that sample's gradient with scale 1,
+    whatever tiles of a workgroup the copies fall on (one chunk and two)."""
+    p, hp, ctx, prob, subs, torch = setup
+    theta = torch.tensor(_theta(5, 2), device="cuda")
+    c = _rhs(subs[1][1], 70)
+    cdev = torch.tensor(c, device="cuda")
+    tiles = (c.size + 15) // 16
+    one, g = torch.empty_like(theta), torch.empty_like(theta)
+    L, _ = prob.train_grad(theta, [1], cdev, [0], one, kbar=2, alpha=0.3, scale=1.0)
+    for n in (2, 9, 32768 // tiles + 2):
+        loss, _ = prob.train_grad(theta, np.full(n, 1), cdev, np.zeros(n, np.int64), g, kbar=2, alpha=0.3, scale=1.0 / n)
+        assert loss == pytest.approx(L, rel=1e-6)  # the loss is scaled too
+        # FP32 sums over the nodes in another order: the bar of the oracle comparison
+        assert float((g - one).abs().max()) <= GRAD_ATOL * float(one.abs().max())
