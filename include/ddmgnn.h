@@ -244,14 +244,19 @@ int ddmgnn_solve_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int32_t n,
  * submission; `setup_threads` host threads (0: 4) run their host setup
  * (validation, local graphs, every array the device needs); one GPU thread
  * admits set-up requests in submission order while their device memory
- * (ddmgnn_problem_device_bytes) fits `hbm_budget` bytes and at most
- * `max_active` are active, advances all active requests together by chunks
+ * (ddmgnn_problem_device_bytes after the solve) fits `hbm_budget` bytes and at
+ * most `max_active` are active, advances all active requests together by chunks
  * of opts.check_every iterations (as ddmgnn_solve_batch), creates newly
  * admitted problems on a stream of its own while a chunk runs, and retires
  * each request as it converges. Requests batch together only when their Krylov method,
  * m_max, precision, prolong and coarse options agree; one that differs from
  * the active set waits until that set has drained (rtol and max_it are per
- * request). A request larger than the budget fails with E_BUDGET. */
+ * request). A request larger than the budget fails with E_BUDGET. Its own arrays
+ * decide that: one that fits without the work arrays of the FP64 or FP32 forward in
+ * tiles runs that forward with one workgroup per sub-mesh (FP32: the same bits; FP64:
+ * another order of sums), and one that does not fit with that form's either (global
+ * sender rows and states, about 80 bytes per sub-mesh node and up to 240) runs alone and
+ * may exceed the budget by them. */
 int ddmgnn_server_create(ddmgnn_ctx* ctx, const ddmgnn_model* model, int64_t hbm_budget, int32_t max_active,
                          int32_t setup_threads, ddmgnn_server** out);
 /* Non-blocking. *ticket identifies the request (> 0). */

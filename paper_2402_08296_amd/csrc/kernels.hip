@@ -1489,20 +1489,14 @@ inline hipError_t done(bool check) { return check ? hipGetLastError() : hipSucce
 
 // ------------------------------------------------------------------ launchers
 namespace {
-// Width 10 in FP64 runs in tiles (dss_tile.hip).
 template <int W>
 hipError_t prepare_dss_valu_w(int precision, size_t shmem) {
-    auto raise = [&](const void* f, const void* wide) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-        return e != hipSuccess ? e : hipFuncSetAttribute(wide, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
-    };
-    if (precision != DDMGNN_FP64)
-        return raise((const void*)dss_kernel<float, W, true, true>,
-                     (const void*)dss_kernel<float, W, true, true, false, DSS_WIDE_BLOCK>);
-    if constexpr (W != 10)
-        return raise((const void*)dss_kernel<double, W, false, true>,
-                     (const void*)dss_kernel<double, W, false, true, false, DSS_WIDE_BLOCK>);
-    return hipErrorInvalidValue;
+    const bool f64 = precision == DDMGNN_FP64;
+    const void* fn = f64 ? (const void*)dss_kernel<double, W, false, true> : (const void*)dss_kernel<float, W, true, true>;
+    const void* fw = f64 ? (const void*)dss_kernel<double, W, false, true, false, DSS_WIDE_BLOCK>
+                         : (const void*)dss_kernel<float, W, true, true, false, DSS_WIDE_BLOCK>;
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    return e != hipSuccess ? e : hipFuncSetAttribute(fw, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
 }
 
 template <typename T, int W, bool HREG, int BLOCK>
@@ -1515,26 +1509,23 @@ void launch_dss_valu_b(const DssArgs<T>& a, const T* theta, int n_work, bool qld
 }
 
 // A launch of fewer sub-meshes than the device has compute units takes the
-// 1024-thread form (d = 5): each sub-mesh then has twice the wavefronts to
-// hide its latency (both forms give the same bits).
+// 1024-thread form (d <= 10): each sub-mesh then has twice the wavefronts to
+// hide its latency (both forms give the same bits). At width 10 launches in tiles
+// (dss_tile.hip) leave this kernel the large FP32 ones and untiled problems.
 template <int W>
-hipError_t launch_dss_valu_w(const DevProb* tab, const int2* work, int n_work, int precision, bool qlds, int kbar,
-                             double alpha, int apply, const float* theta32, const double* theta64, size_t shmem,
-                             hipStream_t s) {
+void launch_dss_valu_w(const DevProb* tab, const int2* work, int n_work, int precision, bool qlds, int kbar,
+                       double alpha, int apply, const float* theta32, const double* theta64, size_t shmem,
+                       hipStream_t s) {
     const bool wide = n_work < N_CU && W <= 10;  // at d = 20 the 1024-thread form spills
-    if (precision != DDMGNN_FP64) {
-        const DssArgs<float> a{tab, work, kbar, (float)alpha, apply};
-        if (wide) launch_dss_valu_b<float, W, true, DSS_WIDE_BLOCK>(a, theta32, n_work, qlds, shmem, s);
-        else launch_dss_valu_b<float, W, true, DSS_BLOCK>(a, theta32, n_work, qlds, shmem, s);
-        return hipSuccess;
-    }
-    if constexpr (W != 10) {
+    if (precision == DDMGNN_FP64) {
         const DssArgs<double> a{tab, work, kbar, alpha, apply};
         if (wide) launch_dss_valu_b<double, W, false, DSS_WIDE_BLOCK>(a, theta64, n_work, qlds, shmem, s);
         else launch_dss_valu_b<double, W, false, DSS_BLOCK>(a, theta64, n_work, qlds, shmem, s);
-        return hipSuccess;
+    } else {
+        const DssArgs<float> a{tab, work, kbar, (float)alpha, apply};
+        if (wide) launch_dss_valu_b<float, W, true, DSS_WIDE_BLOCK>(a, theta32, n_work, qlds, shmem, s);
+        else launch_dss_valu_b<float, W, true, DSS_BLOCK>(a, theta32, n_work, qlds, shmem, s);
     }
-    return hipErrorInvalidValue;
 }
 }  // namespace
 
@@ -1552,14 +1543,16 @@ hipError_t launch_dss_valu(const DevProb* tab, const int2* work, int n_work, int
                            size_t shmem, hipStream_t s, bool check) {
     if (n_work <= 0) return hipSuccess;
     auto run = [&](auto width) {
-        return launch_dss_valu_w<decltype(width)::value>(tab, work, n_work, precision, qlds, kbar, alpha, apply,
-                                                         theta32, theta64, shmem, s);
+        launch_dss_valu_w<decltype(width)::value>(tab, work, n_work, precision, qlds, kbar, alpha, apply, theta32,
+                                                  theta64, shmem, s);
     };
-    const hipError_t e = d == 5    ? run(std::integral_constant<int, 5>())
-                         : d == 10 ? run(std::integral_constant<int, 10>())
-                         : d == 20 ? run(std::integral_constant<int, 20>())
-                                   : hipErrorInvalidValue;
-    return e != hipSuccess ? e : done(check);
+    switch (d) {
+        case 5: run(std::integral_constant<int, 5>()); break;
+        case 10: run(std::integral_constant<int, 10>()); break;
+        case 20: run(std::integral_constant<int, 20>()); break;
+        default: return hipErrorInvalidValue;
+    }
+    return done(check);
 }
 
 hipError_t launch_dss_big(const DevProb* tab, const int2* work, int n_work, int precision, int d, int kbar,

@@ -23,6 +23,20 @@ int fail(int code, const std::string& msg) {
 }
 
 // ------------------------------------------------------------------ batch
+// Sub-meshes of a batch that the FP64 / FP32 forward runs (those of at most kMaxSubNodes).
+struct DssSide {
+    std::vector<int2> host;            // (problem, sub-mesh) by decreasing size
+    DevBuf<int2> work;                 // the same
+    int n = 0, max_k = 0;
+    int64_t tiles = 0;                 // tiles of 16 nodes
+    // Built at the first use in tiles (d = 10): the tiles by problem and sub-mesh, and, where a
+    // problem is untiled, the sub-meshes of the others (subs) and of the untiled ones (plain).
+    std::vector<uint8_t> untiled;      // of each problem, as these lists were built
+    DevBuf<int4> items;
+    DevBuf<int2> subs, plain;
+    int n_items = 0, n_subs = 0, n_plain = 0, max_k_plain = 0;
+};
+
 struct Batch {
     ddmgnn_ctx* ctx = nullptr;
     std::vector<ddmgnn_problem*> probs;
@@ -33,28 +47,24 @@ struct Batch {
     DevBuf<DevProb> hook;              // one-problem table of the entry points that redirect vectors
     // DSS work lists, (problem, sub-mesh) by decreasing sub-mesh size:
     // those that fit the MFMA kernel; the others; of all, those of at most kMaxSubNodes.
-    // (the VALU lists hold sub-meshes of at most kMaxSubNodes nodes; work_big the larger ones,
-    // which run the global-memory form of the VALU kernel in every precision)
-    DevBuf<int2> work_mfma, work_rest, work_valu, work_big;
+    // (work_big: sub-meshes beyond kMaxSubNodes, which run the global-memory form of the VALU
+    // kernel in every precision)
+    DssSide valu, rest;                // all, and those that the MFMA kernel does not run
+    DevBuf<int2> work_mfma, work_big;
     std::vector<int2> all;             // host: every sub-mesh
-    int n_mfma = 0, n_rest = 0, n_valu = 0, n_big = 0;
+    int n_mfma = 0, n_big = 0;
     // the MFMA list split by workgroup size: sub-meshes that run two per compute
     // unit in MFMA_SMALL_BLOCK-thread workgroups, and the rest; dynamic LDS of each launch
     DevBuf<int2> work_mfma_small;
     int n_mfma_small = 0;
     size_t lds_mfma = 0, lds_mfma_small = 0;
-    int max_k_all = 0, max_k_rest = 0, max_k_valu = 0;
-    // exact local solves (built at the first one): units of work_valu's and work_big's
+    int max_k_all = 0;
+    // exact local solves (built at the first one): units of valu's and work_big's
     // sub-meshes, and the sub-meshes whose inverses are held in tiles
     bool lu_ready = false;
     DevBuf<int4> lu_small, lu_big;
     DevBuf<int2> lu_subs;
     int n_lu_small = 0, n_lu_big = 0, n_lu_subs = 0;
-    // tiles of work_valu and work_rest for the tiled FP64 / FP32 forward (d = 10), by
-    // problem and sub-mesh; built at the first use
-    DevBuf<int4> tiles_valu, tiles_rest;
-    int n_tiles_valu = 0, n_tiles_rest = 0;
-    int64_t vt_valu = 0, vt_rest = 0;  // tiles the lists hold once built
     DevBuf<int2> vec_blk;              // (problem, local workgroup)
     int n_vec = 0;
     DevBuf<int2> coarse_rows;          // (problem, row)
@@ -272,7 +282,7 @@ int prepare_exact(Batch& B, bool& changed) {
         return (int)(sp[w.y + 1] - sp[w.y]);
     };
     for (const int2& w : B.all) max_k[w.x] = std::max(max_k[w.x], size(w));
-    static_assert(LU_LDS_K == kMaxSubNodes, "work_valu holds the sub-meshes of the exact solves' LDS form");
+    static_assert(LU_LDS_K == kMaxSubNodes, "valu holds the sub-meshes of the exact solves' LDS form");
     for (const int2& w : B.all) {
         const int k = size(w);
         if (lu_dense(k, max_k[w.x])) {
@@ -351,38 +361,48 @@ struct Carver {
 
 // Tiles of the sub-meshes of at most kMaxSubNodes nodes: their nodes by decreasing
 // in-degree (tnode), so a tile's edge rows are its first node's in-degree (made even: rows
-// are summed in pairs). The sub-meshes that the BF16 kernel does not run come first: BF16
-// keeps arrays for those only.
-void list_tiles(ddmgnn_problem* P) {
-    if (!P->vt_first.empty()) return;
-    const auto& hs = P->hs;
-    P->vt_first.assign((size_t)hs.K, 0);
+// are summed in pairs). The sub-meshes that the BF16 kernel does not run (need: its LDS
+// bytes) come first: BF16 keeps arrays for those only. f(sub-mesh, first slot, position,
+// edge rows) for every tile; rest: the tiles of those sub-meshes; returns all.
+template <class F>
+TileCount for_tiles(const HostSetup& hs, const std::vector<uint32_t>& need, TileCount& rest, F f) {
+    TileCount n;
     for (int side = 0; side < 2; ++side) {
         for (int32_t i = 0; i < hs.K; ++i) {
             const int64_t b = hs.sub_ptr[i], k = hs.sub_ptr[i + 1] - b;
-            if (mfma_runs_sub(P, i) != (side == 1) || k > kMaxSubNodes) continue;
-            P->vt_first[i] = (int32_t)P->vt_tiles.size();
+            if ((need[(size_t)i] <= MFMA_LDS_LIMIT) != (side == 1) || k > kMaxSubNodes) continue;
             for (int64_t q = 0; q < k; q += VT_TILE) {
                 const int64_t slot = b + hs.tnode[b + q];
                 const int64_t deg = (hs.edge_ptr[slot + 1] - hs.edge_ptr[slot] + 1) & ~int64_t(1);
-                P->vt_tiles.push_back(make_int4((int)b, (int)q, (int)P->vt_all.rows, (int)deg));
-                P->vt_all.rows += deg;
+                f(i, b, q, deg);
+                ++n.tiles;
+                n.rows += deg;
             }
         }
-        P->vt_all.tiles = (int64_t)P->vt_tiles.size();
-        if (side == 0) P->vt_rest = P->vt_all;
+        if (side == 0) rest = n;
     }
+    return n;
+}
+void list_tiles(ddmgnn_problem* P) {
+    if (!P->vt_first.empty()) return;
+    P->vt_first.assign((size_t)P->hs.K, 0);
+    int64_t rows = 0;
+    P->vt_all = for_tiles(P->hs, P->mfma_need, P->vt_rest, [&](int32_t i, int64_t b, int64_t q, int64_t deg) {
+        if (q == 0) P->vt_first[i] = (int32_t)P->vt_tiles.size();
+        P->vt_tiles.push_back(make_int4((int)b, (int)q, (int)rows, (int)deg));
+        rows += deg;
+    });
 }
 
 // The nodes of P's tiles and the slots' tile lanes (hook: a one-problem table to build
 // with, left holding P).
-int prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
+hipError_t prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
     hipStream_t s = P->ctx->stream;
     list_tiles(P);
     const size_t nt = P->vt_tiles.size(), K = (size_t)P->hs.K;
     const DevProb v = make_view(P);
-    HIP_TRY(launch_set_view(hook.p, v, s));
-    if (P->vt_pos) return DDMGNN_OK;
+    hipError_t e = launch_set_view(hook.p, v, s);
+    if (e != hipSuccess || P->vt_pos) return e;
     // the tiles and the first of every sub-mesh: one copy
     std::vector<VtTile> host(P->vt_tiles);
     host.resize(nt + (K + 3) / 4);
@@ -399,18 +419,37 @@ int prepare_tile_nodes(ddmgnn_problem* P, DevBuf<DevProb>& hook) {
         }
         return c.used;
     };
-    HIP_TRY(P->vt_mem.alloc(carve(Carver{nullptr}, false)));
-    HIP_TRY(upload_async(P->vt_mem.p, host.data(), host.size() * sizeof(VtTile), s));
+    e = P->vt_mem.alloc(carve(Carver{nullptr}, false));
+    if (e == hipSuccess) e = upload_async(P->vt_mem.p, host.data(), host.size() * sizeof(VtTile), s);
+    if (e != hipSuccess) return e;
     carve(Carver{P->vt_mem.p}, true);
-    const hipError_t e = launch_vt_nodes(hook.p, P->vt_info, (int)nt, P->vt_node, P->vt_pos, s);
-    if (e != hipSuccess) P->vt_pos = nullptr;  // a failed build is retried whole
-    HIP_TRY(e);
-    P->device_bytes += tile_node_bytes((int64_t)nt, P->hs.sk, P->hs.K);
+    e = launch_vt_nodes(hook.p, P->vt_info, (int)nt, P->vt_node, P->vt_pos, s);
+    if (e != hipSuccess)
+        P->vt_pos = nullptr;  // a failed build is retried whole
+    else
+        P->device_bytes += tile_node_bytes((int64_t)nt, P->hs.sk, P->hs.K);
+    return e;
+}
+
+// Frees P's tile arrays in one precision.
+template <typename T>
+void drop_tiles(ddmgnn_problem* P, VtBufs<T>& V) {
+    if (V.mem.p) P->device_bytes -= tile_bytes(V.n, sizeof(T) == 8);
+    V.mem.reset();
+    V.v = VtVecs<T>{};
+    V.n = TileCount{};
+}
+
+// P's FP64 / FP32 forward keeps one workgroup per sub-mesh from now on.
+int make_untiled(ddmgnn_problem* P) {
+    drop_tiles(P, P->vt64);
+    drop_tiles(P, P->vt32);
+    P->untiled = true;
     return DDMGNN_OK;
 }
 
 // Builds the arrays of P's tiled forward in type T for its first n.tiles tiles (hook: a
-// one-problem table to build with).
+// one-problem table to build with); where they cannot be allocated P becomes untiled.
 template <typename T>
 int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, const TileCount& n, DevBuf<DevProb>& hook, bool& changed) {
     if (V.mem.p && V.n.tiles >= n.tiles) return DDMGNN_OK;
@@ -418,7 +457,9 @@ int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, const TileCount& n, DevBuf<De
     const int64_t nt = n.tiles, rows = n.rows + VT_ROWS;
     if (rows * VT_TILE >= INT32_MAX || nt * VT_TILE >= INT32_MAX)
         return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
-    if (int rc = prepare_tile_nodes(P, hook)) return rc;
+    hipError_t e = prepare_tile_nodes(P, hook);
+    if (e == hipErrorOutOfMemory) return make_untiled(P);
+    HIP_TRY(e);
     constexpr bool f64 = sizeof(T) == 8;
     const size_t er = (size_t)rows * VT_TILE, pad = (size_t)VT_ROWS * VT_TILE, qn = (size_t)(nt * VT_TILE + 1) * 2 * D;
     VtRec<T>* rec = nullptr;
@@ -431,13 +472,12 @@ int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, const TileCount& n, DevBuf<De
         v.rec = rec;
         return c.used;
     };
-    if (V.mem.p) P->device_bytes -= tile_bytes(V.n, f64);
-    V.v = VtVecs<T>{};
-    V.n = TileCount{};
+    drop_tiles(P, V);
     changed = true;
     DevBuf<char> mem;  // moved in last: a failed build is retried whole
-    V.mem.reset();
-    HIP_TRY(mem.alloc(carve(Carver{nullptr})));
+    e = mem.alloc(carve(Carver{nullptr}));
+    if (e == hipErrorOutOfMemory) return make_untiled(P);
+    HIP_TRY(e);
     carve(Carver{mem.p});
     HIP_TRY(hipMemsetAsync(rec + er - pad, 0, pad * sizeof(VtRec<T>), s));
     const T inf = std::numeric_limits<T>::infinity();
@@ -523,7 +563,7 @@ int prepare_train(ddmgnn_problem* P) {
     if ((rows + VT_ROWS) * VT_TILE >= INT32_MAX || (P->vt_all.rows + VT_ROWS) * VT_TILE >= INT32_MAX)
         return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
     if (int rc = solo_batch(P)) return rc;
-    if (int rc = prepare_tile_nodes(P, P->solo->hook)) return rc;
+    HIP_TRY(prepare_tile_nodes(P, P->solo->hook));
     std::vector<int32_t> map;
     std::vector<TrainEntry> ent;
     build_train_maps(map, ent);
@@ -559,22 +599,41 @@ int32_t sub_tiles(const ddmgnn_problem* P, int32_t i) {
     return (int32_t)((P->hs.sub_ptr[i + 1] - P->hs.sub_ptr[i] + VT_TILE - 1) / VT_TILE);
 }
 
-// Tile list of a batch: the tiles of the sub-meshes `take` accepts, by problem and sub-mesh.
-template <class F>
-int upload_tiles(Batch& B, DevBuf<int4>& buf, int& n, F take) {
-    if (n) return DDMGNN_OK;
+// The lists of a side that runs in tiles, for the problems' present forms.
+int split_side(Batch& B, DssSide& S) {
+    std::vector<uint8_t> now;
+    for (const ddmgnn_problem* P : B.probs) now.push_back(P->untiled ? 1 : 0);
+    if (S.untiled == now) return DDMGNN_OK;
+    if (!S.untiled.empty()) {  // captured launches read the old lists
+        B.graph.reset();
+        B.brief.reset();
+    }
+    S.untiled.clear();
+    std::vector<int2> subs, plain, order;
+    S.max_k_plain = 0;
+    for (const int2& w : S.host) {
+        const ddmgnn_problem* P = B.probs[w.x];
+        (now[w.x] ? plain : subs).push_back(w);
+        if (now[w.x]) S.max_k_plain = std::max(S.max_k_plain, (int)(P->hs.sub_ptr[w.y + 1] - P->hs.sub_ptr[w.y]));
+    }
+    order = subs;
+    std::sort(order.begin(), order.end(), [](const int2& a, const int2& b) { return a.x != b.x ? a.x < b.x : a.y < b.y; });
     std::vector<int4> v;
-    for (size_t p = 0; p < B.probs.size(); ++p) {
-        const ddmgnn_problem* P = B.probs[p];
-        for (int32_t i = 0; i < P->hs.K; ++i) {
-            if (!take(P, i) || P->hs.sub_ptr[i + 1] - P->hs.sub_ptr[i] > kMaxSubNodes) continue;
-            for (int32_t t = P->vt_first[i], e = t + sub_tiles(P, i); t < e; ++t)
-                v.push_back(make_int4((int)p, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
-        }
+    for (const int2& w : order) {
+        const ddmgnn_problem* P = B.probs[w.x];
+        for (int32_t t = P->vt_first[w.y], e = t + sub_tiles(P, w.y); t < e; ++t)
+            v.push_back(make_int4(w.x, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
     }
     if (v.size() > (size_t)INT32_MAX) return fail(DDMGNN_E_INVALID, "too many tiles in one batch");
-    if (int rc = upload_list(buf, v, B.ctx->stream)) return rc;
-    n = (int)v.size();
+    if (int rc = upload_list(S.items, v, B.ctx->stream)) return rc;
+    if (!plain.empty()) {
+        if (int rc = upload_list(S.subs, subs, B.ctx->stream)) return rc;
+        if (int rc = upload_list(S.plain, plain, B.ctx->stream)) return rc;
+    }
+    S.n_items = (int)v.size();
+    S.n_subs = (int)subs.size();
+    S.n_plain = (int)plain.size();
+    S.untiled = now;
     return DDMGNN_OK;
 }
 
@@ -613,25 +672,23 @@ int prepare_dss(Batch& B, int precision, bool& changed) {
             changed = true;
         }
     }
-    const int max_k = bf16 ? B.max_k_rest : B.max_k_valu;
-    const int n_valu = bf16 ? B.n_rest : B.n_valu;
-    if (n_valu == 0) return DDMGNN_OK;
-    if (runs_tiled(d, valu_prec, bf16 ? B.vt_rest : B.vt_valu)) {
+    DssSide& S = bf16 ? B.rest : B.valu;
+    if (S.n == 0) return DDMGNN_OK;
+    const bool tiled = runs_tiled(d, valu_prec, S.tiles);
+    if (tiled) {
         for (ddmgnn_problem* P : B.probs) {
-            if (bf16 && !any_valu_bf16(P)) continue;
+            if (P->untiled || (bf16 && !any_valu_bf16(P))) continue;
             list_tiles(P);
             const TileCount& n = bf16 ? P->vt_rest : P->vt_all;
             const int rc = f64 ? prepare_tiles(P, P->vt64, n, B.hook, changed) : prepare_tiles(P, P->vt32, n, B.hook, changed);
             if (rc) return rc;
         }
-        if (bf16)
-            return upload_tiles(B, B.tiles_rest, B.n_tiles_rest,
-                                [](const ddmgnn_problem* P, int32_t i) { return !mfma_runs_sub(P, i); });
-        return upload_tiles(B, B.tiles_valu, B.n_tiles_valu, [](const ddmgnn_problem*, int32_t) { return true; });
+        if (int rc = split_side(B, S)) return rc;
+        if (S.n_plain == 0) return DDMGNN_OK;
     }
-    const bool in_lds = valu_q_in_lds(max_k, valu_prec, d);
+    const bool in_lds = valu_q_in_lds(tiled ? S.max_k_plain : S.max_k, valu_prec, d);
     for (ddmgnn_problem* P : B.probs) {
-        if (bf16 && !any_valu_bf16(P)) continue;
+        if ((bf16 && !any_valu_bf16(P)) || (tiled && !P->untiled)) continue;
         const size_t sk = (size_t)P->hs.sk;
         if (!in_lds) {
             if (f64 && P->qglobal64.n < sk * 2 * d) {
@@ -652,6 +709,31 @@ int prepare_dss(Batch& B, int precision, bool& changed) {
     return DDMGNN_OK;
 }
 
+// The FP64 or FP32 forward of a side's sub-meshes.
+int enqueue_side(Batch& B, const DssSide& S, const DevProb* tab, int precision, int apply, bool check) {
+    hipStream_t s = B.ctx->launch;
+    const ModelDev& M = *B.model;
+    const int2* work = S.work.p;
+    int n = S.n, max_k = S.max_k;
+    if (runs_tiled(M.d, precision, S.tiles)) {
+        const bool solo = B.probs.size() == 1;
+        const int2* subs = S.n_plain ? S.subs.p : S.work.p;
+        if (precision == DDMGNN_FP64)
+            HIP_TRY(launch_dss_tiles<double>(tab, subs, S.n_subs, S.items.p, S.n_items, solo, M.kbar, M.alpha, apply,
+                                             M.vt64.p, s, check));
+        else
+            HIP_TRY(launch_dss_tiles<float>(tab, subs, S.n_subs, S.items.p, S.n_items, solo, M.kbar, M.alpha, apply,
+                                            M.vt32.p, s, check));
+        work = S.plain.p;
+        n = S.n_plain;
+        max_k = S.max_k_plain;
+    }
+    const bool qlds = valu_q_in_lds(max_k, precision, M.d);
+    HIP_TRY(launch_dss_valu(tab, work, n, precision, M.d, qlds, M.kbar, M.alpha, apply, M.theta32.p, M.theta64.p,
+                            qlds ? valu_shmem(max_k, precision, M.d) : 0, s, check));
+    return DDMGNN_OK;
+}
+
 // Local solves over every sub-mesh of the table: the DSS forward (apply:
 // restriction and s r~), or the exact solves of DDM-LU.
 int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool capturing, int local = DDMGNN_LOCAL_GNN) {
@@ -659,7 +741,7 @@ int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool cap
     const ModelDev& M = *B.model;
     const bool check = !capturing;
     if (local == DDMGNN_LOCAL_LU) {
-        const LuWork w{B.lu_small.p, B.n_lu_small, B.max_k_valu, B.lu_big.p, B.n_lu_big, B.max_k_all,
+        const LuWork w{B.lu_small.p, B.n_lu_small, B.valu.max_k, B.lu_big.p, B.n_lu_big, B.max_k_all,
                        B.lu_subs.p, B.n_lu_subs};
         HIP_TRY(launch_lu_local(tab, w, s, check));
         return DDMGNN_OK;
@@ -685,30 +767,9 @@ int enqueue_dss(Batch& B, const DevProb* tab, int precision, int apply, bool cap
             a.work = B.work_mfma_small.p;
             HIP_TRY(launch_dss_mfma(a, B.n_mfma_small, B.lds_mfma_small, MFMA_SMALL_BLOCK, s, check));
         }
-        if (runs_tiled(M.d, DDMGNN_FP32, B.vt_rest)) {
-            HIP_TRY(launch_dss_tiles<float>(tab, B.work_rest.p, B.n_rest, B.tiles_rest.p, B.n_tiles_rest,
-                                            B.probs.size() == 1, M.kbar, M.alpha, apply, M.vt32.p, s, check));
-            return DDMGNN_OK;
-        }
-        const bool qlds = valu_q_in_lds(B.max_k_rest, DDMGNN_FP32, M.d);
-        HIP_TRY(launch_dss_valu(tab, B.work_rest.p, B.n_rest, DDMGNN_FP32, M.d, qlds, M.kbar, M.alpha, apply,
-                                M.theta32.p, M.theta64.p, qlds ? valu_shmem(B.max_k_rest, DDMGNN_FP32, M.d) : 0, s,
-                                check));
-    } else if (runs_tiled(M.d, precision, B.vt_valu)) {
-        const bool solo = B.probs.size() == 1;
-        if (precision == DDMGNN_FP64)
-            HIP_TRY(launch_dss_tiles<double>(tab, B.work_valu.p, B.n_valu, B.tiles_valu.p, B.n_tiles_valu, solo, M.kbar,
-                                             M.alpha, apply, M.vt64.p, s, check));
-        else
-            HIP_TRY(launch_dss_tiles<float>(tab, B.work_valu.p, B.n_valu, B.tiles_valu.p, B.n_tiles_valu, solo, M.kbar,
-                                            M.alpha, apply, M.vt32.p, s, check));
-    } else {
-        const bool qlds = valu_q_in_lds(B.max_k_valu, precision, M.d);
-        HIP_TRY(launch_dss_valu(tab, B.work_valu.p, B.n_valu, precision, M.d, qlds, M.kbar, M.alpha, apply,
-                                M.theta32.p, M.theta64.p, qlds ? valu_shmem(B.max_k_valu, precision, M.d) : 0, s,
-                                check));
+        return enqueue_side(B, B.rest, tab, DDMGNN_FP32, apply, check);
     }
-    return DDMGNN_OK;
+    return enqueue_side(B, B.valu, tab, precision, apply, check);
 }
 
 IterArgs iter_args(const ddmgnn_solve_opts& o, int mode) {
@@ -779,8 +840,8 @@ int brief_chunk(const Batch& B, const ddmgnn_solve_opts& o) {
     const int check = std::max(1, o.check_every);
     if (o.krylov == DDMGNN_CG || o.local_solver == DDMGNN_LOCAL_LU || B.last_it > 2 * BRIEF_CHUNK) return check;
     const bool bf16 = o.precision == DDMGNN_BF16;
-    const bool tiled = (bf16 ? B.n_rest : B.n_valu) > 0 &&
-                       runs_tiled(B.model->d, bf16 ? DDMGNN_FP32 : o.precision, bf16 ? B.vt_rest : B.vt_valu);
+    const DssSide& S = bf16 ? B.rest : B.valu;
+    const bool tiled = S.n > 0 && runs_tiled(B.model->d, bf16 ? DDMGNN_FP32 : o.precision, S.tiles);
     return tiled ? std::min(check, BRIEF_CHUNK) : check;
 }
 
@@ -990,7 +1051,12 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
         if (a.p != b.p) return a.p < b.p;
         return a.sub < b.sub;
     });
-    std::vector<int2> wm, wms, wr, wv, wb;
+    std::vector<int2> wm, wms, wb;
+    auto add = [](DssSide& S, const W& w) {
+        S.host.push_back(make_int2(w.p, w.sub));
+        S.max_k = std::max(S.max_k, w.k);
+        S.tiles += (w.k + VT_TILE - 1) / VT_TILE;
+    };
     size_t lds_sb = 0, lds_db = 0, lds_small_sb = 0, lds_small_db = 0;
     for (const W& w : all) {
         B->all.push_back(make_int2(w.p, w.sub));
@@ -1000,10 +1066,7 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
             wb.push_back(make_int2(w.p, w.sub));
             continue;
         }
-        wv.push_back(make_int2(w.p, w.sub));
-        B->max_k_valu = std::max(B->max_k_valu, w.k);
-        const int64_t vt = (w.k + VT_TILE - 1) / VT_TILE;
-        B->vt_valu += vt;
+        add(B->valu, w);
         if (mfma_runs_sub(Q, w.sub)) {
             const size_t need = Q->mfma_need[w.sub];
             // Each launch reserves the largest need of its members; with two Q'
@@ -1020,9 +1083,7 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
                 if (need_db <= MFMA_LDS_LIMIT) lds_db = std::max(lds_db, need_db);
             }
         } else {
-            wr.push_back(make_int2(w.p, w.sub));
-            B->max_k_rest = std::max(B->max_k_rest, w.k);
-            B->vt_rest += vt;
+            add(B->rest, w);
         }
     }
     B->lds_mfma = std::max(lds_sb, lds_db);
@@ -1030,15 +1091,15 @@ int build_batch(ddmgnn_ctx* ctx, ddmgnn_problem* const* probs, int n, BatchPtr& 
     hipStream_t s = ctx->stream;
     if (int rc = upload_list(B->work_mfma, wm, s)) return rc;
     if (int rc = upload_list(B->work_mfma_small, wms, s)) return rc;
-    if (int rc = upload_list(B->work_rest, wr, s)) return rc;
-    if (int rc = upload_list(B->work_valu, wv, s)) return rc;
+    for (DssSide* S : {&B->valu, &B->rest}) {
+        if (int rc = upload_list(S->work, S->host, s)) return rc;
+        S->n = (int)S->host.size();
+    }
     if (int rc = upload_list(B->work_big, wb, s)) return rc;
     if (int rc = upload_list(B->vec_blk, vec, s)) return rc;
     if (int rc = upload_list(B->coarse_rows, rows, s)) return rc;
     B->n_mfma = (int)wm.size();
     B->n_mfma_small = (int)wms.size();
-    B->n_rest = (int)wr.size();
-    B->n_valu = (int)wv.size();
     B->n_big = (int)wb.size();
     B->n_vec = (int)vec.size();
     B->n_coarse = (int)rows.size();
@@ -1207,14 +1268,36 @@ size_t tile_bytes(const TileCount& n, bool f64) {
            (size_t)(n.tiles * VT_TILE + 1) * 4 * D * e;
 }
 
-// The same for a problem that has not listed its tiles: a tile has at most 15 empty
-// lanes per sub-mesh, and its edge rows at most one more than its nodes' largest
-// in-degree, which its nodes (by decreasing in-degree) have but for the last few.
-size_t tile_bytes_bound(const HostSetup& hs, bool f64) {
-    TileCount n;
-    n.tiles = hs.sk / VT_TILE + hs.K;
-    n.rows = hs.n_edges / VT_TILE + 3 * n.tiles;
-    return tile_node_bytes(n.tiles, hs.sk, hs.K) + tile_bytes(n, f64);
+// Bytes of what the forward of a model of width d allocates for a problem (prepare_dss), in
+// tiles where it runs them or not; hs after prepare_upload.
+size_t forward_bytes(const HostSetup& hs, int d, int precision, bool tiles) {
+    const bool bf16 = precision == DDMGNN_BF16, f64 = precision == DDMGNN_FP64;
+    const size_t e = f64 ? 8 : 4, sk = (size_t)hs.sk;
+    bool q = hs.has_big, h = hs.has_big;  // of every slot: sender rows, states
+    int max_k = 0;
+    for (int32_t i = 0; i < hs.K; ++i) {
+        const int k = (int)(hs.sub_ptr[i + 1] - hs.sub_ptr[i]);
+        if (k <= kMaxSubNodes && !(bf16 && d <= D && hs.mfma_need[i] <= MFMA_LDS_LIMIT)) max_k = std::max(max_k, k);
+    }
+    size_t b = hs.has_big ? 8 * sk : 0;
+    if (max_k > 0) {
+        TileCount rest;
+        const TileCount all = for_tiles(hs, hs.mfma_need, rest, [](int32_t, int64_t, int64_t, int64_t) {});
+        const TileCount& n = bf16 ? rest : all;
+        if (tiles && runs_tiled(d, f64 ? DDMGNN_FP64 : DDMGNN_FP32, n.tiles)) {
+            b += tile_node_bytes(all.tiles, hs.sk, hs.K) + tile_bytes(n, f64);
+        } else {
+            q = q || !valu_q_in_lds(max_k, f64 ? DDMGNN_FP64 : DDMGNN_FP32, d);
+            h = h || f64;
+        }
+    }
+    return b + (q ? sk * 2 * d * e : 0) + (h ? sk * d * e : 0);
+}
+
+// Bytes of the coarse level's scratch beyond the direction ring (create_problem).
+size_t coarse_scratch_bytes(int64_t n, int32_t K) {
+    const size_t need = coarse_scratch_doubles(K);
+    return (size_t)2 * (MAX_M + 1) * n < need ? 8 * need : 0;
 }
 
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t ne) {
@@ -1444,7 +1527,7 @@ int create_problem(ddmgnn_ctx* ctx, const ddmgnn_problem_desc& desc, std::shared
     HIP_TRY(P->partials.alloc((size_t)N_PART * VEC_GRID));
     HIP_TRY(hipMemsetAsync(P->st.p, 0, sizeof(KState), s));
     HIP_TRY(hipStreamSynchronize(s));
-    P->device_bytes = problem_device_bytes(n, hs.nnz, K, sk, hs.n_edges);
+    P->device_bytes = problem_device_bytes(n, hs.nnz, K, sk, hs.n_edges) + P->coarse_scratch.n * sizeof(double);
     // host copies of the uploaded arrays are not needed again
     HostSetup& h = P->hs;
     std::vector<int32_t>().swap(h.sp32);
@@ -1869,6 +1952,7 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
     HIP_TRY(launch_set_view(B.hook.p, v, s));
     const ModelDev& M = *B.model;
     const int vprec = precision == DDMGNN_BF16 ? DDMGNN_FP32 : precision;
+    const DssSide& S = precision == DDMGNN_BF16 ? B.rest : B.valu;
     if (k > kMaxSubNodes) {
         HIP_TRY(launch_dss_big(B.hook.p, P->one_work.p, 1, vprec, M.d, M.kbar, M.alpha, 0, M.theta32.p,
                                M.theta64.p, s, true));
@@ -1876,7 +1960,7 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
         DssMfmaArgs a{B.hook.p, P->one_work.p, M.steps.p, M.dec.p, M.kbar, (float)M.alpha, 0};
         const size_t shmem = P->mfma_need_db[sub] <= MFMA_LDS_LIMIT ? P->mfma_need_db[sub] : P->mfma_need[sub];
         HIP_TRY(launch_dss_mfma(a, 1, shmem, MFMA_BLOCK, s, true));
-    } else if (runs_tiled(M.d, vprec, precision == DDMGNN_BF16 ? B.vt_rest : B.vt_valu)) {  // as prepare_dss
+    } else if (runs_tiled(M.d, vprec, S.tiles) && !P->untiled) {  // as prepare_dss
         std::vector<int4> tl;
         for (int32_t t = P->vt_first[sub], e = t + sub_tiles(P, sub); t < e; ++t)
             tl.push_back(make_int4(0, t, P->vt_tiles[t].z, P->vt_tiles[t].w));
@@ -1888,10 +1972,9 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
             HIP_TRY(launch_dss_tiles<float>(B.hook.p, P->one_work.p, 1, P->one_tiles.p, (int)tl.size(), true, M.kbar,
                                             M.alpha, 0, M.vt32.p, s, true));
     } else {
-        const int mk = precision == DDMGNN_BF16 ? B.max_k_rest : B.max_k_valu;  // as prepare_dss sized it
-        const bool qlds = valu_q_in_lds(mk, vprec, M.d);
+        const bool qlds = valu_q_in_lds(S.max_k, vprec, M.d);  // as prepare_dss sized it
         HIP_TRY(launch_dss_valu(B.hook.p, P->one_work.p, 1, vprec, M.d, qlds, M.kbar, M.alpha, 0, M.theta32.p,
-                                M.theta64.p, qlds ? valu_shmem(mk, vprec, M.d) : 0, s, true));
+                                M.theta64.p, qlds ? valu_shmem(S.max_k, vprec, M.d) : 0, s, true));
     }
     HIP_TRY(hipMemcpyAsync(out, P->fwd_out.p + base, (size_t)k * sizeof(double), hipMemcpyDeviceToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));

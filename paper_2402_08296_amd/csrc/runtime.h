@@ -106,11 +106,13 @@ using BatchPtr = std::unique_ptr<Batch, BatchDeleter>;
 size_t problem_device_bytes(int64_t n, int64_t nnz, int32_t K, int64_t sk, int64_t n_edges);
 // Bytes counted for the exact local solves.
 size_t lu_bytes(const HostSetup& hs);
-// Bytes of the nodes of a problem's tiles, of the tiled forward's arrays in one precision,
-// and an estimate of both before the tiles are listed.
+// Bytes of the nodes of a problem's tiles, and of the tiled forward's arrays in one precision.
 size_t tile_node_bytes(int64_t tiles, int64_t sk, int32_t K);
 size_t tile_bytes(const TileCount& n, bool f64);
-size_t tile_bytes_bound(const HostSetup& hs, bool f64);
+// What a solve allocates beyond those: the forward, in tiles or with one workgroup per
+// sub-mesh, and the coarse level's scratch.
+size_t forward_bytes(const HostSetup& hs, int d, int precision, bool tiles);
+size_t coarse_scratch_bytes(int64_t n, int32_t K);
 
 // Creates a problem from a validated descriptor and its host setup (moved in).
 // Fills the device-ready host arrays of hs (plain host work; "" or an error).
@@ -223,6 +225,7 @@ struct ddmgnn_problem {
     int2* vt_node = nullptr;
     ddmgnn::VtBufs<double> vt64;
     ddmgnn::VtBufs<float> vt32;
+    bool untiled = false;                  // one workgroup per sub-mesh instead: the arrays do not fit
     ddmgnn::DevBuf<int4> one_tiles;        // tiles of the one-sub-mesh forward entry
     // apply buffers
     ddmgnn::DevBuf<double> s, y0, y, local;

@@ -43,6 +43,7 @@ struct Request {
     int setup_rc = DDMGNN_OK;
     std::string err;
     size_t bytes = 0;
+    bool untiled = false;  // its tile arrays do not fit the budget
     Clock::time_point t_submit, t_setup0, t_setup1, t_admit, t_created, t_done;
     ddmgnn_problem* prob = nullptr;
     bool fresh = false;  // admitted, not initialised yet
@@ -173,11 +174,17 @@ void ddmgnn_server::setup_worker() {
             const size_t lu_b = lu ? lu_bytes(r->hs) : 0;
             r->bytes = problem_device_bytes(r->hs.n, r->hs.nnz, r->hs.K, r->hs.sk, r->hs.n_edges) + lu_b +
                        (r->opts.krylov == DDMGNN_FGMRES ? fgmres_bytes(r->hs.n, r->opts.restart) : 0);
-            // The FP64 and FP32 forward's work arrays count too, but a request that fits
-            // the budget without them is still taken: it then runs alone.
-            if (!lu && r->opts.krylov != DDMGNN_CG && r->opts.precision != DDMGNN_BF16 &&
-                model->d == D && r->bytes <= budget)
-                r->bytes = std::min<size_t>(budget, r->bytes + tile_bytes_bound(r->hs, r->opts.precision == DDMGNN_FP64));
+            // Work arrays count too, but a request that fits the budget without them is taken:
+            // without tiles if they are too large, and alone if what is left still is.
+            if (r->bytes <= budget) {
+                auto with = [&](bool tiles) {
+                    const bool gnn = !lu && r->opts.krylov != DDMGNN_CG;
+                    return r->bytes + coarse_scratch_bytes(r->hs.n, r->hs.K) +
+                           (gnn ? forward_bytes(r->hs, model->d, r->opts.precision, tiles) : 0);
+                };
+                r->untiled = with(true) > budget && with(false) < with(true);
+                r->bytes = std::min(budget, with(!r->untiled));
+            }
         }
         r->t_setup1 = Clock::now();
         std::lock_guard<std::mutex> lk(mu);
@@ -273,6 +280,7 @@ void ddmgnn_server::gpu_loop() {
             }
             P->rtol = r->opts.rtol;
             P->max_it = r->opts.max_it;
+            P->untiled = r->untiled;
             r->prob = P;
             r->fresh = true;
             incoming.push_back(r);

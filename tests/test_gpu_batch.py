@@ -324,3 +324,86 @@ def test_short_and_long_graphs_agree(ctx, mix, check_every):
         a = prob.solve(u, dg.default_opts(graph=1, **o), check=False)
         b = eager.solve(v, dg.default_opts(graph=0, **o), check=False)
         assert a.iterations == b.iterations and a.status == b.status and torch.equal(u, v), max_it
+
+
+def _fresh(ctx, hp, model):
+    """A problem, its device bytes, and the device memory that creating it takes (its arrays lie in
+    whole pages, which the bytes do not count)."""
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    prob = dg.Problem(ctx, hp, model)
+    return prob, prob.device_bytes(), free - torch.cuda.mem_get_info()[0]
+
+
+def _serve(model, hp, opts, budget):
+    """(rc, stats, u, device memory taken at most) of a served request: the second of two, since
+    the first also has the runtime set up its queue's scratch."""
+    srv = dg.Server(dg.Context(torch.cuda.Stream()), model, hbm_budget=int(budget), max_active=4)
+    for _ in range(2):
+        torch.cuda.synchronize()
+        free = least = torch.cuda.mem_get_info()[0]
+        t = srv.submit(hp, opts)
+        done = None
+        while done is None:
+            least = min(least, torch.cuda.mem_get_info()[0])
+            done = srv.poll(t)
+    srv.close()
+    return (*done, free - least)
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_server_budget_below_the_tile_arrays(ctx, prec):
+    """A request that fits the budget but for the arrays of the forward in tiles is taken, stays
+    within the budget (its forward runs one workgroup per sub-mesh: in FP32 with the bits of
+    the solve in tiles, in FP64 with another order of sums), and with room for the arrays has
+    the solo bits."""
+    print(f"[gpu] served {prec}, budget below the tile arrays", flush=True)
+    model = dg.Model(ctx, SMOOTHER)
+    p = W.make_problem(221, 150_000, 280, 0.2)
+    hp = oracle_problem(p)
+    opts = dg.default_opts(precision=prec, rtol=1e-6, max_it=3000)
+    prob, base, held = _fresh(ctx, hp, model)
+    solo = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    it = prob.solve(solo, opts).iterations
+    full = prob.device_bytes()
+    prob.close()
+    solo = solo.cpu().numpy()
+    assert full > base + (100 if prec == "fp64" else 50) * 2 ** 20
+    slack = 16 * 2 ** 20  # the work arrays' and the batch lists' pages
+    for budget, same in ((base + (60 if prec == "fp64" else 2) * 2 ** 20, prec == "fp32"), (full + 2 ** 20, True)):
+        rc, st, u, used = _serve(model, hp, opts, budget)
+        print(f"[gpu]   budget {budget / 1e6:.0f} MB: rc={rc} iterations {st.iterations} ({it}), used {used / 1e6:.0f} MB", flush=True)
+        assert rc == 0 and st.converged and abs(st.iterations - it) <= 1
+        assert used <= held + (budget - base) + slack
+        assert np.array_equal(u, solo) == same
+        assert np.linalg.norm(u - solo) <= 1e-5 * np.linalg.norm(solo)
+
+
+@pytest.mark.timeout(300)
+def test_server_counts_the_bf16_remainder(ctx):
+    """BF16 requests whose sub-meshes are beyond the matrix-core kernel's LDS run the FP32
+    forward: its arrays count, and a budget below them is kept."""
+    print("[gpu] served BF16 remainder", flush=True)
+    model = dg.Model(ctx, SMOOTHER)
+    p = W.make_problem(222, 200_000, 4, 0.2)
+    hp = oracle_problem(p)
+    nodes = np.argsort(p.mesh.dirichlet, kind="stable")
+    sp = np.append(np.arange(0, p.n, 1990), p.n)
+    for a, b in zip(sp[:-1], sp[1:]):
+        nodes[a:b].sort()
+    hp = dg.HostProblem(hp.xy, hp.tri, hp.dirichlet, hp.rowptr, hp.col, hp.val, hp.b, hp.u0, sp, nodes,
+                        np.where(p.mesh.dirichlet[nodes], 0.0, 1.0))
+    opts = dg.default_opts(precision="bf16", rtol=1e-2, max_it=40)
+    prob, base, held = _fresh(ctx, hp, model)
+    solo = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    st = prob.solve(solo, opts, check=False)
+    full = prob.device_bytes()
+    prob.close()
+    print(f"[gpu]   kernel {st.dss_kernel}, {base / 1e6:.0f} MB, with tiles {full / 1e6:.0f} MB", flush=True)
+    assert st.dss_kernel in (1, 4) and full > base + 40 * 2 ** 20
+    budget = base + 2 ** 20
+    rc, served, u, used = _serve(model, hp, opts, budget)
+    print(f"[gpu]   budget {budget / 1e6:.0f} MB: used {used / 1e6:.0f} MB", flush=True)
+    assert rc == st.status and served.iterations == st.iterations
+    assert used <= held + (budget - base) + 16 * 2 ** 20 and np.array_equal(u, solo.cpu().numpy())
