@@ -455,8 +455,7 @@ int prepare_tiles(ddmgnn_problem* P, VtBufs<T>& V, const TileCount& n, DevBuf<De
     if (V.mem.p && V.n.tiles >= n.tiles) return DDMGNN_OK;
     hipStream_t s = P->ctx->stream;
     const int64_t nt = n.tiles, rows = n.rows + VT_ROWS;
-    if (rows * VT_TILE >= INT32_MAX || nt * VT_TILE >= INT32_MAX)
-        return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
+    if (nt * VT_TILE >= INT32_MAX) return make_untiled(P);  // tile lanes are 32-bit (edge records' offsets are not)
     hipError_t e = prepare_tile_nodes(P, hook);
     if (e == hipErrorOutOfMemory) return make_untiled(P);
     HIP_TRY(e);
@@ -560,8 +559,8 @@ int prepare_train(ddmgnn_problem* P) {
         out_rows[t] = make_int2((int)rows, deg);
         rows += deg;
     }
-    if ((rows + VT_ROWS) * VT_TILE >= INT32_MAX || (P->vt_all.rows + VT_ROWS) * VT_TILE >= INT32_MAX)
-        return fail(DDMGNN_E_INVALID, "edge records beyond 32-bit offsets");
+    if (P->vt_all.tiles * VT_TILE >= INT32_MAX || rows + VT_ROWS >= INT32_MAX)
+        return fail(DDMGNN_E_INVALID, "tile lanes or edge rows beyond 32 bits");
     if (int rc = solo_batch(P)) return rc;
     HIP_TRY(prepare_tile_nodes(P, P->solo->hook));
     std::vector<int32_t> map;
