@@ -14,7 +14,7 @@ namespace ddmgnn {
 
 constexpr int VT_TILE = 16;   // nodes of a tile (the N dimension of the matrix instructions)
 constexpr int VT_BLOCK = 256; // threads of the setup kernels
-constexpr int64_t VT_MAX_FP32 = 48 * 1024;  // most tiles of an FP32 launch in this form
+constexpr int64_t VT_MAX_FP32 = 60 * 1024;  // most tiles of an FP32 launch in this form (runs_tiled)
 constexpr int VT_ROWS = 8;    // edge rows read at a time (the array is padded by as many)
 
 // Values per lane of one block's blob: matrix operands, then per-lane constants.

@@ -338,11 +338,13 @@ int prepare_fgmres(Batch& B, int R, bool& changed) {
 }
 
 // Whether a launch of `tiles` tiles of 16 nodes of a width-d model runs the tiled forward
-// (dss_tile.hip): every FP64 one, and the FP32 ones of up to VT_MAX_FP32 tiles. Larger FP32 launches fill the
-// chip with one workgroup per sub-mesh, whose sender rows stay in LDS, while the tiled
-// form's pass through HBM (537k slots, 34k tiles: 1,176 against 1,462 us per forward;
-// 1.35M slots, 85k tiles: 3,480 against 3,160). Both give the same bits. Other widths
-// and sub-meshes beyond kMaxSubNodes run the kernels of kernels.hip.
+// (dss_tile.hip): every FP64 one, and the FP32 ones of up to VT_MAX_FP32 tiles. Larger FP32
+// launches fill the chip with one workgroup per sub-mesh, whose sender rows stay in LDS, while
+// the tiled form's outgrow the last-level cache and pass through HBM. Per forward, one workgroup
+// per sub-mesh and tiled, sub-meshes of 900 nodes: 35k tiles 1,470 and 1,240 us, 54k 2,030 and
+// 1,870, 60k 2,530 and 2,530, 64k 2,550 and 2,680, 89k 3,590 and 3,730; of 450: 62k 2,680 and
+// 2,590, 73k 3,060 and 3,020; of 1,500: 59k 5,660 and 3,890. Both give the same bits. Other
+// widths and sub-meshes beyond kMaxSubNodes run the kernels of kernels.hip.
 bool runs_tiled(int d, int precision, int64_t tiles) {
     return d == D && (precision == DDMGNN_FP64 || tiles <= VT_MAX_FP32);
 }

@@ -171,3 +171,23 @@ def test_bf16_remainder_runs_tiled(ctx, first):
     small = sum(int(b - a) for a, b in zip(hp.sub_ptr[:-1], hp.sub_ptr[1:]) if b - a <= 2048)
     # 16 + 8 + 4 bytes per slot for the tiles' nodes, and about 300 of FP32 arrays where they are kept
     assert grown <= 20 * hp.sub_nodes.size + 400 * (rest if first == "bf16" else small) + 8192
+
+
+def test_fp32_forms_agree_beyond_60k_tiles(ctx):
+    """Copies of a 5k-node problem, enough for more tiles than an FP32 launch takes in tiles
+    (60 * 1024): one workgroup per sub-mesh gives the bits of the solo (tiled) solve."""
+    p = W.config_problem("c1", 0)
+    hp = oracle_problem(p)
+    tiles = int(((np.diff(hp.sub_ptr) + 15) // 16).sum())
+    copies = 60 * 1024 // tiles + 2
+    model = dg.Model(ctx, SMOOTHER)
+    opts = dg.default_opts(precision="fp32", rtol=1e-6, max_it=500)
+    probs = [dg.Problem(ctx, hp, model) for _ in range(copies)]
+    outs = [torch.empty(p.n, dtype=torch.float64, device="cuda") for _ in probs]
+    solo = torch.empty(p.n, dtype=torch.float64, device="cuda")
+    st = probs[0].solve(solo, opts)
+    for i in (copies, copies - 4):  # on both sides of the line
+        print(f"[gpu] {i * tiles} tiles", flush=True)
+        assert (i * tiles > 60 * 1024) == (i == copies)
+        for s, u in zip(dg.solve_batch(ctx, probs[:i], outs[:i], opts), outs):
+            assert s.converged and s.iterations == st.iterations and torch.equal(u, solo)
