@@ -1940,7 +1940,7 @@ int ddmgnn_dss_forward_sub(ddmgnn_ctx* ctx, ddmgnn_problem* P, int32_t precision
     if (int rc = prepare_dss(B, precision, changed)) return rc;
     hipStream_t s = ctx->stream;
     const int64_t base = P->hs.sub_ptr[sub], k = P->hs.sub_ptr[sub + 1] - base;
-    if (!P->fwd_in.p) {
+    if (!P->one_work.p) {  // the last of them: a failed build is retried whole
         HIP_TRY(P->fwd_in.alloc((size_t)P->hs.sk));
         HIP_TRY(P->fwd_out.alloc((size_t)P->hs.sk));
         HIP_TRY(P->one_work.alloc(1));
