@@ -741,7 +741,10 @@ def main():
     g_local, g_coarse, g_glue = prob.time_apply_stages(r0, zt, opts, reps=20)
     log(f"apply stages (graph replay): local {g_local * 1e3:.1f} us, coarse {g_coarse * 1e3:.1f} us, "
         f"glue {g_glue * 1e3:.1f} us")
-    dss_kernel = {0: "dss_block_kernel<double>", 1: "dss_kernel<float>", 2: "dss_mfma_kernel<1024>"}[sp.dss_kernel]
+    k = np.diff(prob.hp.sub_ptr)
+    tiled = int(((k[k <= 2048] + 15) // 16).sum()) <= 60 * 1024  # FP32: the form a launch of these tiles takes
+    dss_kernel = {0: "dss_block_kernel<double>", 1: "dss_block_kernel<float>" if tiled else "dss_kernel<float>",
+                  2: "dss_mfma_kernel<1024>"}[sp.dss_kernel]
     if sp.dss_kernel == 2 and prob.tuning().small_lds > 0:
         dss_kernel += "+dss_mfma_kernel<512>"  # sub-meshes split over the two workgroup sizes
     n_it = max(1, sp.dss_launches)

@@ -181,8 +181,9 @@ typedef struct {
                           * iteration is many launches and solves are short, of four
                           * (ignored when profile = 1) */
     int32_t local_solver;/* DDMGNN_LOCAL_GNN, or DDMGNN_LOCAL_LU: exact local solves with the
-                          * inverses of R_i A R_i^T (FP64, one triangle in 64 x 64 tiles; counted
-                          * as sum k_i^2 doubles of device memory), assembled and inverted on
+                          * inverses of R_i A R_i^T (FP64, one triangle in 64 x 64 tiles, or
+                          * squares of small sub-meshes; counted as sum k_i^2 doubles of device
+                          * memory), assembled and inverted on
                           * the device at the problem's first LU use (E_NOT_SPD when a pivot is
                           * not positive) */
     int32_t restart;     /* FGMRES: steps per cycle, 1..64 (30); the problem keeps

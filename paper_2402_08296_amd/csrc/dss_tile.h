@@ -38,7 +38,7 @@ struct VtLayout<double> {
 template <>
 struct VtLayout<float> {
     // as above, with the second message layers (FO, FI) and the coordinate weights (WX, WY)
-    static constexpr int P16 = 0, P4 = 3, FO = 6, FI = 9, HID = 12, N_HID = 9, OUT = 21;
+    static constexpr int P16 = 0, P4 = 3, FO = 6, FI = 9, HID = 12, OUT = 21;
     static constexpr int CP = 24, CP4 = 28, WX = 29, WY = 34, WN = 39, CCO = 44, CCI = 47, CH = 50, CO = 53,
                          N_MAIN = 56;
     static constexpr int Q16 = 0, Q4 = 3, QX = 6, QY = 11, N_Q = 16;

@@ -1,22 +1,26 @@
-// VALU kernels of the DDM-GNN apply and of the Krylov iteration, all table
-// driven (one launch serves every problem of a batch).
+// Kernels of the DDM-GNN apply outside the matrix-core forwards, and of the Krylov
+// iteration, all table driven (one launch serves every problem of a batch).
 //
-// One preconditioner apply (Sec. III.A) is three launches:
-//   DSS forward     one workgroup per sub-mesh, largest first. Restricts the
-//                   residual (s_i = |R_i r|, y0_i = (R_0 r)_i, c_i = R_i r / s_i)
-//                   and runs the kbar DSS_theta blocks (Sec. III.B); writes
-//                   s_i r~_i per slot. This file holds the FP64/FP32 VALU
-//                   form; dss_mfma.hip the BF16 matrix-core form.
+// One preconditioner apply (Sec. III.A):
+//   local solves    restrict the residual (s_i = |R_i r|, y0_i = (R_0 r)_i,
+//                   c_i = R_i r / s_i), run the kbar DSS_theta blocks (Sec. III.B) and write
+//                   s_i r~_i per slot. In BF16 one or two launches, a workgroup per
+//                   sub-mesh, largest first (dss_mfma.hip); in FP64 and FP32 at width 10 a
+//                   restriction and a launch per block over tiles of 16 nodes
+//                   (dss_tile.hip). This file holds the one-launch FP64 / FP32 form, a
+//                   workgroup per sub-mesh, of other widths, large FP32 launches, problems
+//                   without tile arrays and sub-meshes beyond 2048 nodes, and the exact
+//                   solves of DDM-LU.
 //   coarse_kernel   y = (R_0 A R_0^T)^{-1} y0 as a GEMV with the inverse
 //                   formed at setup (step 1).
 //   prolong_kernel  z(n) = sum over the sub-meshes holding n of
 //                   w_i(n) s_i r~_i(n) + D_i(n) y_i; z = 0 at Dirichlet nodes
 //                   (step 3), fused with the Krylov dot products that need z.
 // The Krylov iteration adds the direction update with the SpMV and its dots,
-// and the solution update with the convergence test. Every reduction writes
-// one partial sum per workgroup; a finalize kernel with one workgroup per
-// problem sums them in workgroup order and advances the scalar recurrences
-// (alpha, beta, the test) on the device, so the host only polls a flag.
+// and the solution update. Every reduction writes one partial sum per workgroup; the
+// kernel that uses a sum (beta in the SpMV, alpha in the update) adds them in workgroup
+// order itself, and a finalize kernel with one workgroup per problem keeps the problem's
+// state and the convergence test on the device, so the host only polls a flag.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
