@@ -6,7 +6,7 @@
 // group l / 16 of lane l, five message units and three latent components per
 // lane), one launch per block. One workgroup per sample, as before, left the chip
 // to as many compute units as samples and every phase to global-memory latency:
-// 18.6 ms for 100 samples of 900 nodes, and the same for 17; now 2.04 and 0.88 ms.
+// 17.8 ms for 100 samples of 900 nodes, and the same for 17; now 2.00 and 0.89 ms.
 //   forward    block b: message sums, Psi, H^{b+1}, the next sender rows, and the
 //              decoded state r of H^{b+1}; every block's state, sums and sender
 //              rows are kept.
